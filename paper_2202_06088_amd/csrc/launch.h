@@ -17,7 +17,7 @@ struct TraceArgs {
     int4* smp;                     // [cap][2] (32-byte entries). K = 16, C = 8 form, one entry per sample:
                                    // {leaf, delta, x, c_r} {c_g, c_b, next (-1: last), 0}; per-point form,
                                    // two: {leaf, delta, x, y} {c_r, c_g, c_b, next} {dz/dgamma [3], 0} {-}
-    unsigned long long* counter;   // kQueues counters 128 bytes apart: the first 1024 bytes of a 2048-byte
+    unsigned long long* counter;   // samples handed out (take_items), in the first 1024 bytes of a 2048-byte
                                    // header whose second half takes the stores of samples without a slot
     int64_t cap;
 };
@@ -57,7 +57,7 @@ struct RecordArgs {
                                    //           {next record of the same leaf (-1: end), ray, 0, 0};
                                    // K = 16, C = 8 form with one time for every ray: {next, ray
                                    // direction (world, float bits)} instead
-    unsigned long long* counter;   // records handed out so far, one counter per XCD part of the room
+    unsigned long long* counter;   // records handed out so far (take_items)
     unsigned long long* leaf_cursor;   // second pass: leaves handed out so far
     int64_t cap;
 };

@@ -257,7 +257,7 @@ static __global__ void zero_queue_kernel(unsigned long long* q) { q[threadIdx.x]
 // write the miss outputs of the others. MODE 1 (adjoint): keep the rays whose
 // forward composited a sample (the others carry no gradient); MODE 2 and 3
 // (adjoint of a traced forward): of those, the rays without a trace (head
-// < 0, none when out.trace's counters show that every request for trace
+// < 0, none when out.trace's counter shows that every request for trace
 // room was met) and the rays with one. MODE 4: keep the rays hit.keep(ray) accepts
 // and write the miss outputs of the others (no ray loads). The
 // pass is bound by the 24 bytes of ray per slot it reads; at high occupancy
@@ -286,18 +286,10 @@ static __global__ __launch_bounds__(kBlock) void cull_kernel(Hit hit, RayArgs ra
                                                               int32_t* list,
                                                               unsigned long long* count) {
     if constexpr (MODE == 2) {
-        // After a traced forward, out.trace holds its allocation counters and the
-        // room in samples. A trace is incomplete only where a block request of its
-        // XCD part went past the part's end; with none, no ray walks.
-        if (out.trace.counter) {
-            bool over = false;
-#pragma unroll
-            for (int p = 0; p < kQueues; ++p) {
-                const int64_t part = out.trace.cap * (p + 1) / kQueues - out.trace.cap * p / kQueues;
-                over = over || (int64_t)out.trace.counter[p * kQueueStride] > part;
-            }
-            if (!over) return;
-        }
+        // After a traced forward, out.trace holds its allocation counter and the
+        // room in samples. A trace is incomplete only if a block request went past
+        // the room's end; with none, no ray walks.
+        if (out.trace.counter && (int64_t)*out.trace.counter <= out.trace.cap) return;
     }
     const int lane = threadIdx.x & 63;
     const int x = (int)(blockIdx.x & (kQueues - 1));
@@ -510,8 +502,6 @@ static hipError_t with_candidates(const TreeArgs& tr, const InstArgs& in, const 
 // ----------------------------------------------------------------------------
 // records of the two-phase adjoint (see RecordArgs)
 
-// records a wavefront takes from its XCD's counter at a time
-constexpr int kRecBlock = 2048;
 // LDS rows per wavefront for the transposition of finished leaf rows
 constexpr int kFlushSlots = 16;
 
@@ -519,29 +509,45 @@ static __global__ void record_init_kernel(int32_t* head, int64_t n, unsigned lon
                                           unsigned long long* leaf_cursor) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) head[i] = -1;
-    if (i < kQueues) counter[i * kQueueStride] = 0ull;
-    if (i == 0) *leaf_cursor = 0ull;
+    if (i == 0) *counter = *leaf_cursor = 0ull;
 }
 
-// Wave-uniform allocation of n (<= kRecBlock) consecutive items from blocks of
-// kRecBlock taken from one counter per XCD; XCD x owns items
-// [cap x / kQueues, cap (x + 1) / kQueues). [cur, end) is what is left of the
-// wavefront's current block. Returns the first item, or -1 when the XCD's
-// part is exhausted. Call with every lane of the wavefront active.
-__device__ __forceinline__ int take_items(unsigned long long* counter, int64_t cap, int home, int n, int& cur,
-                                          int& end) {
+// Items a wavefront takes from the room's counter at a time: a 16,384th of the
+// room, between 128 (the most that one iteration of a wavefront asks for) and
+// 2048. The rest of a wavefront's last block stays unused, so the block is kept
+// small against the room's share per wavefront; the floor of 16,384 blocks also
+// bounds the atomics on the one counter (12 thousand on the 16.6 M-ray ring).
+// Blocks of 2048 from one counter per XCD left 38 % of the ring's trace room
+// unused and, in rooms below 2 M items, let 8 wavefronts per XCD exhaust it: the
+// rays left over were walked again (65,536 training rays with room for two
+// samples each: 222 us of 717 us; 4 layers at 1920 x 1080: 1462 us of 4247 us).
+__device__ __forceinline__ int item_block(int64_t cap) {
+    const int b = (int)(cap >> 14);
+    return b < 128 ? 128 : (b > 2048 ? 2048 : b);
+}
+
+// Wave-uniform allocation of n (<= 128) consecutive items of a room of cap
+// items, out of blocks taken from its counter. [cur, end) is what is left of
+// the wavefront's current block, end = -1 once the room is exhausted. Returns
+// the first item, or -1 when there is no room. A request that fails has left
+// the counter above cap. Call with every lane of the wavefront active.
+__device__ __forceinline__ int take_items(unsigned long long* counter, int64_t cap, int n, int& cur, int& end) {
     if (cur + n > end) {
-        const int64_t lo = cap * home / kQueues, hi = cap * (home + 1) / kQueues;
+        if (end < 0) return -1;
+        const int block = item_block(cap);
         unsigned long long b = 0;
-        if ((threadIdx.x & 63) == 0) b = atomicAdd(counter + home * kQueueStride, (unsigned long long)kRecBlock);
+        if ((threadIdx.x & 63) == 0) b = atomicAdd(counter, (unsigned long long)block);
         const uint32_t b_lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b);
         const uint32_t b_hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32));
-        const int64_t first = lo + (int64_t)(((uint64_t)b_hi << 32) | b_lo);
-        // the room is below 2^31 items, so the block's bounds fit int32 once clamped to the part
-        cur = (int)(first < hi ? first : hi);
-        end = (int)(first + kRecBlock <= hi ? first + kRecBlock : hi);
+        const int64_t first = (int64_t)(((uint64_t)b_hi << 32) | b_lo);
+        // the room is below 2^31 items, so the block's bounds fit int32 once clamped to it
+        cur = (int)(first < cap ? first : cap);
+        end = (int)(first + block <= cap ? first + block : cap);
+        if (cur + n > end) {
+            end = -1;
+            return -1;
+        }
     }
-    if (cur + n > end) return -1;
     const int at = cur;
     cur += n;
     return at;
@@ -635,8 +641,8 @@ __device__ __forceinline__ void feed_leaves(LeafFeeder& f, const RecordArgs& rec
 }
 
 // Takes the record scratch of one adjoint launch (cap > 0) from the pool and
-// queues its initialisation: kQueues counters 128 bytes apart and a leaf
-// cursor, the leaf heads (-1) and room for cap records of 32 bytes. With
+// queues its initialisation: the counter of records and a leaf cursor,
+// the leaf heads (-1) and room for cap records of 32 bytes. With
 // cap == 0 rec stays empty (per-sample atomics only).
 static hipError_t records_begin(const TreeArgs& tr, int64_t cap, hipStream_t st, RecordArgs& rec, void*& mem) {
     rec = RecordArgs{};

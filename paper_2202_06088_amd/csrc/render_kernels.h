@@ -182,7 +182,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(min_wave
         if constexpr (TRACE) {
             const uint64_t hm = __ballot(leaf >= 0);
             const int n_s = __popcll(hm);
-            const int at = n_s > 0 ? take_items(out.trace.counter, out.trace.cap, cc.home, n_s, tcur, tend) : -1;
+            const int at = n_s > 0 ? take_items(out.trace.counter, out.trace.cap, n_s, tcur, tend) : -1;
             if (leaf >= 0) {
                 if (at >= 0 && t_first != -2) {
                     cur = (int)(at + lane_rank(hm));
@@ -328,9 +328,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(min_wave
     int ns = 0, ns_fwd = 0;
     int tnext = -1;        // replay: the ray's next sample
     float dw0 = 0.0f, dw1 = 0.0f, dw2 = 0.0f;   // the ray's direction (world), for its records
-    // records: the wavefront fills blocks of kRecBlock consecutive records,
-    // taken from its XCD's part of the room; [wrec, wend) is what is left of
-    // the current block (wave-uniform)
+    // records: the wavefront fills blocks of consecutive records (take_items);
+    // [wrec, wend) is what is left of the current block (wave-uniform)
     int wrec = 0, wend = 0;
 
     for (;;) {
@@ -486,7 +485,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(min_wave
             // the record stores of the wavefront are contiguous
             const uint64_t hm = __ballot(has);
             const int n_has = __popcll(hm);
-            const int at = n_has > 0 ? take_items(rec.counter, rec.cap, cc.home, n_has, wrec, wend) : -1;
+            const int at = n_has > 0 ? take_items(rec.counter, rec.cap, n_has, wrec, wend) : -1;
             if (at >= 0) {
                 const RecordRun run = record_run(hm, has, leaf);
                 if (has) {

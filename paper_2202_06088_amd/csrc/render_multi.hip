@@ -251,7 +251,7 @@ constexpr int64_t kMergeRoomPerRay = 2;   // list entries per ray and instance
 struct MergeLists {
     int32_t* head;                 // [n] first entry of the ray's list; -1: empty, -2: the room ran out
     int4* ent;                     // [cap][2]
-    unsigned long long* counter;   // kQueues counters, 128 bytes apart (entries handed out per XCD part)
+    unsigned long long* counter;   // entries handed out (take_items)
     int64_t cap;
 };
 
@@ -348,7 +348,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 8))) 
         const bool gap = leaf >= 0 && (pslot < 0 || df_lt(pb, a));
         const uint64_t m1 = __ballot(leaf >= 0), m2 = __ballot(gap);
         const int n_e = __popcll(m1) + __popcll(m2);
-        const int at = n_e > 0 ? take_items(ml.counter, ml.cap, cc.home, n_e, tcur, tend) : -1;
+        const int at = n_e > 0 ? take_items(ml.counter, ml.cap, n_e, tcur, tend) : -1;
         if (leaf >= 0) {
             if (at < 0) {
                 first = -2;   // the room ran out: the fused kernel renders this ray

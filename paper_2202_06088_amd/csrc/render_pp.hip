@@ -246,7 +246,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 8))) 
         if constexpr (TRACE) {
             const uint64_t hm = __ballot(leaf >= 0);
             const int n_s = __popcll(hm);
-            const int at = n_s > 0 ? take_items(out.trace.counter, t_room, cc.home, n_s, tcur, tend) : -1;
+            const int at = n_s > 0 ? take_items(out.trace.counter, t_room, n_s, tcur, tend) : -1;
             if (leaf >= 0) {
                 if (at >= 0 && t_first != -2) {
                     cur = (int)(at + lane_rank(hm));
@@ -487,7 +487,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(REPLAY ?
             // order; their leaf rows and basis gradients are summed per leaf later
             const uint64_t hm = __ballot(has);
             const int n_has = __popcll(hm);
-            const int at = n_has > 0 ? take_items(rec.counter, rec.cap, cc.home, n_has, wrec, wend) : -1;
+            const int at = n_has > 0 ? take_items(rec.counter, rec.cap, n_has, wrec, wend) : -1;
             if (at >= 0) {
                 const RecordRun run = record_run(hm, has, leaf);
                 if (has) {

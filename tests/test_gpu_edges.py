@@ -1,0 +1,47 @@
+"""GPU parity at the sizes where a kernel or a dispatch rule changes its path:
+block and room edges, remainders, smallest launches. Bars as in the other GPU
+tests: 1e-5 of the largest value for renders, 1e-4 for gradients, against the
+FP64 oracle."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_util import announce, oracle_render, rel_err, stop_ambiguous, tdev, tiny_camera, upload
+from oracle import core as OC
+from paper_2202_06088_amd import ops
+from workloads import make_scene, scene_for_workload
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def tiny():
+    """The tiny workload's view, an upstream gradient (zero where the stop test is within rounding) and its oracle."""
+    sc = scene_for_workload("tiny")
+    cam = tiny_camera(sc)
+    o, d = OC.pinhole_rays(64, 64, cam.intr(), cam.c2w)
+    g = np.random.default_rng(61).normal(size=(o.shape[0], 3)).astype(np.float32)
+    g[stop_ambiguous(oracle_render(sc, o, d, None, 4.0, 1e-4, g_rgb=g), label="tiny")] = 0.0
+    return sc, o, d, g, oracle_render(sc, o, d, None, 4.0, 1e-4, g_rgb=g)
+
+
+@pytest.mark.parametrize("records", [None, "1", "130", "4100"])
+@pytest.mark.parametrize("cap", [1, 127, 128, 129, 2000, 20_000])
+def test_room_edges(tiny, cap, records, monkeypatch):
+    """Traces and records that end inside, at and just after a block of the room: samples without room are walked
+    or scattered, and the gradients are the same."""
+    sc, o, d, g, ref = tiny
+    if records is None:
+        monkeypatch.delenv("NEUVV_BWD_RECORDS", raising=False)
+    else:
+        monkeypatch.setenv("NEUVV_BWD_RECORDS", records)
+    tree, oo, dd = upload(sc), tdev(o), tdev(d)
+    trace = ops.Trace(o.shape[0], cap, oo.device)
+    rgb, alpha, _, nsamp = ops.render(tree, oo, dd, 4.0, None, 1e-4, 64, trace=trace)
+    gl, gb = ops.render_backward(tree, oo, dd, rgb, alpha, nsamp, tdev(g), None, 4.0, None, 1e-4, 64, trace=trace)
+    torch.cuda.synchronize()
+    hh, ws = tree.unpack_grad(gl)
+    e = [rel_err(hh.cpu().numpy(), ref["grad_hh"]), rel_err(ws.cpu().numpy(), ref["grad_wsig"]),
+         rel_err(gb.cpu().numpy(), ref["grad_basis"])]
+    announce(f"cap={cap} records={records}: grad rel errors {e}")
+    assert max(e) <= 1e-4, e
