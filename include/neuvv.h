@@ -430,9 +430,9 @@ int neuvv_compose_backward(int32_t L, int64_t n_pix, const float* rgb, const flo
 /*
  * neuvv_pinhole_rays - world rays of a pinhole camera: origin = camera
  * centre, direction = normalize(R (x_c, y_c, 1)) with x_c = (u + 0.5 - cx)/fx,
- * y_c = (v + 0.5 - cy)/fy, computed in compensated float32 arithmetic and
- * rounded once (agrees with the correctly rounded result except within
- * about 2^-40 relative of a rounding boundary).
+ * y_c = (v + 0.5 - cy)/fy, computed in float64 and rounded once (agrees with
+ * the correctly rounded result except within about 2^-50 relative of a
+ * rounding boundary).
  * cam             host struct. n >= 0.
  * pix             device [n] int32 linear pixel indices v*W + u, or NULL for
  *                 all W*H pixels in row-major order (then n must be W*H).

@@ -1,7 +1,7 @@
 // Elementwise kernels around the renderer:
 //  * compose_fwd / compose_bwd: depth-aware alpha blending of L layers
 //    (Alg. 1), read as a per-pixel depth sort then premultiplied "over";
-//  * pinhole: camera rays, compensated arithmetic rounded once;
+//  * pinhole: camera rays, float64 arithmetic rounded once;
 //  * eval_hh: the per-ray HH basis on its own (Eq. 2-4), a test hook;
 //  * pack: leaf coefficients into the 16-byte-vector structure-of-arrays
 //    storage layout, with round-to-nearest-even for 16-bit storage;
@@ -201,33 +201,45 @@ struct CamArgs {
     int32_t W, H;
 };
 
+// Bound by the 24 bytes it writes per ray, in one 12-byte store each for the
+// origin and the direction (a wavefront's stores are contiguous). The arithmetic
+// is float64, rounded once. In compensated float32 pairs, with a 64-bit division
+// per pixel and 4-byte stores, it was bound by its instructions instead (76 us
+// for 2048 x 2048 rays).
+__device__ __forceinline__ void pinhole_ray(const CamArgs& cam, double ifx, double ify, int64_t u, int64_t v,
+                                            float* __restrict__ o, float* __restrict__ d) {
+    const double xc = ((double)u + 0.5 - (double)cam.intr[2]) * ifx;
+    const double yc = ((double)v + 0.5 - (double)cam.intr[3]) * ify;
+    double dv[3], n2 = 0.0;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        dv[a] = __builtin_fma((double)cam.c2w[4 * a], xc,
+                               __builtin_fma((double)cam.c2w[4 * a + 1], yc, (double)cam.c2w[4 * a + 2]));
+        n2 = __builtin_fma(dv[a], dv[a], n2);
+    }
+    // 1/sqrt(n2): hardware estimate, two Newton steps r += r (1 - n2 r^2) / 2
+    double r = __builtin_amdgcn_rsq(n2);
+#pragma unroll
+    for (int it = 0; it < 2; ++it) r = __builtin_fma(0.5 * r, __builtin_fma(-n2 * r, r, 1.0), r);
+    store3(d, (float)(dv[0] * r), (float)(dv[1] * r), (float)(dv[2] * r));
+    store3(o, cam.c2w[3], cam.c2w[7], cam.c2w[11]);
+}
+
 __global__ __launch_bounds__(kEwBlock) void pinhole_kernel(CamArgs cam, int64_t n, const int32_t* __restrict__ pix,
                                                            float* __restrict__ ray_o, float* __restrict__ ray_d) {
+    const double ifx = rcp64((double)cam.intr[0]), ify = rcp64((double)cam.intr[1]);
     for (int64_t i = blockIdx.x * (int64_t)kEwBlock + threadIdx.x; i < n; i += (int64_t)gridDim.x * kEwBlock) {
         const int64_t p = pix ? (int64_t)pix[i] : i;
-        const int64_t v = p / cam.W, u = p - v * cam.W;
-        // x_c = (u + 0.5 - cx) / fx, y_c = (v + 0.5 - cy) / fy: u + 0.5 is exact below 2^23
-        const df xc = df_div(df_two_sum((float)u + 0.5f, -cam.intr[2]), df_from(cam.intr[0]));
-        const df yc = df_div(df_two_sum((float)v + 0.5f, -cam.intr[3]), df_from(cam.intr[1]));
-        df dv[3];
-        df n2 = df_from(0.0f);
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            df s = df_add(df_mul_f(xc, cam.c2w[4 * a]), df_mul_f(yc, cam.c2w[4 * a + 1]));
-            dv[a] = df_add(s, df_from(cam.c2w[4 * a + 2]));
-            n2 = df_add(n2, df_mul(dv[a], dv[a]));
+        int64_t u, v;
+        if ((uint64_t)p < (1ull << 32)) {   // a 32-bit division is a quarter of a 64-bit one
+            const uint32_t row = (uint32_t)p / (uint32_t)cam.W;
+            v = row;
+            u = (uint32_t)p - row * (uint32_t)cam.W;
+        } else {
+            v = p / cam.W;
+            u = p - v * cam.W;
         }
-        // 1/sqrt(n2): float estimate refined by two compensated Newton steps r += r (1 - n2 r^2) / 2
-        df r = df_from(1.0f / sqrtf(n2.hi));
-        for (int it = 0; it < 2; ++it) {
-            const df e = df_sub(df_from(1.0f), df_mul(n2, df_mul(r, r)));
-            r = df_add(r, df_mul_f(df_mul(r, e), 0.5f));
-        }
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            ray_d[3 * i + a] = df_f(df_mul(dv[a], r));
-            ray_o[3 * i + a] = cam.c2w[4 * a + 3];
-        }
+        pinhole_ray(cam, ifx, ify, u, v, ray_o + 3 * i, ray_d + 3 * i);
     }
 }
 

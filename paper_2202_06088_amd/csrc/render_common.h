@@ -205,19 +205,6 @@ __device__ __forceinline__ bool no_candidates(const RayArgs& ra) {
     return total == 0;
 }
 
-// 12-byte vector access to a ray's origin or direction, or a pixel's colour
-// (one dwordx3 memory instruction instead of three).
-typedef float f3v __attribute__((ext_vector_type(3)));
-__device__ __forceinline__ f3v load3(const float* p) {
-    f3v v;
-    __builtin_memcpy(&v, p, 12);
-    return v;
-}
-__device__ __forceinline__ void store3(float* p, float x, float y, float z) {
-    const f3v v = {x, y, z};
-    __builtin_memcpy(p, &v, 12);
-}
-
 __device__ __forceinline__ void write_miss(const RenderOut& out, int64_t ray) {
     if (out.rgb) store3(out.rgb + 3 * ray, 0.0f, 0.0f, 0.0f);
     if (out.alpha) out.alpha[ray] = 0.0f;

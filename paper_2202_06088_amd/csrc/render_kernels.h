@@ -121,7 +121,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(min_wave
             // Acquisition: idle lanes take the next slots; rays the plain-float
             // test rejects get their miss outputs at once and the lane takes
             // another slot, while at least refill_min lanes are idle. Then the
-            // compensated setup runs once for all accepted rays together.
+            // setup runs once for all accepted rays together.
             bool cand = false;
             float o[3], d[3], t = 0.0f;
             for (;;) {

@@ -10,7 +10,7 @@
 // next boundary of any instance (optical depth sum kappa_k du over the
 // instances covering it, colour the kappa-weighted mean of theirs; Eq. 8),
 // and fetches the next segment of every instance whose segment ended there.
-// Boundaries are compensated ray parameters, so every interval length keeps
+// Boundaries are float64 ray parameters, so every interval length keeps
 // float32 relative accuracy.
 //
 // Two forms compute this. The two-phase form (below the fused kernel) first
@@ -35,7 +35,7 @@
 namespace neuvv {
 
 struct MSeg {
-    df a, b;                  // current segment [a, b) in the ray parameter
+    double a, b;              // current segment [a, b) in the ray parameter
     float kap, c0, c1, c2;    // extinction per unit u, colour
     bool has;                 // a segment is held (false: the instance has no more)
 };
@@ -44,7 +44,7 @@ struct MSeg {
 template <int DT>
 __device__ __forceinline__ void fetch_segment(const TreeArgs& tr, const RaySetup& rs, Walk& w, MSeg& sg) {
     float delta, umid;
-    df a, b;
+    double a, b;
     const int leaf = walk_next(tr, rs, w, delta, umid, a, b);
     if (leaf < 0) {
         sg.has = false;
@@ -101,7 +101,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(L <= 3 ?
     RaySetup rs[L];
     Walk w[L];
     MSeg sg[L];
-    df u = df_from(0.0f);     // current position
+    double u = 0.0;     // current position
     float Tr = 1.0f, acc0 = 0.0f, acc1 = 0.0f, acc2 = 0.0f, wsum = 0.0f, dsum = 0.0f, dlen = 0.0f;
     int ns = 0;
 
@@ -154,7 +154,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(L <= 3 ?
                     bool first = true;
 #pragma unroll
                     for (int k = 0; k < L; ++k)
-                        if (sg[k].has && (first || df_lt(sg[k].a, u))) { u = sg[k].a; first = false; }
+                        if (sg[k].has && (first || (sg[k].a < u))) { u = sg[k].a; first = false; }
                     alive = true;
                 } else {
                     write_miss(out, ray);
@@ -165,15 +165,15 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(L <= 3 ?
         if (n_idle == kWave) break;
         if (alive) {
             // next boundary of any instance, and the instances covering [u, nb)
-            df nb = df_from(0.0f);
+            double nb = 0.0;
             bool have_nb = false;
             float ksum = 0.0f, kc0 = 0.0f, kc1 = 0.0f, kc2 = 0.0f;
 #pragma unroll
             for (int k = 0; k < L; ++k) {
                 if (!sg[k].has) continue;
-                const bool inside = !df_lt(u, sg[k].a);          // a <= u (< b)
-                const df e = inside ? sg[k].b : sg[k].a;
-                if (!have_nb || df_lt(e, nb)) { nb = e; have_nb = true; }
+                const bool inside = !(u < sg[k].a);          // a <= u (< b)
+                const double e = inside ? sg[k].b : sg[k].a;
+                if (!have_nb || (e < nb)) { nb = e; have_nb = true; }
                 if (inside) {
                     ksum += sg[k].kap;
                     kc0 = fmaf(sg[k].kap, sg[k].c0, kc0);
@@ -183,7 +183,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(L <= 3 ?
             }
             bool finish = !have_nb;
             if (have_nb && ksum > 0.0f) {
-                const float du = df_f(df_sub(nb, u));
+                const float du = (float)(nb - u);
                 const float od = ksum * du;
                 float a, e_od;
                 absorb(od, a, e_od);
@@ -193,7 +193,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(L <= 3 ?
                 acc1 = fmaf(wt, kc1 * inv, acc1);
                 acc2 = fmaf(wt, kc2 * inv, acc2);
                 wsum += wt;
-                dsum = fmaf(wt, 0.5f * (df_f(u) + df_f(nb)) * dlen, dsum);
+                dsum = fmaf(wt, 0.5f * ((float)u + (float)nb) * dlen, dsum);
                 Tr *= e_od;
                 ++ns;
                 finish = t_stop > 0.0f && Tr < t_stop;
@@ -203,7 +203,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(L <= 3 ?
                 bool any = false;
 #pragma unroll
                 for (int k = 0; k < L; ++k) {
-                    if (sg[k].has && !df_lt(u, sg[k].b))        // this instance's segment ends here
+                    if (sg[k].has && !(u < sg[k].b))        // this instance's segment ends here
                         fetch_segment<DT>(ma.tr[k], rs[k], w[k], sg[k]);
                     any = any || sg[k].has;
                 }
@@ -227,8 +227,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(L <= 3 ?
 // cull pass for all instances) walks the rays through
 // one instance, as the forward does, and writes that instance's segments
 // along each ray as a linked list of 32-byte entries in increasing u:
-// {b.hi, b.lo, kappa, c_r} {c_g, c_b, next (-1: last), 0}, where b is the
-// compensated end of the entry's interval; an interval starts where the
+// {b (two words), kappa, c_r} {c_g, c_b, next (-1: last), 0}, where b is the
+// float64 end of the entry's interval; an interval starts where the
 // previous entry's ends. The stretch before the first segment, and every gap
 // between two segments, is an entry of extinction 0, so that a list reads as
 // a sequence of abutting intervals. A ray stops once the instance's own
@@ -255,10 +255,10 @@ struct MergeLists {
     int64_t cap;
 };
 
-__device__ __forceinline__ void store_entry(int4* ent, int slot, df b, float kap, float c0, float c1, float c2,
+__device__ __forceinline__ void store_entry(int4* ent, int slot, double b, float kap, float c0, float c1, float c2,
                                             int next) {
     int4* e = ent + 2 * (int64_t)slot;
-    e[0] = make_int4(__float_as_int(b.hi), __float_as_int(b.lo), __float_as_int(kap), __float_as_int(c0));
+    e[0] = make_int4(__double2loint(b), __double2hiint(b), __float_as_int(kap), __float_as_int(c0));
     e[1] = make_int4(__float_as_int(c1), __float_as_int(c2), next, 0);
 }
 
@@ -280,7 +280,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 8))) 
     float Tr = 1.0f;
     int first = -1;               // the ray's first entry; -2: the room ran out
     int pslot = -1;               // the last segment's entry, stored once what follows it is known
-    df pb = df_from(0.0f);        // that segment's end, extinction and colour
+    double pb = 0.0;        // that segment's end, extinction and colour
     float pk = 0.0f, pc0 = 0.0f, pc1 = 0.0f, pc2 = 0.0f;
     int tcur = 0, tend = 0;   // what is left of the wavefront's block of entries (wave-uniform)
 
@@ -338,14 +338,14 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 8))) 
         bool finish = false;
         int leaf = -1;
         float delta = 0.0f, umid = 0.0f;
-        df a = df_from(0.0f), b = df_from(0.0f);
+        double a = 0.0, b = 0.0;
         if (alive) {
             leaf = walk_next<kWalkBudget>(tr, rs, w, delta, umid, a, b);
             finish = leaf == -1;
         }
         // this iteration's entries: the segment, after a gap entry when it does
         // not start where the previous one ended (always before the first)
-        const bool gap = leaf >= 0 && (pslot < 0 || df_lt(pb, a));
+        const bool gap = leaf >= 0 && (pslot < 0 || (pb < a));
         const uint64_t m1 = __ballot(leaf >= 0), m2 = __ballot(gap);
         const int n_e = __popcll(m1) + __popcll(m2);
         const int at = n_e > 0 ? take_items(ml.counter, ml.cap, n_e, tcur, tend) : -1;
@@ -394,11 +394,11 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 8))) 
     }
 }
 
-__device__ __forceinline__ void load_entry(const int4* __restrict__ ent, int slot, df& b, float& kap, float& c0,
+__device__ __forceinline__ void load_entry(const int4* __restrict__ ent, int slot, double& b, float& kap, float& c0,
                                            float& c1, float& c2, int& next) {
     const int4* e = ent + 2 * (int64_t)slot;
     const int4 A = e[0], B = e[1];
-    b = df{__int_as_float(A.x), __int_as_float(A.y)};
+    b = __hiloint2double(A.y, A.x);
     kap = __int_as_float(A.z);
     c0 = __int_as_float(A.w);
     c1 = __int_as_float(B.x);
@@ -429,11 +429,11 @@ __global__ __launch_bounds__(kBlock) void merge_lists_kernel(RayArgs ra, const i
     bool more = true;
     bool alive = false;
     int64_t ray = -1;
-    df cb[L];                                     // per instance: the current entry's end,
+    double cb[L];                                 // per instance: the current entry's end,
     float ck[L], cr[L], cg[L], cbl[L];            // extinction, colour
     int nx[L];                                    // and next entry
     bool act[L];                                  // false: the instance's list is done
-    df u = df_from(0.0f);
+    double u = 0.0;
     float Tr = 1.0f, acc0 = 0.0f, acc1 = 0.0f, acc2 = 0.0f, wsum = 0.0f, dsum = 0.0f, dlen = 0.0f;
     int ns = 0;
     const int64_t n = ra.n;
@@ -493,7 +493,7 @@ __global__ __launch_bounds__(kBlock) void merge_lists_kernel(RayArgs ra, const i
                     if (act[k]) {
                         load_entry(ent, hd[k], cb[k], ck[k], cr[k], cg[k], cbl[k], nx[k]);
                         // a list opens with the gap before its first segment: start at the earliest
-                        if (first || df_lt(cb[k], u)) { u = cb[k]; first = false; }
+                        if (first || (cb[k] < u)) { u = cb[k]; first = false; }
                     }
                 }
                 alive = true;
@@ -505,19 +505,19 @@ __global__ __launch_bounds__(kBlock) void merge_lists_kernel(RayArgs ra, const i
             // every instance whose entry ends here moves to its next entry
 #pragma unroll
             for (int k = 0; k < L; ++k) {
-                if (act[k] && !df_lt(u, cb[k])) {
+                if (act[k] && !(u < cb[k])) {
                     if (nx[k] >= 0) load_entry(ent, nx[k], cb[k], ck[k], cr[k], cg[k], cbl[k], nx[k]);
                     else act[k] = false;
                 }
             }
             // the next entry end, and the extinction and colour over [u, nb)
-            df nb = df_from(0.0f);
+            double nb = 0.0;
             bool any = false;
             float ksum = 0.0f, kc0 = 0.0f, kc1 = 0.0f, kc2 = 0.0f;
 #pragma unroll
             for (int k = 0; k < L; ++k) {
                 if (!act[k]) continue;
-                if (!any || df_lt(cb[k], nb)) nb = cb[k];
+                if (!any || (cb[k] < nb)) nb = cb[k];
                 any = true;
                 ksum += ck[k];
                 kc0 = fmaf(ck[k], cr[k], kc0);
@@ -526,7 +526,7 @@ __global__ __launch_bounds__(kBlock) void merge_lists_kernel(RayArgs ra, const i
             }
             bool finish = !any;
             if (any && ksum > 0.0f) {
-                const float du = df_f(df_sub(nb, u));
+                const float du = (float)(nb - u);
                 const float od = ksum * du;
                 float a, e_od;
                 absorb(od, a, e_od);
@@ -536,7 +536,7 @@ __global__ __launch_bounds__(kBlock) void merge_lists_kernel(RayArgs ra, const i
                 acc1 = fmaf(wt, kc1 * inv, acc1);
                 acc2 = fmaf(wt, kc2 * inv, acc2);
                 wsum += wt;
-                dsum = fmaf(wt, 0.5f * (df_f(u) + df_f(nb)) * dlen, dsum);
+                dsum = fmaf(wt, 0.5f * ((float)u + (float)nb) * dlen, dsum);
                 Tr *= e_od;
                 ++ns;
                 finish = t_stop > 0.0f && Tr < t_stop;

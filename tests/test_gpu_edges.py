@@ -8,7 +8,7 @@ import torch
 
 from gpu_util import announce, oracle_render, rel_err, stop_ambiguous, tdev, tiny_camera, upload
 from oracle import core as OC
-from paper_2202_06088_amd import ops
+from paper_2202_06088_amd import _lib, ops
 from workloads import make_scene, scene_for_workload
 
 pytestmark = pytest.mark.gpu
@@ -45,3 +45,15 @@ def test_room_edges(tiny, cap, records, monkeypatch):
          rel_err(gb.cpu().numpy(), ref["grad_basis"])]
     announce(f"cap={cap} records={records}: grad rel errors {e}")
     assert max(e) <= 1e-4, e
+
+
+@pytest.mark.parametrize("width,height", [(1, 1), (1, 70), (257, 1), (1237, 31), (64, 64)])
+def test_pinhole_edges(width, height):
+    """Camera rays equal the oracle's bit for bit (both round one float64 value), whole images and pixel lists."""
+    c = np.random.default_rng(width).normal(size=(3, 4)).astype(np.float32)
+    intr = np.array([1.3 * width, 0.9 * width, 0.4 * width, 0.55 * height], np.float32)
+    cam = _lib.make_camera(width, height, *intr, c)
+    for pix in (None, np.arange(width * height, dtype=np.int32)[::-3].copy()):
+        ro, rd = OC.pinhole_rays(width, height, intr, c, pix)
+        o, d = ops.pinhole_rays(cam, None if pix is None else torch.from_numpy(pix).cuda())
+        assert np.array_equal(o.cpu().numpy(), ro) and np.array_equal(d.cpu().numpy(), rd)
