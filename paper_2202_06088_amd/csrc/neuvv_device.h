@@ -52,10 +52,6 @@ __device__ __forceinline__ double rcp64(double d) {
     return __builtin_fma(r, __builtin_fma(-d, r, 1.0), r);
 }
 
-// Index of the half-open unit cell a ray occupies just after passing x along
-// a direction that is negative or not: ceil(x) - 1 moving down, else floor(x).
-__device__ __forceinline__ int cell_of(double x, bool neg) { return (int)(neg ? __builtin_ceil(x) - 1.0 : __builtin_floor(x)); }
-
 // ----------------------------------------------------------------------------
 // Real 4-D hyperspherical harmonics H_nlm(d, gamma) = g_nl(gamma) Y_lm(d)
 // with g_nl = A_nl sin^l(gamma) C^{l+1}_{n-l}(cos gamma), A_nl =
@@ -214,8 +210,10 @@ __device__ __forceinline__ int64_t slot_to_ray(const RayArgs& ra, int64_t slot) 
 // Per-ray constants: local ray x_l(u) = O + u D with the world parameter u,
 // reciprocal direction, box interval [u_in, u_out), frame interpolation.
 struct RaySetup {
-    double O[3], D[3], inv[3];   // D and 1/D on an axis the ray does not move along: 0, +inf
-    bool neg[3];                 // the ray moves down this axis
+    // the walk's ray, mirrored on the axes it moves down: D >= 0, inv = 1/D > 0 (0 and +inf on an
+    // axis it does not move along), flip = -1 on a mirrored axis, else 0
+    double O[3], D[3], inv[3];
+    int flip[3];
     double u_in, u_out;
     float len_local;   // |D|: leaf units per unit of u
     float len_world;   // |d|: world distance per unit of u
@@ -358,19 +356,24 @@ __device__ __forceinline__ void ray_setup(const TreeArgs& tr, const InstArgs& in
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
         const bool zero = fabsf((float)rs.D[a]) <= 1.0e-20f * dmax;
-        rs.neg[a] = !zero && rs.D[a] < 0.0;
+        const bool neg = !zero && rs.D[a] < 0.0;
         const double lo_p = (double)tr.box_lo[a], hi_p = (double)tr.box_hi[a];
         if (zero) {
             if (rs.O[a] < lo_p || !(rs.O[a] < hi_p)) hit = false;
+            rs.flip[a] = 0;
             rs.D[a] = 0.0;
             rs.inv[a] = (double)INFINITY;
             continue;
         }
-        rs.inv[a] = rcp64(rs.D[a]);
-        const double t0 = (lo_p - rs.O[a]) * rs.inv[a], t1 = (hi_p - rs.O[a]) * rs.inv[a];
-        const double lo = rs.neg[a] ? t1 : t0, hi = rs.neg[a] ? t0 : t1;
+        const double inv = rcp64(rs.D[a]);
+        const double t0 = (lo_p - rs.O[a]) * inv, t1 = (hi_p - rs.O[a]) * inv;
+        const double lo = neg ? t1 : t0, hi = neg ? t0 : t1;
         if (u_in < lo) u_in = lo;
         if (!have_out || hi < u_out) { u_out = hi; have_out = true; }
+        rs.flip[a] = neg ? -1 : 0;
+        rs.O[a] = neg ? -rs.O[a] : rs.O[a];
+        rs.D[a] = neg ? -rs.D[a] : rs.D[a];
+        rs.inv[a] = neg ? -inv : inv;
     }
     if (!have_out || !(u_in < u_out)) hit = false;
     rs.u_in = u_in;
@@ -383,8 +386,7 @@ __device__ __forceinline__ void ray_setup(const TreeArgs& tr, const InstArgs& in
 // octree walk
 
 struct Walk {
-    int cell[3];     // leaf-level cell containing the ray just after the entry point
-    int steps;
+    int m[3];        // leaf-level cell containing the ray just after the entry point, mirrored: cell ^ flip
     double u;        // ray parameter of the entry point
     bool done;
     int brick;       // directory entry of the brick whose node is held below, -1: none
@@ -411,10 +413,10 @@ __host__ __device__ __forceinline__ int64_t directory_entries(int D) {
 __device__ __forceinline__ void walk_begin(const TreeArgs& tr, const RaySetup& rs, Walk& w) {
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        const int c = cell_of(__builtin_fma(rs.u_in, rs.D[a], rs.O[a]), rs.neg[a]);
-        w.cell[a] = c < tr.box_lo[a] ? tr.box_lo[a] : (c > tr.box_hi[a] - 1 ? tr.box_hi[a] - 1 : c);
+        // the half-open cell just after the entry point: floor along the mirrored axis
+        const int c = (int)__builtin_floor(__builtin_fma(rs.u_in, rs.D[a], rs.O[a])) ^ rs.flip[a];
+        w.m[a] = (c < tr.box_lo[a] ? tr.box_lo[a] : (c > tr.box_hi[a] - 1 ? tr.box_hi[a] - 1 : c)) ^ rs.flip[a];
     }
-    w.steps = 0;
     w.u = rs.u_in;
     w.done = !rs.hit;
     w.brick = -1;
@@ -442,24 +444,26 @@ __device__ __forceinline__ void walk_begin(const TreeArgs& tr, const RaySetup& r
 // same instructions for every lane. (Float estimates with error bounds, redone
 // in compensated pairs where a bound was met, cost a visit about four times
 // the instructions, and some lane of a wavefront met a bound in 27 % of its
-// iterations.)
+// iterations.) The walk runs in coordinates mirrored on the axes the ray moves
+// down, so that it only ever moves up: a step needs no selects by direction,
+// and a cell is turned back (one xor per axis) only to look it up. It ends by
+// construction: every visit moves up by a cell at least, and none back.
+// It never leaves the grid either: the box's far planes give u_out by the
+// same expression, which grows with the plane, so a step past them has ue >= u_out.
 template <int kBudget = 0>
 __device__ __forceinline__ int walk_next(const TreeArgs& tr, const RaySetup& rs, Walk& w, float& delta,
                                          float& umid, double& seg_a, double& seg_b) {
-    const int Dp = tr.depth;
-    const int G = 1 << Dp;
-    const int eb = Dp <= 2 ? 0 : Dp - 2;   // log2 of the directory's edge
-    const int max_steps = 3 * G + 16;
+    const int eb = tr.depth <= 2 ? 0 : tr.depth - 2;   // log2 of the directory's edge
     int budget = kBudget;
     while (!w.done) {
         if (kBudget > 0 && budget-- == 0) return -2;
-        if (++w.steps > max_steps) { w.done = true; break; }
         // the cell's brick, or the empty cube around its region; sh = log2 of the
         // edge of the empty cube or cell reached (0 for a leaf)
         int leaf = -1;
         int sh = 0;
         {
-            const int bid = ((((w.cell[2] >> 2) << eb) + (w.cell[1] >> 2)) << eb) + (w.cell[0] >> 2);
+            const int x = w.m[0] ^ rs.flip[0], y = w.m[1] ^ rs.flip[1], z = w.m[2] ^ rs.flip[2];
+            const int bid = ((((z >> 2) << eb) + (y >> 2)) << eb) + (x >> 2);
             bool held = bid == w.brick;
             if (!held) {
                 const int e = tr.dir[bid];
@@ -475,36 +479,35 @@ __device__ __forceinline__ int walk_next(const TreeArgs& tr, const RaySetup& rs,
                 }
             }
             if (held) {
-                // child q of the brick node: bit 0 of x, y, z, then bit 1 of x, y, z
-                const int x = w.cell[0], y = w.cell[1], z = w.cell[2];
-                const int q = (x & 1) | ((y & 1) << 1) | ((z & 1) << 2) | ((x & 2) << 2) | ((y & 2) << 3) | ((z & 2) << 4);
-                const uint64_t m = ((uint64_t)w.bm_hi << 32) | w.bm_lo;
-                if ((m >> q) & 1ull)
-                    leaf = w.bbase + (int)__builtin_popcountll(m & ((1ull << q) - 1ull));
+                // child q of the brick node: bit 0 of x, y, z, then bit 1 of x, y, z; the last picks the mask's half
+                const uint32_t q = (x & 1) | ((y & 1) << 1) | ((z & 1) << 2) | ((x & 2) << 2) | ((y & 2) << 3);
+                const bool top = (z & 2) != 0;
+                const uint32_t half = top ? w.bm_hi : w.bm_lo;
+                if ((half >> q) & 1u)
+                    leaf = w.bbase + (top ? __popc(w.bm_lo) : 0) + __popc(half & ((1u << q) - 1u));
                 else   // an empty cell; its 2^3 group (one byte of the mask) may be empty as a whole
-                    sh = ((m >> (q & 56)) & 0xffull) == 0ull ? 1 : 0;
+                    sh = ((half >> (q & 24u)) & 0xffu) == 0u ? 1 : 0;
             }
         }
         const int S = 1 << sh;
         // Exit face of the cell (or empty node) of edge S: the smallest crossing of
         // its far planes, the first axis on a tie. An axis the ray does not move
         // along has inv = +inf and its far plane above O, so it is never left.
-        int corner[3], plane[3];
+        int plane[3];
         double t[3];
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
-            corner[a] = w.cell[a] & -S;
-            plane[a] = corner[a] + (rs.neg[a] ? 0 : S);
+            plane[a] = (w.m[a] & -S) + S;
             t[a] = ((double)plane[a] - rs.O[a]) * rs.inv[a];
         }
         const bool y_first = t[1] < t[0];
         const double t01 = y_first ? t[1] : t[0];
         const bool z_first = t[2] < t01;
         const double ue = z_first ? t[2] : t01;
-        const bool last = !(ue < rs.u_out);   // leaving the box
+        w.done = !(ue < rs.u_out);   // leaving the box
         bool produced = false;
         if (leaf >= 0) {
-            const double ux = last ? rs.u_out : ue;
+            const double ux = w.done ? rs.u_out : ue;
             if (w.u < ux) {
                 delta = (float)(ux - w.u) * rs.len_local;
                 umid = 0.5f * ((float)w.u + (float)ux);
@@ -516,17 +519,14 @@ __device__ __forceinline__ int walk_next(const TreeArgs& tr, const RaySetup& rs,
         // The next cell: across the exit plane on the exit axis; on the other
         // axes the cell of the position at the exit, within the node.
         const bool ex[3] = {!z_first && !y_first, !z_first && y_first, z_first};
-        int n_am = 0;
 #pragma unroll
         for (int b = 0; b < 3; ++b) {
-            const int c = cell_of(__builtin_fma(ue, rs.D[b], rs.O[b]), rs.neg[b]);
-            const int across = rs.neg[b] ? plane[b] - 1 : plane[b];
-            const int within = c < corner[b] ? corner[b] : (c > corner[b] + S - 1 ? corner[b] + S - 1 : c);
-            w.cell[b] = ex[b] ? across : within;
-            n_am = ex[b] ? across : n_am;
+            int c = (int)__builtin_floor(__builtin_fma(ue, rs.D[b], rs.O[b]));
+            c = c < plane[b] - 1 ? c : plane[b] - 1;
+            c = c > w.m[b] ? c : w.m[b];
+            w.m[b] = ex[b] ? plane[b] : c;
         }
         w.u = ue;
-        w.done = last || n_am < 0 || n_am >= G;
         if (produced) return leaf;
     }
     return -1;
