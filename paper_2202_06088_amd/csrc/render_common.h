@@ -78,6 +78,22 @@ __device__ __forceinline__ void load_leaf(const void* base, int64_t N, int64_t s
     }
 }
 
+// Value e of the R-value row of leaf `slot` (layouts as in load_leaf).
+template <int DT, int R>
+__device__ __forceinline__ float leaf_elem(const void* base, int64_t N, int64_t slot, int e, int layout) {
+    constexpr int V = StoreTraits<DT>::V;
+    constexpr int NG = (R + V - 1) / V;
+    const int g = e / V, r = e - (e / V) * V;
+    const int64_t vec = layout ? slot * NG + g : (int64_t)g * N + slot;
+    if constexpr (DT == 0) {
+        return reinterpret_cast<const float*>(base)[vec * 4 + r];
+    } else {
+        const uint16_t u = reinterpret_cast<const uint16_t*>(base)[vec * 8 + r];
+        if constexpr (DT == 1) return (float)__builtin_bit_cast(_Float16, u);
+        else return __uint_as_float((uint32_t)u << 16);
+    }
+}
+
 // Per-sample transcendentals on the hardware base-2 exponential, base-2
 // logarithm and reciprocal (about 1 ulp each) instead of the correctly
 // rounded library sequences, which cost several times the instructions.

@@ -289,12 +289,9 @@ __host__ __device__ constexpr int grad_row() { return ((3 * K + C + 63) / 64) * 
 
 
 
-// REPLAY: every ray of the launch has a trace in io.trace (the forward's
-// samples) and replays it (segment length, density logit and colours)
-// without walking the tree or reading the HH coefficients; otherwise the
-// rays walk.
-template <int K, int C, int DT, bool IDENT, bool REPLAY>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(min_waves<K, C>(REPLAY ? 4 : 3), 8))) void render_bwd_kernel(
+// The walking adjoint: each ray walks the tree and evaluates its leaves again.
+template <int K, int C, int DT, bool IDENT>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(min_waves<K, C>(3), 8))) void render_bwd_kernel(
     TreeArgs tr, InstArgs in, RayArgs ra, BackwardIO io, RecordArgs rec) {
     if (no_candidates(ra)) return;
     constexpr int ROW = grad_row<K, C>();
@@ -326,7 +323,6 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(min_wave
     float Tr = 1.0f, Tfin = 0.0f, p0 = 0.0f, p1 = 0.0f, p2 = 0.0f, F0 = 0.0f, F1 = 0.0f, F2 = 0.0f;
     float g0 = 0.0f, g1 = 0.0f, g2 = 0.0f, ga = 0.0f;
     int ns = 0, ns_fwd = 0;
-    int tnext = -1;        // replay: the ray's next sample
     float dw0 = 0.0f, dw1 = 0.0f, dw2 = 0.0f;   // the ray's direction (world), for its records
     // records: the wavefront fills blocks of consecutive records (take_items);
     // [wrec, wend) is what is left of the current block (wave-uniform)
@@ -375,8 +371,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(min_wave
 #pragma unroll
                         for (int c = 0; c < C; ++c) s_b[threadIdx.x * C + c] = bv[c];
                     }
-                    if constexpr (REPLAY) tnext = io.trace.head[ray];
-                    else walk_begin(tr, rs, w);
+                    walk_begin(tr, rs, w);
                     ns_fwd = io.nsamp[ray];
                     ns = 0;
                     Tr = 1.0f;
@@ -403,44 +398,28 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(min_wave
             bool finish;
             float x = 0.0f, c0 = 0.0f, c1 = 0.0f, c2 = 0.0f;
             float sv[C];
-            if constexpr (REPLAY) {
-                // replay the forward's sample
-                if (tnext >= 0) {
-                    const int4 A = io.trace.smp[2 * (int64_t)tnext], B = io.trace.smp[2 * (int64_t)tnext + 1];
-                    leaf = A.x;
-                    delta = __int_as_float(A.y);
-                    x = __int_as_float(A.z);
-                    c0 = __int_as_float(A.w);
-                    c1 = __int_as_float(B.x);
-                    c2 = __int_as_float(B.y);
-                    tnext = B.z;
-                    if (basis_here) load_leaf<DT, C>(tr.wsig, N, leaf, tr.layout, sv);
-                }
-                finish = leaf < 0;
-            } else {
-                float umid;
-                leaf = walk_next<kWalkBudget>(tr, rs, w, delta, umid);
-                finish = leaf == -1;
-                if (leaf >= 0) {
-                    float wv[3 * K];
-                    load_leaf<DT, 3 * K>(tr.hh, N, leaf, tr.layout, wv);
-                    load_leaf<DT, C>(tr.wsig, N, leaf, tr.layout, sv);
-                    const float* hl = s_h + threadIdx.x * K;
-                    const float* bl = s_b + threadIdx.x * C;
+            float umid;
+            leaf = walk_next<kWalkBudget>(tr, rs, w, delta, umid);
+            finish = leaf == -1;
+            if (leaf >= 0) {
+                float wv[3 * K];
+                load_leaf<DT, 3 * K>(tr.hh, N, leaf, tr.layout, wv);
+                load_leaf<DT, C>(tr.wsig, N, leaf, tr.layout, sv);
+                const float* hl = s_h + threadIdx.x * K;
+                const float* bl = s_b + threadIdx.x * C;
 #pragma unroll
-                    for (int c = 0; c < C; ++c) x = fmaf(sv[c], bl[c], x);
-                    float z0 = 0.0f, z1 = 0.0f, z2 = 0.0f;
+                for (int c = 0; c < C; ++c) x = fmaf(sv[c], bl[c], x);
+                float z0 = 0.0f, z1 = 0.0f, z2 = 0.0f;
 #pragma unroll
-                    for (int k = 0; k < K; ++k) {
-                        const float hk = hl[k];
-                        z0 = fmaf(wv[k], hk, z0);
-                        z1 = fmaf(wv[K + k], hk, z1);
-                        z2 = fmaf(wv[2 * K + k], hk, z2);
-                    }
-                    c0 = sigmoid_f(z0);
-                    c1 = sigmoid_f(z1);
-                    c2 = sigmoid_f(z2);
+                for (int k = 0; k < K; ++k) {
+                    const float hk = hl[k];
+                    z0 = fmaf(wv[k], hk, z0);
+                    z1 = fmaf(wv[K + k], hk, z1);
+                    z2 = fmaf(wv[2 * K + k], hk, z2);
                 }
+                c0 = sigmoid_f(z0);
+                c1 = sigmoid_f(z1);
+                c2 = sigmoid_f(z2);
             }
             if (leaf >= 0) {
                 const float sig = density_f(x, tr.relu);
@@ -546,6 +525,213 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(min_wave
             float f;
             time_setup(tr, in, ra.t_scalar, i0, i1, f);
             const float v = s_gb[threadIdx.x];
+            unsafeAtomicAdd(io.grad_basis + (int64_t)i0 * C + threadIdx.x, (1.0f - f) * v);
+            if (f != 0.0f) unsafeAtomicAdd(io.grad_basis + (int64_t)i1 * C + threadIdx.x, f * v);
+        }
+    }
+}
+
+// The adjoint of rays with a trace: replays the forward's samples (segment
+// length, density logit and colours) without walking the tree or evaluating
+// leaves. It is bound by the rate of the exchanges that link records and, with
+// few rays, by the latency of a ray's chain of entries, so it holds nothing a
+// sample with a record does not need (a ray's geometry and basis are made only
+// for samples without one, one at a time), and a ray's next entry is on its way
+// while one is replayed. Against one kernel with the walking adjoint, which set
+// up every ray and loaded each entry when it came to it: four layers of a
+// 1920 x 1080 image 508 -> 433 us, 65,536 rays 88 -> 79 us, ring 472 -> 457 us. More
+// than four wavefronts per SIMD spill and gain nothing (ring 450 us at 5, 462 at 6,
+// 484 at 8; layers 471 us at 5).
+// PER_T: a time per ray; the basis gradient is then summed per ray here.
+template <int K, int C, int DT, bool IDENT, bool PER_T>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(min_waves<K, C>(4), 8))) void replay_bwd_kernel(
+    TreeArgs tr, InstArgs in, RayArgs ra, BackwardIO io, RecordArgs rec) {
+    if (no_candidates(ra)) return;
+    constexpr int ROW = grad_row<K, C>();
+    __shared__ float s_row[kBlock / kWave][K + C];   // basis of the sample being scattered
+    __shared__ float s_gb[C];
+    if (threadIdx.x < C) s_gb[threadIdx.x] = 0.0f;
+    __syncthreads();
+    ChunkCursor cc = chunk_cursor();
+    bool more = true;   // wave-uniform: chunks may be left
+    const int lane = threadIdx.x & 63;
+    float* const srow = s_row[threadIdx.x >> 6];
+
+    bool alive = false;
+    int ray = -1;
+    float gb[PER_T ? C : 1];
+    float Tr = 1.0f, Tfin = 0.0f, p0 = 0.0f, p1 = 0.0f, p2 = 0.0f, F0 = 0.0f, F1 = 0.0f, F2 = 0.0f;
+    float g0 = 0.0f, g1 = 0.0f, g2 = 0.0f, ga = 0.0f;
+    f3v dw = {0.0f, 0.0f, 0.0f};   // the ray's direction (world)
+    int left = 0;                  // samples of the ray still to replay
+    int4 nA = make_int4(0, 0, 0, 0), nB = make_int4(0, 0, -1, 0);   // its next sample, on its way while one is replayed
+    int i0 = 0;                    // PER_T: its frame and the weight of the next
+    float f = 0.0f;
+    int wrec = 0, wend = 0;        // what is left of the wavefront's block of records (wave-uniform)
+
+    for (;;) {
+        const uint64_t idle = __ballot(!alive);
+        const int n_idle = __popcll(idle);
+        if (more && (n_idle >= ra.refill_min || n_idle == kWave)) {
+            // idle lanes take the next rays (the list holds only rays with a trace)
+            if (cc.pos == kWave && !next_chunk(ra, cc)) {
+                more = false;
+                continue;
+            }
+            const int take = n_idle < kWave - cc.pos ? n_idle : kWave - cc.pos;
+            const int r = lane_rank(idle);
+            if (!alive && r < take) {
+                ray = (int)chunk_ray(ra, cc, cc.pos + r);
+                if (ray >= 0) {
+                    const int first = io.trace.head[ray];
+                    left = io.nsamp[ray];
+                    Tr = 1.0f;
+                    Tfin = 1.0f - io.alpha[ray];
+                    const f3v F = load3(io.rgb + 3 * (int64_t)ray), g = load3(io.grad_rgb + 3 * (int64_t)ray);
+                    F0 = F.x; F1 = F.y; F2 = F.z;
+                    g0 = g.x; g1 = g.y; g2 = g.z;
+                    ga = io.grad_alpha ? io.grad_alpha[ray] : 0.0f;
+                    dw = load3(ra.d + 3 * (int64_t)ray);
+                    p0 = p1 = p2 = 0.0f;
+                    if constexpr (PER_T) {
+#pragma unroll
+                        for (int c = 0; c < C; ++c) gb[c] = 0.0f;
+                    }
+                    if constexpr (PER_T) {
+                        int i1;
+                        time_setup(tr, in, ra.t[ray], i0, i1, f);
+                    }
+                    alive = left > 0 && first >= 0;
+                    if (alive) {
+                        nA = io.trace.smp[2 * (int64_t)first];
+                        nB = io.trace.smp[2 * (int64_t)first + 1];
+                    }
+                }
+            }
+            cc.pos += take;
+            continue;
+        }
+        if (n_idle == kWave) break;
+        bool has = false;
+        int leaf = -1, my_rec = -1;
+        float gz0 = 0.0f, gz1 = 0.0f, gz2 = 0.0f, gx = 0.0f;
+        if (alive) {
+            const int4 A = nA, B = nB;
+            const int tnext = B.z;
+            if (tnext >= 0) {
+                nA = io.trace.smp[2 * (int64_t)tnext];
+                nB = io.trace.smp[2 * (int64_t)tnext + 1];
+            }
+            leaf = A.x;
+            const float delta = __int_as_float(A.y), x = __int_as_float(A.z);
+            const float c0 = __int_as_float(A.w), c1 = __int_as_float(B.x), c2 = __int_as_float(B.y);
+            const float sig = density_f(x, tr.relu);
+            const float od = sig * delta;
+            float a, e;
+            absorb(od, a, e);
+            const float wt = Tr * a;
+            const float Tn = Tr * e;
+            p0 = fmaf(wt, c0, p0);
+            p1 = fmaf(wt, c1, p1);
+            p2 = fmaf(wt, c2, p2);
+            const float gdotc = g0 * c0 + g1 * c1 + g2 * c2;
+            const float gsuf = g0 * (F0 - p0) + g1 * (F1 - p1) + g2 * (F2 - p2);
+            // dL/dsigma = delta (T_{k+1} <g, c_k> - <g, rgb - rgb_<=k>) + g_a delta T_final
+            const float gsig = delta * (Tn * gdotc - gsuf) + ga * delta * Tfin;
+            gx = gsig * density_dx(x, tr.relu);
+            gz0 = g0 * wt * c0 * (1.0f - c0);
+            gz1 = g1 * wt * c1 * (1.0f - c1);
+            gz2 = g2 * wt * c2 * (1.0f - c2);
+            if constexpr (PER_T) {
+                if (io.grad_basis) {
+                    float sv[C];
+                    load_leaf<DT, C>(tr.wsig, tr.n_leaves, leaf, tr.layout, sv);
+#pragma unroll
+                    for (int c = 0; c < C; ++c) gb[c] = fmaf(gx, sv[c], gb[c]);
+                }
+            }
+            has = true;
+            Tr = Tn;
+            if (--left == 0 || tnext < 0) {
+                if constexpr (PER_T) {
+                    if (io.grad_basis) {
+                        const int i1 = i0 + 1 < tr.T ? i0 + 1 : tr.T - 1;
+#pragma unroll
+                        for (int c = 0; c < C; ++c) {
+                            unsafeAtomicAdd(io.grad_basis + (int64_t)i0 * C + c, (1.0f - f) * gb[c]);
+                            if (f != 0.0f) unsafeAtomicAdd(io.grad_basis + (int64_t)i1 * C + c, f * gb[c]);
+                        }
+                    }
+                }
+                alive = false;
+            }
+        }
+        if (rec.head) {
+            // this iteration's samples take consecutive records in lane order, so
+            // the record stores of the wavefront are contiguous
+            const uint64_t hm = __ballot(has);
+            const int at = take_items(rec.counter, rec.cap, __popcll(hm), wrec, wend);
+            if (at >= 0) {
+                const RecordRun run = record_run(hm, has, leaf);
+                if (has) {
+                    my_rec = at + lane_rank(hm);
+                    rec.rec[2 * (int64_t)my_rec] =
+                        make_int4(__float_as_int(gz0), __float_as_int(gz1), __float_as_int(gz2), __float_as_int(gx));
+                    const int nxt = run.count > 0 ? atomicExch(rec.head + leaf, my_rec + run.count - 1) : my_rec - 1;
+                    // one time for every ray: the record carries the ray's direction
+                    // (all the reduction needs of the ray), else the ray's index
+                    rec.rec[2 * (int64_t)my_rec + 1] =
+                        PER_T ? make_int4(nxt, ray, 0, 0)
+                              : make_int4(nxt, __float_as_int(dw.x), __float_as_int(dw.y), __float_as_int(dw.z));
+                }
+            }
+        }
+        // samples without a record: every lane of the wavefront adds one
+        // component of each sample's row, whose basis its own lane makes first
+        uint64_t m = __ballot(has && my_rec < 0);
+        while (__builtin_expect_with_probability(m != 0, 0, 0.99999)) {
+            const int src = __builtin_ctzll(m);
+            m &= m - 1;
+            __builtin_amdgcn_wave_barrier();
+            if (lane == src) {
+                RaySetup rs;
+                float dmax, h[K], bv[C];
+                const float d[3] = {dw.x, dw.y, dw.z};
+                ray_direction<IDENT>(in, d, rs, dmax);
+                time_setup(tr, in, PER_T ? ra.t[ray] : ra.t_scalar, rs.i0, rs.i1, rs.f);
+                ray_basis<K, C>(tr, rs, h, bv);
+#pragma unroll
+                for (int k = 0; k < K; ++k) srow[k] = h[k];
+#pragma unroll
+                for (int c = 0; c < C; ++c) srow[K + c] = bv[c];
+            }
+            __builtin_amdgcn_wave_barrier();
+            const int L = __builtin_amdgcn_readlane(leaf, src);
+            const float a0 = readlane_f(gz0, src), a1 = readlane_f(gz1, src), a2 = readlane_f(gz2, src);
+            const float ax = readlane_f(gx, src);
+            float* row = io.grad_leaf + (int64_t)L * ROW;
+#pragma unroll
+            for (int c0 = 0; c0 < 3 * K + C; c0 += kWave) {
+                const int c = c0 + lane;
+                if (c < 3 * K) {
+                    const int ch = c / K;
+                    const float gzc = ch == 0 ? a0 : (ch == 1 ? a1 : a2);
+                    unsafeAtomicAdd(row + c, gzc * srow[c - ch * K]);
+                } else if (c < 3 * K + C) {
+                    unsafeAtomicAdd(row + c, ax * srow[K + c - 3 * K]);
+                }
+            }
+            if (!PER_T && io.grad_basis && lane < C)   // (summed per leaf by the reduction for samples with records)
+                atomicAdd(&s_gb[lane], ax * leaf_elem<DT, C>(tr.wsig, tr.n_leaves, L, lane, tr.layout));
+        }
+    }
+    if (!PER_T && io.grad_basis) {
+        __syncthreads();
+        const float v = threadIdx.x < C ? s_gb[threadIdx.x] : 0.0f;
+        if (v != 0.0f) {
+            int i0, i1;
+            float f;
+            time_setup(tr, in, ra.t_scalar, i0, i1, f);
             unsafeAtomicAdd(io.grad_basis + (int64_t)i0 * C + threadIdx.x, (1.0f - f) * v);
             if (f != 0.0f) unsafeAtomicAdd(io.grad_basis + (int64_t)i1 * C + threadIdx.x, f * v);
         }
@@ -763,16 +949,20 @@ static hipError_t fwd_t(const TreeArgs& tr, const InstArgs& in, const RayArgs& r
     }
 }
 
-template <int K, int C, int DT, bool REPLAY>
-static hipError_t bwd_k(const TreeArgs& tr, const InstArgs& in, const RayArgs& ra, const BackwardIO& io,
-                        const RecordArgs& rec, hipStream_t st) {
-    if (in.identity) {
-        auto kern = render_bwd_kernel<K, C, DT, true, REPLAY>;
-        hipLaunchKernelGGL(kern, dim3(grid_for(kern, ra)), dim3(kBlock), 0, st, tr, in, ra, io, rec);
-    } else {
-        auto kern = render_bwd_kernel<K, C, DT, false, REPLAY>;
-        hipLaunchKernelGGL(kern, dim3(grid_for(kern, ra)), dim3(kBlock), 0, st, tr, in, ra, io, rec);
-    }
+template <int K, int C, int DT>
+static hipError_t bwd_walk(const TreeArgs& tr, const InstArgs& in, const RayArgs& ra, const BackwardIO& io,
+                           const RecordArgs& rec, hipStream_t st) {
+    auto kern = in.identity ? render_bwd_kernel<K, C, DT, true> : render_bwd_kernel<K, C, DT, false>;
+    hipLaunchKernelGGL(kern, dim3(grid_for(kern, ra)), dim3(kBlock), 0, st, tr, in, ra, io, rec);
+    return hipGetLastError();
+}
+
+template <int K, int C, int DT>
+static hipError_t bwd_replay(const TreeArgs& tr, const InstArgs& in, const RayArgs& ra, const BackwardIO& io,
+                             const RecordArgs& rec, hipStream_t st) {
+    auto kern = ra.t ? (in.identity ? replay_bwd_kernel<K, C, DT, true, true> : replay_bwd_kernel<K, C, DT, false, true>)
+                     : (in.identity ? replay_bwd_kernel<K, C, DT, true, false> : replay_bwd_kernel<K, C, DT, false, false>);
+    hipLaunchKernelGGL(kern, dim3(grid_for(kern, ra)), dim3(kBlock), 0, st, tr, in, ra, io, rec);
     return hipGetLastError();
 }
 
@@ -788,8 +978,8 @@ static hipError_t bwd_t(const TreeArgs& tr, const InstArgs& in, const RayArgs& r
     if (e == hipSuccess) {
         // one cull pass and render adjoint per source of samples: rays that walk,
         // and (traced forward) rays that replay their trace
-        auto walk = [&](const RayArgs& r) { return bwd_k<K, C, DT, false>(tr, in, r, io, rec, st); };
-        auto replay = [&](const RayArgs& r) { return bwd_k<K, C, DT, true>(tr, in, r, io, rec, st); };
+        auto walk = [&](const RayArgs& r) { return bwd_walk<K, C, DT>(tr, in, r, io, rec, st); };
+        auto replay = [&](const RayArgs& r) { return bwd_replay<K, C, DT>(tr, in, r, io, rec, st); };
         // the walking adjoint's cull reads whether the forward's traces are all complete
         const RenderOut trace_out{nullptr, nullptr, nullptr, nullptr, nullptr, io.trace};
         if (io.trace.head) {

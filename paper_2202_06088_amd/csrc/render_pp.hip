@@ -55,22 +55,6 @@ __device__ __forceinline__ float basis_dot(const float (&w)[N], const float* s_r
     return x;
 }
 
-// Value e of the R-value row of leaf `slot` (layouts as in load_leaf).
-template <int DT, int R>
-__device__ __forceinline__ float leaf_elem(const void* base, int64_t N, int64_t slot, int e, int layout) {
-    constexpr int V = StoreTraits<DT>::V;
-    constexpr int NG = (R + V - 1) / V;
-    const int g = e / V, r = e - (e / V) * V;
-    const int64_t vec = layout ? slot * NG + g : (int64_t)g * N + slot;
-    if constexpr (DT == 0) {
-        return reinterpret_cast<const float*>(base)[vec * 4 + r];
-    } else {
-        const uint16_t u = reinterpret_cast<const uint16_t*>(base)[vec * 8 + r];
-        if constexpr (DT == 1) return (float)__builtin_bit_cast(_Float16, u);
-        else return __uint_as_float((uint32_t)u << 16);
-    }
-}
-
 // Stages the interpolated basis rows shared by every ray (scalar time) in
 // LDS; the caller's barrier makes them visible.
 __device__ __forceinline__ void stage_common_rows(const TreeArgs& tr, const InstArgs& in, float t, float* s_b,
@@ -326,10 +310,11 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 8))) 
 // Component of lane slot j (0, 1) of the gradient row.
 __device__ __forceinline__ int pp_component(int j, int lane) { return j * kWave + lane; }
 
-// REPLAY: every ray of the launch has a trace in io.trace (the forward's
-// samples) and replays it without walking the tree or reading the leaf
-// payload: dL/dgamma = sum_ch gz_ch dz_ch/dgamma comes from the traced
-// derivatives, and h is recomputed from y only for samples without a record.
+// REPLAY (a time per ray; replay_pp_kernel below takes one time for every ray):
+// every ray of the launch has a trace in io.trace (the forward's samples) and
+// replays it without walking the tree or reading the leaf payload: dL/dgamma =
+// sum_ch gz_ch dz_ch/dgamma comes from the traced derivatives, and h is
+// recomputed from y.
 template <int DT, bool IDENT, bool REPLAY>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(REPLAY ? 3 : 2, 8))) void render_pp_bwd_kernel(
     TreeArgs tr, InstArgs in, RayArgs ra, BackwardIO io, RecordArgs rec) {
@@ -609,6 +594,183 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(REPLAY ?
     }
 }
 
+// The adjoint of rays with a trace and one time for every ray, as
+// replay_bwd_kernel of the global form: only what a sample with a record
+// needs, the ray's next entry on its way while one is replayed, and the basis
+// of a sample without a record made when it is scattered.
+template <int DT, bool IDENT>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) void replay_pp_kernel(
+    TreeArgs tr, InstArgs in, RayArgs ra, BackwardIO io, RecordArgs rec) {
+    if (no_candidates(ra)) return;
+    using namespace pp;
+    __shared__ float s_row[kBlock / kWave][K];   // basis h of the sample being scattered
+    __shared__ float s_brow[C], s_bgrow[CG];
+    __shared__ float s_acc[2 * kWave];           // block sum of the basis gradients of scattered samples
+    stage_common_rows(tr, in, ra.t_scalar, s_brow, s_bgrow);
+    if (threadIdx.x < 2 * kWave) s_acc[threadIdx.x] = 0.0f;
+    __syncthreads();
+    ChunkCursor cc = chunk_cursor();
+    bool more = true;
+    const int lane = threadIdx.x & 63;
+    float* const srow = s_row[threadIdx.x >> 6];
+
+    bool alive = false;
+    int ray = -1;
+    float Tr = 1.0f, Tfin = 0.0f, p0 = 0.0f, p1 = 0.0f, p2 = 0.0f, F0 = 0.0f, F1 = 0.0f, F2 = 0.0f;
+    float g0 = 0.0f, g1 = 0.0f, g2 = 0.0f, ga = 0.0f;
+    int left = 0;              // samples of the ray still to replay
+    int4 nA = make_int4(0, 0, 0, 0), nB = make_int4(0, 0, 0, -1), nQ = make_int4(0, 0, 0, 0);   // its next sample
+    int wrec = 0, wend = 0;    // what is left of the wavefront's block of records (wave-uniform)
+
+    for (;;) {
+        const uint64_t idle = __ballot(!alive);
+        const int n_idle = __popcll(idle);
+        if (more && (n_idle >= ra.refill_min || n_idle == kWave)) {
+            // idle lanes take the next rays (the list holds only rays with a trace)
+            if (cc.pos == kWave && !next_chunk(ra, cc)) {
+                more = false;
+                continue;
+            }
+            const int take = n_idle < kWave - cc.pos ? n_idle : kWave - cc.pos;
+            const int r = lane_rank(idle);
+            if (!alive && r < take) {
+                ray = (int)chunk_ray(ra, cc, cc.pos + r);
+                if (ray >= 0) {
+                    const int first = io.trace.head[ray];
+                    left = io.nsamp[ray];
+                    Tr = 1.0f;
+                    Tfin = 1.0f - io.alpha[ray];
+                    const f3v F = load3(io.rgb + 3 * (int64_t)ray), g = load3(io.grad_rgb + 3 * (int64_t)ray);
+                    F0 = F.x; F1 = F.y; F2 = F.z;
+                    g0 = g.x; g1 = g.y; g2 = g.z;
+                    ga = io.grad_alpha ? io.grad_alpha[ray] : 0.0f;
+                    p0 = p1 = p2 = 0.0f;
+                    alive = left > 0 && first >= 0;
+                    if (alive) {
+                        const int4* e = io.trace.smp + kPPTraceInt4 * (int64_t)first;
+                        nA = e[0];
+                        nB = e[1];
+                        nQ = e[2];
+                    }
+                }
+            }
+            cc.pos += take;
+            continue;
+        }
+        if (n_idle == kWave) break;
+        bool has = false;
+        int leaf = -1, my_rec = -1;
+        float gz0 = 0.0f, gz1 = 0.0f, gz2 = 0.0f, gx = 0.0f, gy = 0.0f, y = 0.0f;
+        if (alive) {
+            const int4 A = nA, B = nB, Q = nQ;
+            if (B.w >= 0) {
+                const int4* e = io.trace.smp + kPPTraceInt4 * (int64_t)B.w;
+                nA = e[0];
+                nB = e[1];
+                nQ = e[2];
+            }
+            leaf = A.x;
+            const float delta = __int_as_float(A.y), x = __int_as_float(A.z);
+            y = __int_as_float(A.w);
+            const float c0 = __int_as_float(B.x), c1 = __int_as_float(B.y), c2 = __int_as_float(B.z);
+            const float sig = density_f(x, tr.relu);
+            const float od = sig * delta;
+            float a, e;
+            absorb(od, a, e);
+            const float wt = Tr * a;
+            const float Tn = Tr * e;
+            p0 = fmaf(wt, c0, p0);
+            p1 = fmaf(wt, c1, p1);
+            p2 = fmaf(wt, c2, p2);
+            const float gdotc = g0 * c0 + g1 * c1 + g2 * c2;
+            const float gsuf = g0 * (F0 - p0) + g1 * (F1 - p1) + g2 * (F2 - p2);
+            const float gsig = delta * (Tn * gdotc - gsuf) + ga * delta * Tfin;
+            gx = gsig * density_dx(x, tr.relu);
+            gz0 = g0 * wt * c0 * (1.0f - c0);
+            gz1 = g1 * wt * c1 * (1.0f - c1);
+            gz2 = g2 * wt * c2 * (1.0f - c2);
+            // dL/dgamma through every h_k = g_nl(gamma) Y_k, from the traced dz/dgamma
+            const float ggam = gz0 * __int_as_float(Q.x) + gz1 * __int_as_float(Q.y) + gz2 * __int_as_float(Q.z);
+            const float sg = sigmoid_f(y);
+            gy = ggam * kPi * sg * (1.0f - sg);
+            has = true;
+            Tr = Tn;
+            if (--left == 0 || B.w < 0) alive = false;
+        }
+        if (rec.head) {
+            const uint64_t hm = __ballot(has);
+            const int at = take_items(rec.counter, rec.cap, __popcll(hm), wrec, wend);
+            if (at >= 0) {
+                const RecordRun run = record_run(hm, has, leaf);
+                if (has) {
+                    my_rec = at + lane_rank(hm);
+                    rec.rec[2 * (int64_t)my_rec] =
+                        make_int4(__float_as_int(gz0), __float_as_int(gz1), __float_as_int(gz2), __float_as_int(gx));
+                    const int nxt = run.count > 0 ? atomicExch(rec.head + leaf, my_rec + run.count - 1) : my_rec - 1;
+                    rec.rec[2 * (int64_t)my_rec + 1] = make_int4(nxt, ray, __float_as_int(gy), 0);
+                }
+            }
+        }
+        // samples without a record: their row, one component per lane, and their basis gradients
+        uint64_t m = __ballot(has && my_rec < 0);
+        while (__builtin_expect_with_probability(m != 0, 0, 0.99999)) {
+            const int src = __builtin_ctzll(m);
+            m &= m - 1;
+            __builtin_amdgcn_wave_barrier();
+            if (lane == src) {
+                RaySetup rs;
+                float dmax, Y[8], g[6], dg[6], h[K], sn, cs;
+                const f3v dv = load3(ra.d + 3 * (int64_t)ray);
+                const float d[3] = {dv.x, dv.y, dv.z};
+                ray_direction<IDENT>(in, d, rs, dmax);
+                sh_deg2(rs.dir[0], rs.dir[1], rs.dir[2], Y);
+                sincosf(kPi * sigmoid_f(y), &sn, &cs);
+                radial_n2(sn, cs, g, dg);
+                hh14(g, Y, h);
+#pragma unroll
+                for (int k = 0; k < K; ++k) srow[k] = h[k];
+            }
+            __builtin_amdgcn_wave_barrier();
+            const int L = __builtin_amdgcn_readlane(leaf, src);
+            const float a0 = readlane_f(gz0, src), a1 = readlane_f(gz1, src), a2 = readlane_f(gz2, src);
+            const float ax = readlane_f(gx, src), ay = readlane_f(gy, src);
+            float* row = io.grad_leaf + (int64_t)L * ROW;
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const int c = pp_component(j, lane);
+                if (c < 3 * K) {
+                    const int ch = c / K;
+                    const float gzc = ch == 0 ? a0 : (ch == 1 ? a1 : a2);
+                    unsafeAtomicAdd(row + c, gzc * srow[c - ch * K]);
+                } else if (c < 3 * K + C + CG) {
+                    const bool dens = c < 3 * K + C;
+                    const int e = dens ? c - 3 * K : c - 3 * K - C;
+                    unsafeAtomicAdd(row + c, dens ? ax * s_brow[e] : ay * s_bgrow[e]);
+                    const float wl = dens ? leaf_elem<DT, C>(tr.wsig, tr.n_leaves, L, e, tr.layout)
+                                          : leaf_elem<DT, CG>(tr.wgam, tr.n_leaves, L, e, tr.layout);
+                    atomicAdd(&s_acc[dens ? e : kWave + e], (dens ? ax : ay) * wl);
+                }
+            }
+        }
+    }
+    // (the basis gradients of samples with records are summed per leaf by the reduction)
+    __syncthreads();
+    const int c = threadIdx.x;
+    const bool dens = c < C;
+    const bool gam = c >= kWave && c < kWave + CG;
+    float* gB = dens ? io.grad_basis : io.grad_basis_g;
+    if ((dens || gam) && gB && s_acc[c] != 0.0f) {
+        const int e = dens ? c : c - kWave;
+        const int R = dens ? C : CG;
+        int i0, i1;
+        float f;
+        time_setup(tr, in, ra.t_scalar, i0, i1, f);
+        const float v = s_acc[c];
+        unsafeAtomicAdd(gB + (int64_t)i0 * R + e, (1.0f - f) * v);
+        if (f != 0.0f) unsafeAtomicAdd(gB + (int64_t)i1 * R + e, f * v);
+    }
+}
+
 // ----------------------------------------------------------------------------
 // second pass of the two-phase adjoint (scalar time)
 //
@@ -789,13 +951,9 @@ static hipError_t pp_fwd_t(const TreeArgs& tr, const InstArgs& in, const RayArgs
 template <int DT, bool REPLAY>
 static hipError_t pp_bwd_k(const TreeArgs& tr, const InstArgs& in, const RayArgs& ra, const BackwardIO& io,
                            const RecordArgs& rec, hipStream_t st) {
-    if (in.identity) {
-        auto kern = render_pp_bwd_kernel<DT, true, REPLAY>;
-        hipLaunchKernelGGL(kern, dim3(grid_for(kern, ra)), dim3(kBlock), 0, st, tr, in, ra, io, rec);
-    } else {
-        auto kern = render_pp_bwd_kernel<DT, false, REPLAY>;
-        hipLaunchKernelGGL(kern, dim3(grid_for(kern, ra)), dim3(kBlock), 0, st, tr, in, ra, io, rec);
-    }
+    auto kern = REPLAY && !ra.t ? (in.identity ? replay_pp_kernel<DT, true> : replay_pp_kernel<DT, false>)
+                                : (in.identity ? render_pp_bwd_kernel<DT, true, REPLAY> : render_pp_bwd_kernel<DT, false, REPLAY>);
+    hipLaunchKernelGGL(kern, dim3(grid_for(kern, ra)), dim3(kBlock), 0, st, tr, in, ra, io, rec);
     return hipGetLastError();
 }
 
