@@ -254,19 +254,22 @@ static int grid_for(KernelT kernel, const RayArgs& ra) {
 // graph) and freed after the render kernel in stream order. The candidate
 // form adds kQueues counts (the second KiB) and a list of n_chunks * 64
 // int32 ray indices.
-static __global__ void zero_queue_kernel(unsigned long long* q) { q[threadIdx.x] = 0ull; }
+// extra: nullptr, or one more counter to clear.
+static __global__ void zero_queue_kernel(unsigned long long* q, unsigned long long* extra) {
+    q[threadIdx.x] = 0ull;
+    if (extra && threadIdx.x == 0) *extra = 0ull;
+}
 
 // Cull pass of the candidate form: each wavefront tests kCullGroup chunks of
 // one XCD part at a time (64 slots per chunk, one per lane), reserves room for
 // the rays it keeps with one atomic on the part's count (atomics on one
 // address serialise, so the groups are large), and lists them in slot order.
 // MODE 0 (forward): keep the rays the plain-float box test cannot reject and
-// write the miss outputs of the others. MODE 1 (adjoint): keep the rays whose
-// forward composited a sample (the others carry no gradient); MODE 2 and 3
-// (adjoint of a traced forward): of those, the rays without a trace (head
-// < 0, none when out.trace's counter shows that every request for trace
-// room was met) and the rays with one. MODE 4: keep the rays hit.keep(ray) accepts
-// and write the miss outputs of the others (no ray loads). The
+// write the miss outputs of the others. MODE 4: keep the rays hit.keep(ray) accepts
+// and write the miss outputs of the others (no ray loads). MODE 1 (adjoint):
+// keep the rays whose forward composited a sample (the others carry no
+// gradient); with a trace (head not NULL) the rays that have one go on a second
+// list, and only the others on the first. The
 // pass is bound by the 24 bytes of ray per slot it reads; at high occupancy
 // it runs near HBM bandwidth, where the render kernel's refill rounds would
 // take one memory latency per round for every ray. Launches of fewer than
@@ -287,17 +290,45 @@ struct TreeHit {
     }
 };
 
-template <int MODE, class Hit, int GROUP = kCullGroup>
-static __global__ __launch_bounds__(kBlock) void cull_kernel(Hit hit, RayArgs ra, RenderOut out,
-                                                              const int32_t* nsamp, const int32_t* head,
-                                                              int32_t* list,
-                                                              unsigned long long* count) {
-    if constexpr (MODE == 2) {
-        // After a traced forward, out.trace holds its allocation counter and the
-        // room in samples. A trace is incomplete only if a block request went past
-        // the room's end; with none, no ray walks.
-        if (out.trace.counter && (int64_t)*out.trace.counter <= out.trace.cap) return;
+// What the adjoint's cull reads and its second list (MODE 1).
+struct CullAdjoint {
+    const int32_t* nsamp;
+    const int32_t* head;           // nullptr: no trace
+    int32_t* list2;
+    unsigned long long* count2;
+};
+
+template <int MODE, class Hit>
+__device__ __forceinline__ void cull_test(const Hit& hit, const RayArgs& ra, const RenderOut& out,
+                                          const CullAdjoint& adj, int64_t ray, bool& k, bool& k2) {
+    if constexpr (MODE == 0) {
+        const f3v ov = load3(ra.o + 3 * ray), dv = load3(ra.d + 3 * ray);
+        const float o[3] = {ov.x, ov.y, ov.z};
+        const float d[3] = {dv.x, dv.y, dv.z};
+        k = hit(o, d);
+        if (!k) write_miss(out, ray);
+    } else if constexpr (MODE == 4) {
+        k = hit.keep(ray);
+        if (!k) write_miss(out, ray);
+    } else {
+        const bool s = adj.nsamp[ray] > 0, traced = adj.head && adj.head[ray] >= 0;
+        k = s && !traced;
+        k2 = s && traced;
     }
+}
+
+// Room for n list entries of part x: one atomic by one lane. Wave-uniform.
+__device__ __forceinline__ int64_t list_room(unsigned long long* count, int x, int n) {
+    unsigned long long b = 0;
+    if ((threadIdx.x & 63) == 0) b = atomicAdd(count + x * kQueueStride, (unsigned long long)n);
+    const uint32_t b_lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b);
+    const uint32_t b_hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32));
+    return (int64_t)(((uint64_t)b_hi << 32) | b_lo);
+}
+
+template <int MODE, class Hit, int GROUP = kCullGroup>
+static __global__ __launch_bounds__(kBlock) void cull_kernel(Hit hit, RayArgs ra, RenderOut out, CullAdjoint adj,
+                                                              int32_t* list, unsigned long long* count) {
     const int lane = threadIdx.x & 63;
     const int x = (int)(blockIdx.x & (kQueues - 1));
     const int64_t n_chunks = (ra.n_slots + 63) >> 6;
@@ -325,104 +356,82 @@ static __global__ __launch_bounds__(kBlock) void cull_kernel(Hit hit, RayArgs ra
             const int64_t tx = 8 * j + jt;
             const int64_t px = 8 * tx + (lane & 7);
             const bool lane_ok = tx >= kx0 && tx < kx1 && px < ra.img_w;
-            uint64_t keep[8];
-            int total = 0;
+            uint64_t keep[8], keep2[8];
+            int total = 0, total2 = 0;
 #pragma unroll
             for (int r = 0; r < 8; ++r) {
                 const int64_t ray = (8 * ty + r) * ra.img_w + px;
-                bool k = false;
-                if (lane_ok && ray < ra.n) {
-                    if constexpr (MODE == 0) {
-                        const f3v ov = load3(ra.o + 3 * ray), dv = load3(ra.d + 3 * ray);
-                        const float o[3] = {ov.x, ov.y, ov.z};
-                        const float d[3] = {dv.x, dv.y, dv.z};
-                        k = hit(o, d);
-                        if (!k) write_miss(out, ray);
-                    } else if constexpr (MODE == 4) {
-                        k = hit.keep(ray);
-                        if (!k) write_miss(out, ray);
-                    } else {
-                        k = nsamp[ray] > 0;
-                        if constexpr (MODE == 2) k = k && head[ray] < 0;
-                        if constexpr (MODE == 3) k = k && head[ray] >= 0;
-                    }
-                }
+                bool k = false, k2 = false;
+                if (lane_ok && ray < ra.n) cull_test<MODE>(hit, ra, out, adj, ray, k, k2);
                 keep[r] = __ballot(k);
                 total += __popcll(keep[r]);
-            }
-            if (total == 0) continue;   // wave-uniform
-            unsigned long long b = 0;
-            if (lane == 0) b = atomicAdd(count + x * kQueueStride, (unsigned long long)total);
-            const uint32_t b_lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b);
-            const uint32_t b_hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32));
-            const int64_t at = lo * 64 + (int64_t)(((uint64_t)b_hi << 32) | b_lo);
-            // this lane's tile: its kept-slot mask (bit 8r + column) and the rays
-            // kept in the segment's earlier tiles
-            uint64_t tm = 0ull;
-            int before = 0;
-            const uint64_t below = jt ? (~0ull >> (64 - 8 * jt)) : 0ull;
-#pragma unroll
-            for (int r = 0; r < 8; ++r) {
-                tm |= ((keep[r] >> (8 * jt)) & 0xffull) << (8 * r);
-                before += __popcll(keep[r] & below);
-            }
-#pragma unroll
-            for (int r = 0; r < 8; ++r) {
-                if ((keep[r] >> lane) & 1ull) {
-                    const int within = 8 * r + (lane & 7);
-                    const int64_t ray = (8 * ty + r) * ra.img_w + px;
-                    list[at + before + __popcll(tm & ((1ull << within) - 1ull))] = (int32_t)ray;
+                if constexpr (MODE == 1) {
+                    keep2[r] = __ballot(k2);
+                    total2 += __popcll(keep2[r]);
                 }
             }
+            // lists the kept rays: per lane its tile's kept-slot mask (bit 8r + column) and
+            // the rays kept in the segment's earlier tiles
+            auto emit = [&](const uint64_t(&kp)[8], int n, int32_t* ls, unsigned long long* ct) {
+                const int64_t at = lo * 64 + list_room(ct, x, n);
+                uint64_t tm = 0ull;
+                int before = 0;
+                const uint64_t below = jt ? (~0ull >> (64 - 8 * jt)) : 0ull;
+#pragma unroll
+                for (int r = 0; r < 8; ++r) {
+                    tm |= ((kp[r] >> (8 * jt)) & 0xffull) << (8 * r);
+                    before += __popcll(kp[r] & below);
+                }
+#pragma unroll
+                for (int r = 0; r < 8; ++r) {
+                    if ((kp[r] >> lane) & 1ull) {
+                        const int within = 8 * r + (lane & 7);
+                        const int64_t ray = (8 * ty + r) * ra.img_w + px;
+                        ls[at + before + __popcll(tm & ((1ull << within) - 1ull))] = (int32_t)ray;
+                    }
+                }
+            };
+            if (total) emit(keep, total, list, count);   // wave-uniform
+            if constexpr (MODE == 1)
+                if (total2) emit(keep2, total2, adj.list2, adj.count2);
         }
         return;
     }
     for (int64_t c0 = lo + wi * GROUP; c0 < hi; c0 += nw * GROUP) {
-        uint64_t keep[GROUP];
+        uint64_t keep[GROUP], keep2[GROUP];
         int32_t rays[GROUP];
-        int total = 0;
+        int total = 0, total2 = 0;
 #pragma unroll
         for (int j = 0; j < GROUP; ++j) {
             const int64_t c = c0 + j;
             const int64_t ray = c < hi ? slot_to_ray(ra, c * 64 + lane) : -1;
-            bool k = false;
-            if (ray >= 0) {
-                if constexpr (MODE == 0) {
-                    const f3v ov = load3(ra.o + 3 * ray), dv = load3(ra.d + 3 * ray);
-                    const float o[3] = {ov.x, ov.y, ov.z};
-                    const float d[3] = {dv.x, dv.y, dv.z};
-                    k = hit(o, d);
-                    if (!k) write_miss(out, ray);
-                } else if constexpr (MODE == 4) {
-                    k = hit.keep(ray);
-                    if (!k) write_miss(out, ray);
-                } else {
-                    k = nsamp[ray] > 0;
-                    if constexpr (MODE == 2) k = k && head[ray] < 0;
-                    if constexpr (MODE == 3) k = k && head[ray] >= 0;
-                }
-            }
+            bool k = false, k2 = false;
+            if (ray >= 0) cull_test<MODE>(hit, ra, out, adj, ray, k, k2);
             keep[j] = __ballot(k);
             rays[j] = (int32_t)ray;
             total += __popcll(keep[j]);
+            if constexpr (MODE == 1) {
+                keep2[j] = __ballot(k2);
+                total2 += __popcll(keep2[j]);
+            }
         }
-        if (total == 0) continue;   // wave-uniform
-        unsigned long long b = 0;
-        if (lane == 0) b = atomicAdd(count + x * kQueueStride, (unsigned long long)total);
-        const uint32_t b_lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b);
-        const uint32_t b_hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32));
-        int64_t at = lo * 64 + (int64_t)(((uint64_t)b_hi << 32) | b_lo);
+        auto emit = [&](const uint64_t(&kp)[GROUP], int n, int32_t* ls, unsigned long long* ct) {
+            int64_t at = lo * 64 + list_room(ct, x, n);
 #pragma unroll
-        for (int j = 0; j < GROUP; ++j) {
-            if ((keep[j] >> lane) & 1ull) list[at + lane_rank(keep[j])] = rays[j];
-            at += __popcll(keep[j]);
-        }
+            for (int j = 0; j < GROUP; ++j) {
+                if ((kp[j] >> lane) & 1ull) ls[at + lane_rank(kp[j])] = rays[j];
+                at += __popcll(kp[j]);
+            }
+        };
+        if (total) emit(keep, total, list, count);   // wave-uniform
+        if constexpr (MODE == 1)
+            if (total2) emit(keep2, total2, adj.list2, adj.count2);
     }
 }
 
 template <int MODE, class Hit>
-static hipError_t launch_cull_hit(const Hit& hit, const RayArgs& ra, const RenderOut& out, const int32_t* nsamp,
-                                  const int32_t* head, int32_t* list, unsigned long long* count, hipStream_t st) {
+static hipError_t launch_cull_hit(const Hit& hit, const RayArgs& ra, const RenderOut& out, const CullAdjoint& adj,
+                                  int32_t* list, unsigned long long* count, hipStream_t st) {
     const int64_t n_chunks = (ra.n_slots + 63) >> 6;
     const bool small = ra.img_w <= 0 && n_chunks < kCullSmall;
     const int group = small ? kCullGroupSmall : kCullGroup;
@@ -433,32 +442,26 @@ static hipError_t launch_cull_hit(const Hit& hit, const RayArgs& ra, const Rende
     if (blocks < 1) blocks = 1;
     const dim3 grid((unsigned)(blocks * kQueues));
     if (small)
-        hipLaunchKernelGGL((cull_kernel<MODE, Hit, kCullGroupSmall>), grid, dim3(kBlock), 0, st, hit, ra, out, nsamp,
-                           head, list, count);
+        hipLaunchKernelGGL((cull_kernel<MODE, Hit, kCullGroupSmall>), grid, dim3(kBlock), 0, st, hit, ra, out, adj, list,
+                           count);
     else
-        hipLaunchKernelGGL((cull_kernel<MODE, Hit>), grid, dim3(kBlock), 0, st, hit, ra, out, nsamp, head, list, count);
+        hipLaunchKernelGGL((cull_kernel<MODE, Hit>), grid, dim3(kBlock), 0, st, hit, ra, out, adj, list, count);
     return hipGetLastError();
-}
-
-template <int MODE>
-static hipError_t launch_cull(const TreeArgs& tr, const InstArgs& in, const RayArgs& ra, const RenderOut& out,
-                              const int32_t* nsamp, const int32_t* head, int32_t* list, unsigned long long* count,
-                              hipStream_t st) {
-    if (in.identity) return launch_cull_hit<MODE>(TreeHit<true>{tr, in}, ra, out, nsamp, head, list, count, st);
-    return launch_cull_hit<MODE>(TreeHit<false>{tr, in}, ra, out, nsamp, head, list, count, st);
 }
 
 // Runs launch(ra) with the launch's queue counters set; rays are the slots.
 // ws: caller-provided scratch of at least list_scratch_bytes(n_slots) bytes
-// (nothing is allocated), or nullptr to take it from the pool.
+// (nothing is allocated), or nullptr to take it from the pool. extra: a counter
+// that starts at zero with the launch, or nullptr.
 template <typename Launch>
-static hipError_t with_queue(const RayArgs& ra_in, hipStream_t st, Launch&& launch, void* ws = nullptr) {
+static hipError_t with_queue(const RayArgs& ra_in, hipStream_t st, Launch&& launch, void* ws = nullptr,
+                             unsigned long long* extra = nullptr) {
     RayArgs ra = ra_in;
     void* q = ws;
     hipError_t e = ws ? hipSuccess : work_alloc(&q, kQueues * kQueueStride * sizeof(unsigned long long), st);
     if (e != hipSuccess) return e;
     ra.queue = static_cast<unsigned long long*>(q);
-    hipLaunchKernelGGL(zero_queue_kernel, dim3(1), dim3(kQueues * kQueueStride), 0, st, ra.queue);
+    hipLaunchKernelGGL(zero_queue_kernel, dim3(1), dim3(kQueues * kQueueStride), 0, st, ra.queue, extra);
     e = hipGetLastError();
     if (e == hipSuccess) e = launch(ra);
     const hipError_t f = ws ? hipSuccess : work_free(q, st);
@@ -470,11 +473,11 @@ static_assert(2 * kQueues * kQueueStride * sizeof(unsigned long long) == kListHe
 
 // Candidate form: cull(list, count) lists the rays, then launch(ra) runs over
 // them. Ray indices must fit int32; larger launches take the slot form (the
-// render kernels then test every ray themselves). ws as in with_queue.
+// render kernels then test every ray themselves). ws and extra as in with_queue.
 template <typename Cull, typename Launch>
 static hipError_t with_list(const RayArgs& ra_in, hipStream_t st, Cull&& cull, Launch&& launch,
-                            void* ws = nullptr) {
-    if (ra_in.n > (int64_t)INT32_MAX) return with_queue(ra_in, st, launch, ws);
+                            void* ws = nullptr, unsigned long long* extra = nullptr) {
+    if (ra_in.n > (int64_t)INT32_MAX) return with_queue(ra_in, st, launch, ws, extra);
     const size_t qbytes = kListHeaderBytes;
     RayArgs ra = ra_in;
     void* q = ws;
@@ -485,7 +488,7 @@ static hipError_t with_list(const RayArgs& ra_in, hipStream_t st, Cull&& cull, L
     int32_t* list = reinterpret_cast<int32_t*>(static_cast<char*>(q) + qbytes);
     ra.count = count;
     ra.list = list;
-    hipLaunchKernelGGL(zero_queue_kernel, dim3(1), dim3(2 * kQueues * kQueueStride), 0, st, ra.queue);
+    hipLaunchKernelGGL(zero_queue_kernel, dim3(1), dim3(2 * kQueues * kQueueStride), 0, st, ra.queue, extra);
     e = hipGetLastError();
     if (e == hipSuccess) e = cull(list, count);
     if (e == hipSuccess) e = launch(ra);
@@ -493,17 +496,19 @@ static hipError_t with_list(const RayArgs& ra_in, hipStream_t st, Cull&& cull, L
     return e != hipSuccess ? e : f;
 }
 
-// Candidate form with the cull pass of one placed tree (MODE as in cull_kernel).
-template <int MODE, typename Launch>
-static hipError_t with_candidates(const TreeArgs& tr, const InstArgs& in, const RayArgs& ra_in,
-                                  const RenderOut& out, const int32_t* nsamp, hipStream_t st, Launch&& launch,
-                                  const int32_t* head = nullptr, void* ws = nullptr) {
+// Candidate form of a forward: the cull pass of one placed tree. The counter of
+// out's trace, if it has one, starts at zero.
+template <typename Launch>
+static hipError_t with_candidates(const TreeArgs& tr, const InstArgs& in, const RayArgs& ra_in, const RenderOut& out,
+                                  hipStream_t st, Launch&& launch, void* ws = nullptr) {
     return with_list(
         ra_in, st,
         [&](int32_t* list, unsigned long long* count) {
-            return launch_cull<MODE>(tr, in, ra_in, out, nsamp, head, list, count, st);
+            if (in.identity)
+                return launch_cull_hit<0>(TreeHit<true>{tr, in}, ra_in, out, CullAdjoint{}, list, count, st);
+            return launch_cull_hit<0>(TreeHit<false>{tr, in}, ra_in, out, CullAdjoint{}, list, count, st);
         },
-        launch, ws);
+        launch, ws, out.trace.head ? out.trace.counter : nullptr);
 }
 
 // ----------------------------------------------------------------------------
@@ -512,11 +517,11 @@ static hipError_t with_candidates(const TreeArgs& tr, const InstArgs& in, const 
 // LDS rows per wavefront for the transposition of finished leaf rows
 constexpr int kFlushSlots = 16;
 
-static __global__ void record_init_kernel(int32_t* head, int64_t n, unsigned long long* counter,
-                                          unsigned long long* leaf_cursor) {
+// Clears hdr (n_hdr counters) and sets the n leaf heads to "no record".
+static __global__ void adjoint_init_kernel(unsigned long long* hdr, int n_hdr, int32_t* head, int64_t n) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) head[i] = -1;
-    if (i == 0) *counter = *leaf_cursor = 0ull;
+    if (i < n_hdr) hdr[i] = 0ull;
 }
 
 // Items a wavefront takes from the room's counter at a time: a 16,384th of the
@@ -647,28 +652,64 @@ __device__ __forceinline__ void feed_leaves(LeafFeeder& f, const RecordArgs& rec
     }
 }
 
-// Takes the record scratch of one adjoint launch (cap > 0) from the pool and
-// queues its initialisation: the counter of records and a leaf cursor,
-// the leaf heads (-1) and room for cap records of 32 bytes. With
-// cap == 0 rec stays empty (per-sample atomics only).
-static hipError_t records_begin(const TreeArgs& tr, int64_t cap, hipStream_t st, RecordArgs& rec, void*& mem) {
-    rec = RecordArgs{};
-    mem = nullptr;
-    if (cap <= 0) return hipSuccess;
-    const size_t head_b = ((size_t)tr.n_leaves * sizeof(int32_t) + 255) & ~(size_t)255;
-    const size_t rec_b = (size_t)cap * 2 * sizeof(int4);
-    constexpr size_t hdr = 2048;
-    hipError_t e = work_alloc(&mem, hdr + head_b + rec_b, st);
-    if (e != hipSuccess) return e;
-    char* p = static_cast<char*>(mem);
-    rec.counter = reinterpret_cast<unsigned long long*>(p);
-    rec.leaf_cursor = reinterpret_cast<unsigned long long*>(p + 1024);
-    rec.head = reinterpret_cast<int32_t*>(p + hdr);
-    rec.rec = reinterpret_cast<int4*>(p + hdr + head_b);
-    rec.cap = cap;
-    hipLaunchKernelGGL(record_init_kernel, dim3((unsigned)((tr.n_leaves + 255) / 256)), dim3(256), 0, st, rec.head,
-                       tr.n_leaves, rec.counter, rec.leaf_cursor);
-    return hipGetLastError();
+// Scratch of one adjoint call, taken from the pool in one piece and initialised
+// by one kernel: the queues and list counts of the rays that walk and of those
+// that replay their trace, the lists, the counter of records, the leaf heads
+// and the records (room for cap of 32 bytes; with cap == 0 rec stays empty:
+// per-sample atomics only). One cull pass then lists the rays. (An allocation,
+// a clearing kernel and a cull pass per list and another of each for the
+// records cost an adjoint of four 1920 x 1080 layers about 25 us a layer.)
+struct AdjointScratch {
+    RayArgs walk, replay;
+    RecordArgs rec;
+    void* mem;
+};
+struct NoHit {};
+static hipError_t adjoint_begin(const TreeArgs& tr, const RayArgs& ra, const int32_t* nsamp, const int32_t* trace_head,
+                                int64_t cap, hipStream_t st, AdjointScratch& s) {
+    s = AdjointScratch{ra, ra, RecordArgs{}, nullptr};
+    const bool listed = ra.n <= (int64_t)INT32_MAX;   // else the slot form: the walking kernel tests every ray
+    if (trace_head && !listed) return hipErrorInvalidValue;
+    constexpr int kCounters = kQueues * kQueueStride;
+    constexpr int n_hdr = 4 * kCounters + kQueueStride;
+    constexpr size_t hdr = ((size_t)n_hdr * sizeof(unsigned long long) + 255) & ~(size_t)255;
+    const size_t list_b = listed ? (size_t)((ra.n_slots + 63) >> 6) * 64 * sizeof(int32_t) : 0;
+    const size_t lists = trace_head ? 2 * list_b : list_b;
+    const size_t head_b = cap > 0 ? ((size_t)tr.n_leaves * sizeof(int32_t) + 255) & ~(size_t)255 : 0;
+    hipError_t e = work_alloc(&s.mem, hdr + lists + head_b + (size_t)(cap > 0 ? cap : 0) * 2 * sizeof(int4), st);
+    if (e != hipSuccess) {
+        s.mem = nullptr;
+        return e;
+    }
+    char* p = static_cast<char*>(s.mem);
+    auto* counters = reinterpret_cast<unsigned long long*>(p);
+    auto* list = reinterpret_cast<int32_t*>(p + hdr);
+    auto* list2 = reinterpret_cast<int32_t*>(p + hdr + list_b);
+    s.walk.queue = counters;
+    s.replay.queue = counters + 2 * kCounters;
+    if (cap > 0) {
+        s.rec.counter = counters + 4 * kCounters;
+        s.rec.head = reinterpret_cast<int32_t*>(p + hdr + lists);
+        s.rec.rec = reinterpret_cast<int4*>(p + hdr + lists + head_b);
+        s.rec.cap = cap;
+    }
+    const int64_t n_init = cap > 0 && tr.n_leaves > n_hdr ? tr.n_leaves : n_hdr;
+    hipLaunchKernelGGL(adjoint_init_kernel, dim3((unsigned)((n_init + 255) / 256)), dim3(256), 0, st, counters, n_hdr,
+                       s.rec.head, cap > 0 ? tr.n_leaves : 0);
+    e = hipGetLastError();
+    if (e == hipSuccess && listed) {
+        s.walk.list = list;
+        s.walk.count = counters + kCounters;
+        s.replay.list = list2;
+        s.replay.count = counters + 3 * kCounters;
+        const CullAdjoint adj{nsamp, trace_head, list2, counters + 3 * kCounters};
+        e = launch_cull_hit<1>(NoHit{}, ra, RenderOut{}, adj, list, counters + kCounters, st);
+    }
+    return e;
+}
+static hipError_t adjoint_end(const AdjointScratch& s, hipError_t e, hipStream_t st) {
+    const hipError_t f = s.mem ? work_free(s.mem, st) : hipSuccess;
+    return e != hipSuccess ? e : f;
 }
 
 }  // namespace neuvv

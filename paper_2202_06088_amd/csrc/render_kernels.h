@@ -918,10 +918,6 @@ __global__ __launch_bounds__(kBlock) void reduce_records_kernel(TreeArgs tr, Ins
 template <int K, int C, int DT, bool EDIT, bool TRACE>
 static hipError_t fwd_e(const TreeArgs& tr, const InstArgs& in, const RayArgs& ra, float t_stop, const RenderOut& o,
                         hipStream_t st) {
-    if constexpr (TRACE) {
-        // the trace's allocation counters start at zero
-        hipLaunchKernelGGL(zero_queue_kernel, dim3(1), dim3(kQueues * kQueueStride), 0, st, o.trace.counter);
-    }
     if (in.identity) {
         auto kern = render_fwd_kernel<K, C, DT, true, EDIT, TRACE>;
         hipLaunchKernelGGL(kern, dim3(grid_for(kern, ra)), dim3(kBlock), 0, st, tr, in, ra, t_stop, o);
@@ -972,24 +968,11 @@ static hipError_t bwd_t(const TreeArgs& tr, const InstArgs& in, const RayArgs& r
     // records need int32 ray and record indices
     const int64_t cap =
         ra.n <= (int64_t)INT32_MAX && tr.n_leaves > 0 && tr.n_leaves <= (int64_t)INT32_MAX ? io.record_cap : 0;
-    RecordArgs rec{};
-    void* mem = nullptr;
-    hipError_t e = records_begin(tr, cap, st, rec, mem);
-    if (e == hipSuccess) {
-        // one cull pass and render adjoint per source of samples: rays that walk,
-        // and (traced forward) rays that replay their trace
-        auto walk = [&](const RayArgs& r) { return bwd_walk<K, C, DT>(tr, in, r, io, rec, st); };
-        auto replay = [&](const RayArgs& r) { return bwd_replay<K, C, DT>(tr, in, r, io, rec, st); };
-        // the walking adjoint's cull reads whether the forward's traces are all complete
-        const RenderOut trace_out{nullptr, nullptr, nullptr, nullptr, nullptr, io.trace};
-        if (io.trace.head) {
-            if (ra.n > (int64_t)INT32_MAX) e = hipErrorInvalidValue;   // traced calls take candidate lists
-            if (e == hipSuccess) e = with_candidates<2>(tr, in, ra, trace_out, io.nsamp, st, walk, io.trace.head);
-            if (e == hipSuccess) e = with_candidates<3>(tr, in, ra, RenderOut{}, io.nsamp, st, replay, io.trace.head);
-        } else {
-            e = with_candidates<1>(tr, in, ra, RenderOut{}, io.nsamp, st, walk);
-        }
-    }
+    AdjointScratch sc;
+    hipError_t e = adjoint_begin(tr, ra, io.nsamp, io.trace.head, cap, st, sc);
+    const RecordArgs& rec = sc.rec;
+    if (e == hipSuccess) e = bwd_walk<K, C, DT>(tr, in, sc.walk, io, rec, st);
+    if (e == hipSuccess && io.trace.head) e = bwd_replay<K, C, DT>(tr, in, sc.replay, io, rec, st);
     if (e == hipSuccess && cap > 0) {
         // persistent: four blocks per CU
         int64_t blocks = (tr.n_leaves + kBlock - 1) / kBlock;
@@ -1013,11 +996,7 @@ static hipError_t bwd_t(const TreeArgs& tr, const InstArgs& in, const RayArgs& r
         }
         e = hipGetLastError();
     }
-    if (mem) {
-        const hipError_t f = work_free(mem, st);
-        if (e == hipSuccess) e = f;
-    }
-    return e;
+    return adjoint_end(sc, e, st);
 }
 
 
@@ -1028,10 +1007,9 @@ template <int K, int C>
 hipError_t launch_render_fwd_shape(int dtype, const TreeArgs& tr, const InstArgs& in, const RayArgs& ra,
                                    float t_stop, const RenderOut& out, hipStream_t stream, void* ws) {
     auto run = [&](auto dt) {
-        return with_candidates<0>(
-            tr, in, ra, out, nullptr, stream,
-            [&](const RayArgs& r) { return fwd_t<K, C, decltype(dt)::value>(tr, in, r, t_stop, out, stream); },
-            nullptr, ws);
+        return with_candidates(
+            tr, in, ra, out, stream,
+            [&](const RayArgs& r) { return fwd_t<K, C, decltype(dt)::value>(tr, in, r, t_stop, out, stream); }, ws);
     };
     switch (dtype) {
         case 0: return run(std::integral_constant<int, 0>{});

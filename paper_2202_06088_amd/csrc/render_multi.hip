@@ -592,7 +592,7 @@ static hipError_t multi_lists(const MultiArgs& ma, const RayArgs& ra, float t_st
         e = with_list(
             ra, st,
             [&](int32_t* list, unsigned long long* count) {
-                return launch_cull_hit<0>(AnyTreeHit<L>{ma}, ra, RenderOut{}, nullptr, nullptr, list, count, st);
+                return launch_cull_hit<0>(AnyTreeHit<L>{ma}, ra, RenderOut{}, CullAdjoint{}, list, count, st);
             },
             [&](const RayArgs& r) {
                 hipError_t le = hipSuccess;
@@ -619,7 +619,7 @@ static hipError_t multi_lists(const MultiArgs& ma, const RayArgs& ra, float t_st
         e = with_list(
             ra, st,
             [&](int32_t* list, unsigned long long* count) {
-                return launch_cull_hit<4>(AnyList<L>{head, n}, ra, o, nullptr, nullptr, list, count, st);
+                return launch_cull_hit<4>(AnyList<L>{head, n}, ra, o, CullAdjoint{}, list, count, st);
             },
             [&](const RayArgs& rm) {
                 auto kern = merge_lists_kernel<L>;
@@ -650,7 +650,7 @@ static hipError_t multi_t(const MultiArgs& ma, const RayArgs& ra, float t_stop, 
     return with_list(
         ra, st,
         [&](int32_t* list, unsigned long long* count) {
-            return launch_cull_hit<0>(AnyTreeHit<L>{ma}, ra, o, nullptr, nullptr, list, count, st);
+            return launch_cull_hit<0>(AnyTreeHit<L>{ma}, ra, o, CullAdjoint{}, list, count, st);
         },
         [&](const RayArgs& r) {
             auto kern = render_multi_kernel<L, DT>;

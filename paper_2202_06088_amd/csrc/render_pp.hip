@@ -928,10 +928,6 @@ __global__ __launch_bounds__(kBlock) void reduce_pp_records_kernel(TreeArgs tr, 
 template <int DT, bool TRACE>
 static hipError_t pp_fwd_e(const TreeArgs& tr, const InstArgs& in, const RayArgs& ra, float t_stop,
                            const RenderOut& o, hipStream_t st) {
-    if constexpr (TRACE) {
-        // the trace's allocation counters start at zero
-        hipLaunchKernelGGL(zero_queue_kernel, dim3(1), dim3(kQueues * kQueueStride), 0, st, o.trace.counter);
-    }
     if (in.identity) {
         auto kern = render_pp_fwd_kernel<DT, true, TRACE>;
         hipLaunchKernelGGL(kern, dim3(grid_for(kern, ra)), dim3(kBlock), 0, st, tr, in, ra, t_stop, o);
@@ -965,26 +961,11 @@ static hipError_t pp_bwd_t(const TreeArgs& tr, const InstArgs& in, const RayArgs
                                 tr.n_leaves <= (int64_t)INT32_MAX
                             ? io.record_cap
                             : 0;
-    RecordArgs rec{};
-    void* mem = nullptr;
-    hipError_t e = records_begin(tr, cap, st, rec, mem);
-    if (e == hipSuccess) {
-        // one cull pass and adjoint per source of samples: rays that walk, and
-        // (traced forward) rays that replay their trace
-        auto walk = [&](const RayArgs& r) { return pp_bwd_k<DT, false>(tr, in, r, io, rec, st); };
-        auto replay = [&](const RayArgs& r) { return pp_bwd_k<DT, true>(tr, in, r, io, rec, st); };
-        // the walking adjoint's cull reads whether the forward's traces are all complete
-        TraceArgs room = io.trace;
-        room.cap = io.trace.cap / 2;   // two entries per sample
-        const RenderOut trace_out{nullptr, nullptr, nullptr, nullptr, nullptr, room};
-        if (io.trace.head) {
-            if (ra.n > (int64_t)INT32_MAX) e = hipErrorInvalidValue;   // traced calls take candidate lists
-            if (e == hipSuccess) e = with_candidates<2>(tr, in, ra, trace_out, io.nsamp, st, walk, io.trace.head);
-            if (e == hipSuccess) e = with_candidates<3>(tr, in, ra, RenderOut{}, io.nsamp, st, replay, io.trace.head);
-        } else {
-            e = with_candidates<1>(tr, in, ra, RenderOut{}, io.nsamp, st, walk);
-        }
-    }
+    AdjointScratch sc;
+    hipError_t e = adjoint_begin(tr, ra, io.nsamp, io.trace.head, cap, st, sc);
+    const RecordArgs& rec = sc.rec;
+    if (e == hipSuccess) e = pp_bwd_k<DT, false>(tr, in, sc.walk, io, rec, st);
+    if (e == hipSuccess && io.trace.head) e = pp_bwd_k<DT, true>(tr, in, sc.replay, io, rec, st);
     if (e == hipSuccess && cap > 0) {
         int64_t blocks = (tr.n_leaves + kBlock - 1) / kBlock;
         const int64_t lim = (int64_t)device_cu_count() * 4;
@@ -997,21 +978,22 @@ static hipError_t pp_bwd_t(const TreeArgs& tr, const InstArgs& in, const RayArgs
                                tr, in, ra, rec, io);
         e = hipGetLastError();
     }
-    if (mem) {
-        const hipError_t f = work_free(mem, st);
-        if (e == hipSuccess) e = f;
-    }
-    return e;
+    return adjoint_end(sc, e, st);
 }
 
 hipError_t launch_render_pp_fwd(int dtype, const TreeArgs& tr, const InstArgs& in, const RayArgs& ra, float t_stop,
                                 const RenderOut& out, hipStream_t stream, void* ws) {
     if (ra.n_slots <= 0) return hipSuccess;
-    switch (dtype) {
-        case 0: return with_candidates<0>(tr, in, ra, out, nullptr, stream, [&](const RayArgs& r) { return pp_fwd_t<0>(tr, in, r, t_stop, out, stream); }, nullptr, ws);
-        case 1: return with_candidates<0>(tr, in, ra, out, nullptr, stream, [&](const RayArgs& r) { return pp_fwd_t<1>(tr, in, r, t_stop, out, stream); }, nullptr, ws);
-        default: return with_candidates<0>(tr, in, ra, out, nullptr, stream, [&](const RayArgs& r) { return pp_fwd_t<2>(tr, in, r, t_stop, out, stream); }, nullptr, ws);
-    }
+    return with_candidates(
+        tr, in, ra, out, stream,
+        [&](const RayArgs& r) {
+            switch (dtype) {
+                case 0: return pp_fwd_t<0>(tr, in, r, t_stop, out, stream);
+                case 1: return pp_fwd_t<1>(tr, in, r, t_stop, out, stream);
+                default: return pp_fwd_t<2>(tr, in, r, t_stop, out, stream);
+            }
+        },
+        ws);
 }
 
 hipError_t launch_render_pp_bwd(int dtype, const TreeArgs& tr, const InstArgs& in, const RayArgs& ra,
