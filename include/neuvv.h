@@ -264,6 +264,20 @@ int neuvv_pack_rows(int32_t R, int32_t dtype, int32_t layout, int64_t n_leaves, 
                     const int64_t* slot_of_input, void* out, void* stream);
 
 /*
+ * neuvv_unpack_grad_rows - rearranges leaf gradient rows (layout above) into
+ * the float32 payload layout, slot order kept, padding values zero: for an
+ * element-wise optimizer step on float32 payload arrays.
+ * grad_leaf       device [n_leaves][ROW], ROW = neuvv_grad_row_elems(K, C, Cg).
+ * layout          neuvv_layout of the outputs.
+ * hh_out, wsig_out, wgam_out  device outputs of ceil(R/4) * n_leaves * 4
+ *                 floats for R = 3K, C and Cg, 16-byte aligned; wgam_out may
+ *                 be NULL when Cg = 0.
+ * Errors: ARG, RANGE (K, C, Cg, n_leaves >= 2^31), UNSUPPORTED (layout), HIP.
+ */
+int neuvv_unpack_grad_rows(int32_t K, int32_t C, int32_t Cg, int32_t layout, int64_t n_leaves, const float* grad_leaf,
+                           float* hh_out, float* wsig_out, float* wgam_out, void* stream);
+
+/*
  * neuvv_render - volume rendering of a VOctree along n rays (Sec. 4.3
  * "Rendering", Eq. 4, 5, 8, 9).
  *

@@ -245,6 +245,24 @@ int neuvv_pack_rows(int32_t R, int32_t dtype, int32_t layout, int64_t n_leaves, 
     NEUVV_GUARD_END
 }
 
+int neuvv_unpack_grad_rows(int32_t K, int32_t C, int32_t Cg, int32_t layout, int64_t n_leaves, const float* grad_leaf,
+                           float* hh_out, float* wsig_out, float* wgam_out, void* stream) {
+    NEUVV_GUARD_BEGIN
+    if (K < 1 || K > 30 || C < 1 || C > 64 || Cg < 0 || Cg > 64)
+        return fail(NEUVV_ERR_RANGE, "K in [1,30], C in [1,64] and Cg in [0,64] required");
+    if (layout < 0 || layout > 1) return fail(NEUVV_ERR_UNSUPPORTED, "unknown layout %d", layout);
+    if (n_leaves < 0) return fail(NEUVV_ERR_ARG, "n_leaves < 0");
+    if (n_leaves > (int64_t)INT32_MAX) return fail(NEUVV_ERR_RANGE, "n_leaves must be below 2^31");
+    if (n_leaves > 0 && (!grad_leaf || !hh_out || !wsig_out || (Cg > 0 && !wgam_out)))
+        return fail(NEUVV_ERR_ARG, "NULL buffer");
+    if (((uintptr_t)hh_out | (uintptr_t)wsig_out | (uintptr_t)wgam_out) & 15)
+        return fail(NEUVV_ERR_ARG, "outputs must be 16-byte aligned");
+    return hip_status(neuvv::launch_unpack_rows(K, C, Cg, layout, n_leaves, grad_leaf, hh_out, wsig_out, wgam_out,
+                                                (hipStream_t)stream),
+                      "unpack_grad_rows launch");
+    NEUVV_GUARD_END
+}
+
 int neuvv_pack_leaves(int32_t K, int32_t C, int32_t dtype, int32_t layout, int64_t n_leaves, const float* hh_in,
                       const float* wsig_in, const int64_t* slot_of_input, void* hh_out, void* wsig_out,
                       void* stream) {

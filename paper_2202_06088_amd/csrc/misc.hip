@@ -5,6 +5,7 @@
 //  * eval_hh: the per-ray HH basis on its own (Eq. 2-4), a test hook;
 //  * pack: leaf coefficients into the 16-byte-vector structure-of-arrays
 //    storage layout, with round-to-nearest-even for 16-bit storage;
+//  * unpack_rows: gradient rows into the float32 payload layout;
 //  * directory: the brick directory of a node table (one descent per 4^3
 //    region of leaf cells, done once per tree).
 // All are memory-bound streaming kernels: one thread per pixel / ray / leaf,
@@ -272,6 +273,46 @@ __global__ __launch_bounds__(kEwBlock) void eval_hh_kernel(int K, int64_t n, con
 hipError_t launch_eval_hh(int K, int64_t n, const float* dirs, const float* gam, float* out, hipStream_t stream) {
     if (n <= 0) return hipSuccess;
     hipLaunchKernelGGL(eval_hh_kernel, dim3(ew_grid(n)), dim3(kEwBlock), 0, stream, K, n, dirs, gam, out);
+    return hipGetLastError();
+}
+
+// ----------------------------------------------------------------------------
+// gradient rows -> the float32 payload layout
+
+// One thread per (leaf, vector) of the three arrays; consecutive threads read
+// consecutive values of one gradient row. Bound by its bytes: 256 read and 224
+// written per leaf at K = 16, C = 8. (Five framework kernels that cleared the
+// arrays and copied slices into them took 105 us for 500,000 leaves.)
+__global__ __launch_bounds__(kEwBlock) void unpack_rows_kernel(int K3, int C, int Cg, int row, int layout, uint32_t n,
+                                                               const float* __restrict__ rows, float4* __restrict__ hh,
+                                                               float4* __restrict__ wsig, float4* __restrict__ wgam) {
+    const uint32_t gh = (K3 + 3) / 4, gs = (C + 3) / 4, gg = (Cg + 3) / 4, per = gh + gs + gg;
+    const uint32_t step = gridDim.x * (kEwBlock / 64);   // a wavefront takes 64 vectors' worth of leaves at a time
+    const uint32_t lane = threadIdx.x & 63u;
+    // leaves per wavefront pass, so that vector indices stay small and the division is by a small constant
+    const uint32_t lpp = 64u / per > 0u ? 64u / per : 1u;
+    for (uint32_t w = blockIdx.x * (kEwBlock / 64) + (threadIdx.x >> 6); (uint64_t)w * lpp < n; w += step) {
+        for (uint32_t v = lane; v < lpp * per; v += 64u) {
+            const uint32_t l = v / per, g = v - l * per, s = w * lpp + l;
+            if (s >= n) continue;
+            const bool a = g < gh, b = !a && g < gh + gs;
+            const uint32_t gi = a ? g : (b ? g - gh : g - gh - gs), ng = a ? gh : (b ? gs : gg);
+            const int R = a ? K3 : (b ? C : Cg), start = a ? 0 : (b ? K3 : K3 + C);
+            const float* src = rows + (int64_t)s * row + start + 4 * gi;
+            const int left = R - 4 * (int)gi;
+            const float4 o = make_float4(src[0], left > 1 ? src[1] : 0.0f, left > 2 ? src[2] : 0.0f, left > 3 ? src[3] : 0.0f);
+            (a ? hh : (b ? wsig : wgam))[layout ? (int64_t)s * ng + gi : (int64_t)gi * n + s] = o;
+        }
+    }
+}
+
+hipError_t launch_unpack_rows(int K, int C, int Cg, int layout, int64_t n, const float* rows, float* hh, float* wsig,
+                              float* wgam, hipStream_t stream) {
+    if (n <= 0) return hipSuccess;
+    const int per = (3 * K + 3) / 4 + (C + 3) / 4 + (Cg + 3) / 4;
+    hipLaunchKernelGGL(unpack_rows_kernel, dim3(ew_grid(n * per)), dim3(kEwBlock), 0, stream, 3 * K, C, Cg,
+                       grad_row_elems(K, C, Cg), layout, (uint32_t)n, rows, reinterpret_cast<float4*>(hh),
+                       reinterpret_cast<float4*>(wsig), reinterpret_cast<float4*>(wgam));
     return hipGetLastError();
 }
 

@@ -171,16 +171,9 @@ class VOctree:
     def rows_to_payload_f32(self, grad_leaf: torch.Tensor):
         """Leaf gradient rows -> the float32 payload layout of hh and wsig (and wgam), a
         rearrangement only, for an element-wise optimizer step on float32 payload tensors."""
-        N, K, C, G = self.n_leaves, self.K, self.C, self.Cg
-        rows = grad_leaf.view(N, self.grad_row)
-        parts = [(0, 3 * K), (3 * K, C)] + ([(3 * K + C, G)] if G > 0 else [])
-        out = []
-        for start, R in parts:
-            ng = -(-R // 4)
-            a = torch.zeros(N, ng * 4, device=rows.device)
-            a[:, :R] = rows[:, start:start + R]
-            if self.layout == _lib.LAYOUT_LEAF_ROWS:
-                out.append(a.reshape(-1).contiguous())
-            else:
-                out.append(a.view(N, ng, 4).permute(1, 0, 2).reshape(-1).contiguous())
+        N = self.n_leaves
+        rows = grad_leaf.view(N, self.grad_row).detach().to(self.nodes.device, torch.float32).contiguous()
+        out = [torch.empty(N * (-(-R // 4) * 4), device=rows.device)
+               for R in (3 * self.K, self.C) + ((self.Cg,) if self.Cg > 0 else ())]
+        _lib.neuvv_unpack_grad_rows(self.K, self.C, self.Cg, self.layout, N, rows, *out)
         return tuple(out)

@@ -57,3 +57,22 @@ def test_pinhole_edges(width, height):
         ro, rd = OC.pinhole_rays(width, height, intr, c, pix)
         o, d = ops.pinhole_rays(cam, None if pix is None else torch.from_numpy(pix).cuda())
         assert np.array_equal(o.cpu().numpy(), ro) and np.array_equal(d.cpu().numpy(), rd)
+
+
+@pytest.mark.parametrize("layout", [_lib.LAYOUT_LEAF_ROWS, _lib.LAYOUT_VEC_SOA])
+@pytest.mark.parametrize("K,C,Cg", [(16, 8, 0), (14, 31, 31), (30, 31, 0), (14, 8, 0), (1, 1, 0), (30, 64, 64)])
+@pytest.mark.parametrize("n", [1, 2, 3, 5, 257, 70_001])
+def test_unpack_grad_rows_edges(n, K, C, Cg, layout):
+    """Rows to payload vectors is a rearrangement: every value, and zeros in the padding, for leaf counts around a
+    wavefront's share and rows of fewer and of more than 64 values."""
+    R = _lib.neuvv_grad_row_elems(K, C, Cg)
+    rows = torch.arange(n * R, dtype=torch.float32, device="cuda").remainder_(65_521.0).view(n, R) + 1.0
+    parts = [(0, 3 * K), (3 * K, C)] + ([(3 * K + C, Cg)] if Cg else [])
+    out = [torch.full((-(-r // 4) * 4 * n,), -1.0, device="cuda") for _, r in parts]
+    _lib.neuvv_unpack_grad_rows(K, C, Cg, layout, n, rows, *out)
+    for (start, r), got in zip(parts, out):
+        want = torch.zeros(n, -(-r // 4) * 4, device="cuda")
+        want[:, :r] = rows[:, start:start + r]
+        if layout == _lib.LAYOUT_VEC_SOA:
+            want = want.view(n, -1, 4).permute(1, 0, 2)
+        assert torch.equal(got, want.reshape(-1))
