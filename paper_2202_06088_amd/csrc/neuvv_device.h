@@ -325,10 +325,11 @@ __device__ __forceinline__ void ray_direction(const InstArgs& in, const float d[
     if (!(rs.len_local > 0.0f)) rs.dir[2] = 1.0f;
 }
 
-// Exact per-ray setup (float64 geometry); call for rays ray_may_hit accepts.
+// Exact geometry of a ray (float64): everything of RaySetup but its time; call
+// for rays ray_may_hit accepts.
 template <bool IDENT>
-__device__ __forceinline__ void ray_setup(const TreeArgs& tr, const InstArgs& in, const float o[3],
-                                          const float d[3], float t, RaySetup& rs) {
+__device__ __forceinline__ void ray_geometry(const TreeArgs& tr, const InstArgs& in, const float o[3],
+                                             const float d[3], RaySetup& rs) {
     float dmax;
     ray_direction<IDENT>(in, d, rs, dmax);
     if constexpr (IDENT) {
@@ -379,6 +380,13 @@ __device__ __forceinline__ void ray_setup(const TreeArgs& tr, const InstArgs& in
     rs.u_in = u_in;
     rs.u_out = u_out;
     rs.hit = hit;
+}
+
+// Geometry and time of a ray.
+template <bool IDENT>
+__device__ __forceinline__ void ray_setup(const TreeArgs& tr, const InstArgs& in, const float o[3],
+                                          const float d[3], float t, RaySetup& rs) {
+    ray_geometry<IDENT>(tr, in, o, d, rs);
     time_setup(tr, in, t, rs.i0, rs.i1, rs.f, &rs.tau);
 }
 

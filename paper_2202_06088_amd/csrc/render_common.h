@@ -129,6 +129,46 @@ __device__ __forceinline__ void absorb(float od, float& a, float& e) {
     e = small ? 1.0f - s : x;
 }
 
+// What one time for every ray makes common to all of them, in LDS: the radial
+// factors of the HH basis, the density-basis row and the local time. A ray's
+// setup is then its geometry and the products with its harmonics, without the
+// table reads (two dependent latencies in every refill of a wavefront), the
+// frame arithmetic and the sine and cosine; the values are those ray_basis
+// makes (same expressions).
+template <int C>
+struct CommonTime {
+    float g[10];
+    float b[C];
+    float tau;
+};
+// Call with the whole block; the caller synchronises.
+template <int C>
+__device__ __forceinline__ void stage_common_time(const TreeArgs& tr, const InstArgs& in, float t, CommonTime<C>& s) {
+    int i0, i1;
+    float f, tau;
+    time_setup(tr, in, t, i0, i1, f, &tau);
+    if (threadIdx.x == 0) {
+        float g[10];
+        hh_radial((1.0f - f) * tr.gamma[i0] + f * tr.gamma[i1], g);
+#pragma unroll
+        for (int k = 0; k < 10; ++k) s.g[k] = g[k];
+        s.tau = tau;
+    }
+    if (threadIdx.x < C)
+        s.b[threadIdx.x] = (1.0f - f) * tr.basis[(int64_t)i0 * C + threadIdx.x] +
+                           f * tr.basis[(int64_t)i1 * C + threadIdx.x];
+}
+// The first K HH values of a unit direction at the common time.
+template <int K, int C>
+__device__ __forceinline__ void common_basis(const CommonTime<C>& s, const float (&dir)[3], float (&h)[K]) {
+    float g[10], hall[30];
+#pragma unroll
+    for (int k = 0; k < 10; ++k) g[k] = s.g[k];
+    hh_assemble(g, dir[0], dir[1], dir[2], hall);
+#pragma unroll
+    for (int k = 0; k < K; ++k) h[k] = hall[k];
+}
+
 __device__ __forceinline__ int lane_rank(uint64_t mask) {
     return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
@@ -169,13 +209,13 @@ __device__ __forceinline__ bool next_chunk(const RayArgs& ra, ChunkCursor& cc) {
     while (cc.tried < kQueues) {
         const int x = (cc.home + cc.tried) & (kQueues - 1);
         const int64_t lo = n_chunks * x / kQueues, hi = n_chunks * (x + 1) / kQueues;
+        const int64_t cnt = ra.list ? (int64_t)ra.count[x * kQueueStride] : 0;   // (on its way with the ticket)
         unsigned long long t = 0;
         if ((int)(threadIdx.x & 63) == leader) t = atomicAdd(ra.queue + x * kQueueStride, 1ull);
         const uint32_t t_lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)t);
         const uint32_t t_hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(t >> 32));
         const int64_t t64 = (int64_t)(((uint64_t)t_hi << 32) | t_lo);
         if (ra.list) {
-            const int64_t cnt = (int64_t)ra.count[x * kQueueStride];
             if (t64 * 64 < cnt) {
                 cc.pos = 0;
                 cc.base = lo * 64 + t64 * 64;

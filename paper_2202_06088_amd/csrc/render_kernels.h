@@ -82,19 +82,21 @@ __device__ __forceinline__ void ray_basis(const TreeArgs& tr, const RaySetup& rs
 // its own slot (which the same lane overwrites later), and a ray whose trace
 // is incomplete stores into its last slot, or, if it has none, into the spare
 // half of the trace header.
-template <int K, int C, int DT, bool IDENT, bool EDIT, bool TRACE>
+template <int K, int C, int DT, bool IDENT, bool EDIT, bool TRACE, bool PER_T>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(min_waves<K, C>(3), 8))) void render_fwd_kernel(
     TreeArgs tr, InstArgs in, RayArgs ra, float t_stop, RenderOut out) {
     if (no_candidates(ra)) return;
     __shared__ float s_h[kBlock * K];
-    __shared__ float s_b[kBlock * C];
+    __shared__ float s_b[PER_T ? kBlock * C : 1];
     // traced: the output addresses, needed once per ray, wait in LDS rather than in scalar
     // registers, which the trace's allocation takes
     __shared__ RenderOut s_out;
     if constexpr (TRACE) {
         if (threadIdx.x == 0) s_out = out;
-        __syncthreads();
     }
+    __shared__ CommonTime<C> s_ct;
+    if constexpr (!PER_T) stage_common_time<C>(tr, in, ra.t_scalar, s_ct);
+    __syncthreads();
     const RenderOut& fo = TRACE ? s_out : out;
     ChunkCursor cc = chunk_cursor();
     bool more = true;   // wave-uniform: chunks may be left
@@ -103,9 +105,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(min_wave
     int64_t ray = -1;
     RaySetup rs;
     Walk w;
-    // the ray's basis h and density row b live in LDS (this lane's columns)
+    // the ray's basis h and density row b live in LDS (this lane's columns, or the common row b)
     float* const hl = s_h + threadIdx.x * K;
-    float* const bl = s_b + threadIdx.x * C;
+    const float* const bl = PER_T ? s_b + threadIdx.x * C : s_ct.b;
     float Tr = 1.0f, acc0 = 0.0f, acc1 = 0.0f, acc2 = 0.0f, wsum = 0.0f, dsum = 0.0f;
     int ns = 0, last = -1;
     int t_first = -1;                // trace: the ray's first entry; -2: broken
@@ -115,9 +117,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(min_wave
     int tcur = 0, tend = 0;      // trace: what is left of the wavefront's block (wave-uniform)
 
     for (;;) {
-        const uint64_t idle = __ballot(!alive);
-        const int n_idle = __popcll(idle);
-        if (more && (n_idle >= ra.refill_min || n_idle == kWave)) {
+        for (;;) {   // refill, until too few lanes are idle or no rays are left
+            const uint64_t idle = __ballot(!alive);
+            const int n_idle = __popcll(idle);
+            if (!more || n_idle < ra.refill_min) break;
             // Acquisition: idle lanes take the next slots; rays the plain-float
             // test rejects get their miss outputs at once and the lane takes
             // another slot, while at least refill_min lanes are idle. Then the
@@ -140,7 +143,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(min_wave
                         if (ray >= 0) {
                             o[0] = ra.o[3 * ray]; o[1] = ra.o[3 * ray + 1]; o[2] = ra.o[3 * ray + 2];
                             d[0] = ra.d[3 * ray]; d[1] = ra.d[3 * ray + 1]; d[2] = ra.d[3 * ray + 2];
-                            t = ra.t ? ra.t[ray] : ra.t_scalar;
+                            if constexpr (PER_T) t = ra.t[ray];
                             cand = ra.list != nullptr || ray_may_hit<IDENT>(tr, in, o, d);
                             if (!cand) write_miss(out, ray);
                         }
@@ -149,17 +152,21 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(min_wave
                 cc.pos += take;
             }
             if (cand) {
-                ray_setup<IDENT>(tr, in, o, d, t, rs);
+                ray_geometry<IDENT>(tr, in, o, d, rs);
                 Tr = 1.0f; acc0 = acc1 = acc2 = 0.0f; wsum = dsum = 0.0f; ns = 0;
                 if (rs.hit) {
-                    {
-                        float h[K], bv[C];
+                    float h[K];
+                    if constexpr (!PER_T) {
+                        common_basis<K, C>(s_ct, rs.dir, h);
+                    } else {
+                        float bv[C];
+                        time_setup(tr, in, t, rs.i0, rs.i1, rs.f, &rs.tau);
                         ray_basis<K, C>(tr, rs, h, bv);
 #pragma unroll
-                        for (int k = 0; k < K; ++k) hl[k] = h[k];
-#pragma unroll
-                        for (int c = 0; c < C; ++c) bl[c] = bv[c];
+                        for (int c = 0; c < C; ++c) s_b[threadIdx.x * C + c] = bv[c];
                     }
+#pragma unroll
+                    for (int k = 0; k < K; ++k) hl[k] = h[k];
                     walk_begin(tr, rs, w);
                     alive = true;
                     t_first = -1;
@@ -168,100 +175,102 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(min_wave
                     write_miss(out, ray);
                 }
             }
-            continue;
         }
-        if (n_idle == kWave) break;
-        bool finish = false, stopped = false;
-        int leaf = -1;
-        float delta = 0.0f, umid = 0.0f;
-        if (alive) {
-            leaf = walk_next<kWalkBudget>(tr, rs, w, delta, umid);
-            finish = leaf == -1;
-        }
-        int cur = -1;
-        if constexpr (TRACE) {
-            const uint64_t hm = __ballot(leaf >= 0);
-            const int n_s = __popcll(hm);
-            const int at = n_s > 0 ? take_items(out.trace.counter, out.trace.cap, n_s, tcur, tend) : -1;
-            if (leaf >= 0) {
-                if (at >= 0 && t_first != -2) {
-                    cur = (int)(at + lane_rank(hm));
-                    if (t_first == -1) t_first = cur;
-                } else {
-                    t_first = -2;   // incomplete: the adjoint walks this ray
-                }
+        if (!__ballot(alive)) break;
+        const int limit = more ? ra.refill_min : kWave;   // idle lanes that end the inner loop
+        do {
+            bool finish = false, stopped = false;
+            int leaf = -1;
+            float delta = 0.0f, umid = 0.0f;
+            if (alive) {
+                leaf = walk_next<kWalkBudget>(tr, rs, w, delta, umid);
+                finish = leaf == -1;
             }
-        }
-        if (leaf >= 0) {
-            {
-                float wv[3 * K], sv[C];
-                load_leaf<DT, 3 * K>(tr.hh, tr.n_leaves, leaf, tr.layout, wv);
-                load_leaf<DT, C>(tr.wsig, tr.n_leaves, leaf, tr.layout, sv);
-                if constexpr (TRACE) {
-                    // the previous sample's entry, linked to this one
-                    const int tgt = pslot >= 0 ? pslot : cur;
-                    int4* dst = tgt >= 0 ? out.trace.smp + 2 * (int64_t)tgt
-                                         : reinterpret_cast<int4*>(reinterpret_cast<char*>(out.trace.counter) + 1024) +
-                                               2 * (threadIdx.x & 31);
-                    dst[0] = make_int4(pleaf, __float_as_int(pdelta), __float_as_int(px), __float_as_int(pc0));
-                    dst[1] = make_int4(__float_as_int(pc1), __float_as_int(pc2), cur, 0);
-                }
-                float x = 0.0f;
-#pragma unroll
-                for (int c = 0; c < C; ++c) x = fmaf(sv[c], bl[c], x);
-                float z0 = 0.0f, z1 = 0.0f, z2 = 0.0f;
-#pragma unroll
-                for (int k = 0; k < K; ++k) {
-                    const float hk = hl[k];
-                    z0 = fmaf(wv[k], hk, z0);
-                    z1 = fmaf(wv[K + k], hk, z1);
-                    z2 = fmaf(wv[2 * K + k], hk, z2);
-                }
-                float sig = density_f(x, tr.relu);
-                float c0 = sigmoid_f(z0), c1 = sigmoid_f(z1), c2 = sigmoid_f(z2);
-                if constexpr (EDIT) {
-                    const float4 e0 = tr.edit[2 * (int64_t)leaf], e1 = tr.edit[2 * (int64_t)leaf + 1];
-                    if (rs.tau >= e1.x) {
-                        c0 = e0.x; c1 = e0.y; c2 = e0.z;
-                        if (e0.w >= 0.0f) sig = e0.w;
+            int cur = -1;
+            if constexpr (TRACE) {
+                const uint64_t hm = __ballot(leaf >= 0);
+                const int n_s = __popcll(hm);
+                const int at = n_s > 0 ? take_items(out.trace.counter, out.trace.cap, n_s, tcur, tend) : -1;
+                if (leaf >= 0) {
+                    if (at >= 0 && t_first != -2) {
+                        cur = (int)(at + lane_rank(hm));
+                        if (t_first == -1) t_first = cur;
+                    } else {
+                        t_first = -2;   // incomplete: the adjoint walks this ray
                     }
                 }
-                const float od = sig * delta;
-                float a, e_od;
-                absorb(od, a, e_od);
-                const float wt = Tr * a;
-                acc0 = fmaf(wt, c0, acc0);
-                acc1 = fmaf(wt, c1, acc1);
-                acc2 = fmaf(wt, c2, acc2);
-                wsum += wt;
-                dsum = fmaf(wt, umid * rs.len_world, dsum);
-                Tr *= e_od;
-                ++ns;
-                last = leaf;
-                finish = t_stop > 0.0f && Tr < t_stop;
-                stopped = finish;
+            }
+            if (leaf >= 0) {
+                {
+                    float wv[3 * K], sv[C];
+                    load_leaf<DT, 3 * K>(tr.hh, tr.n_leaves, leaf, tr.layout, wv);
+                    load_leaf<DT, C>(tr.wsig, tr.n_leaves, leaf, tr.layout, sv);
+                    if constexpr (TRACE) {
+                        // the previous sample's entry, linked to this one
+                        const int tgt = pslot >= 0 ? pslot : cur;
+                        int4* dst = tgt >= 0 ? out.trace.smp + 2 * (int64_t)tgt
+                                             : reinterpret_cast<int4*>(reinterpret_cast<char*>(out.trace.counter) + 1024) +
+                                                   2 * (threadIdx.x & 31);
+                        dst[0] = make_int4(pleaf, __float_as_int(pdelta), __float_as_int(px), __float_as_int(pc0));
+                        dst[1] = make_int4(__float_as_int(pc1), __float_as_int(pc2), cur, 0);
+                    }
+                    float x = 0.0f;
+#pragma unroll
+                    for (int c = 0; c < C; ++c) x = fmaf(sv[c], bl[c], x);
+                    float z0 = 0.0f, z1 = 0.0f, z2 = 0.0f;
+#pragma unroll
+                    for (int k = 0; k < K; ++k) {
+                        const float hk = hl[k];
+                        z0 = fmaf(wv[k], hk, z0);
+                        z1 = fmaf(wv[K + k], hk, z1);
+                        z2 = fmaf(wv[2 * K + k], hk, z2);
+                    }
+                    float sig = density_f(x, tr.relu);
+                    float c0 = sigmoid_f(z0), c1 = sigmoid_f(z1), c2 = sigmoid_f(z2);
+                    if constexpr (EDIT) {
+                        const float4 e0 = tr.edit[2 * (int64_t)leaf], e1 = tr.edit[2 * (int64_t)leaf + 1];
+                        if ((PER_T ? rs.tau : s_ct.tau) >= e1.x) {
+                            c0 = e0.x; c1 = e0.y; c2 = e0.z;
+                            if (e0.w >= 0.0f) sig = e0.w;
+                        }
+                    }
+                    const float od = sig * delta;
+                    float a, e_od;
+                    absorb(od, a, e_od);
+                    const float wt = Tr * a;
+                    acc0 = fmaf(wt, c0, acc0);
+                    acc1 = fmaf(wt, c1, acc1);
+                    acc2 = fmaf(wt, c2, acc2);
+                    wsum += wt;
+                    dsum = fmaf(wt, umid * rs.len_world, dsum);
+                    Tr *= e_od;
+                    ++ns;
+                    last = leaf;
+                    finish = t_stop > 0.0f && Tr < t_stop;
+                    stopped = finish;
+                    if constexpr (TRACE) {
+                        if (cur >= 0) pslot = cur;
+                        pleaf = leaf; pdelta = delta; px = x; pc0 = c0; pc1 = c1; pc2 = c2;
+                    }
+                }
+            }
+            if (alive && finish) {
+                if (fo.rgb) store3(fo.rgb + 3 * ray, acc0, acc1, acc2);
+                if (fo.alpha) fo.alpha[ray] = 1.0f - Tr;
+                if (fo.depth) fo.depth[ray] = wsum > 0.0f ? dsum / wsum : INFINITY;
+                if (fo.nsamp) fo.nsamp[ray] = ns;
+                if (fo.last_leaf) fo.last_leaf[ray] = stopped ? last : -1;
                 if constexpr (TRACE) {
-                    if (cur >= 0) pslot = cur;
-                    pleaf = leaf; pdelta = delta; px = x; pc0 = c0; pc1 = c1; pc2 = c2;
+                    if (t_first >= 0) {
+                        out.trace.smp[2 * (int64_t)pslot] =
+                            make_int4(pleaf, __float_as_int(pdelta), __float_as_int(px), __float_as_int(pc0));
+                        out.trace.smp[2 * (int64_t)pslot + 1] = make_int4(__float_as_int(pc1), __float_as_int(pc2), -1, 0);
+                    }
+                    fo.trace.head[ray] = t_first >= 0 ? t_first : -1;
                 }
+                alive = false;
             }
-        }
-        if (alive && finish) {
-            if (fo.rgb) store3(fo.rgb + 3 * ray, acc0, acc1, acc2);
-            if (fo.alpha) fo.alpha[ray] = 1.0f - Tr;
-            if (fo.depth) fo.depth[ray] = wsum > 0.0f ? dsum / wsum : INFINITY;
-            if (fo.nsamp) fo.nsamp[ray] = ns;
-            if (fo.last_leaf) fo.last_leaf[ray] = stopped ? last : -1;
-            if constexpr (TRACE) {
-                if (t_first >= 0) {
-                    out.trace.smp[2 * (int64_t)pslot] =
-                        make_int4(pleaf, __float_as_int(pdelta), __float_as_int(px), __float_as_int(pc0));
-                    out.trace.smp[2 * (int64_t)pslot + 1] = make_int4(__float_as_int(pc1), __float_as_int(pc2), -1, 0);
-                }
-                fo.trace.head[ray] = t_first >= 0 ? t_first : -1;
-            }
-            alive = false;
-        }
+        } while (__popcll(__ballot(!alive)) < limit);
     }
 }
 
@@ -290,20 +299,22 @@ __host__ __device__ constexpr int grad_row() { return ((3 * K + C + 63) / 64) * 
 
 
 // The walking adjoint: each ray walks the tree and evaluates its leaves again.
-template <int K, int C, int DT, bool IDENT>
+template <int K, int C, int DT, bool IDENT, bool PER_T>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(min_waves<K, C>(3), 8))) void render_bwd_kernel(
     TreeArgs tr, InstArgs in, RayArgs ra, BackwardIO io, RecordArgs rec) {
     if (no_candidates(ra)) return;
     constexpr int ROW = grad_row<K, C>();
     __shared__ float s_h[kBlock * K];
-    __shared__ float s_b[kBlock * C];
+    __shared__ float s_b[PER_T ? kBlock * C : 1];
     __shared__ float s_gb[C];
+    __shared__ CommonTime<C> s_ct;
+    constexpr bool per_ray_t = PER_T;
+    if constexpr (!PER_T) stage_common_time<C>(tr, in, ra.t_scalar, s_ct);
     if (threadIdx.x < C) s_gb[threadIdx.x] = 0.0f;
     __syncthreads();
     ChunkCursor cc = chunk_cursor();
     bool more = true;   // wave-uniform: chunks may be left
     const int64_t N = tr.n_leaves;
-    const bool per_ray_t = ra.t != nullptr;
     const int lane = threadIdx.x & 63;
     const int wbase = threadIdx.x - lane;
     // one time for every ray and records: the basis gradient of recorded samples
@@ -329,9 +340,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(min_wave
     int wrec = 0, wend = 0;
 
     for (;;) {
-        const uint64_t idle = __ballot(!alive);
-        const int n_idle = __popcll(idle);
-        if (more && (n_idle >= ra.refill_min || n_idle == kWave)) {
+        for (;;) {   // refill, until too few lanes are idle or no rays are left
+            const uint64_t idle = __ballot(!alive);
+            const int n_idle = __popcll(idle);
+            if (!more || n_idle < ra.refill_min) break;
             // Acquisition: idle lanes take the next slots while at least refill_min
             // lanes are idle; rays that composited no sample carry no gradient and
             // are passed over. The setup then runs once for all taken rays together.
@@ -357,20 +369,23 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(min_wave
             if (cand) {
                 const float o[3] = {ra.o[3 * ray], ra.o[3 * ray + 1], ra.o[3 * ray + 2]};
                 const float d[3] = {ra.d[3 * ray], ra.d[3 * ray + 1], ra.d[3 * ray + 2]};
-                const float t = per_ray_t ? ra.t[ray] : ra.t_scalar;
-                ray_setup<IDENT>(tr, in, o, d, t, rs);
+                ray_geometry<IDENT>(tr, in, o, d, rs);
                 dw0 = d[0];
                 dw1 = d[1];
                 dw2 = d[2];
                 if (rs.hit) {
-                    {
-                        float h[K], bv[C];
+                    float h[K];
+                    if constexpr (!PER_T) {
+                        common_basis<K, C>(s_ct, rs.dir, h);
+                    } else {
+                        float bv[C];
+                        time_setup(tr, in, ra.t[ray], rs.i0, rs.i1, rs.f);
                         ray_basis<K, C>(tr, rs, h, bv);
-#pragma unroll
-                        for (int k = 0; k < K; ++k) s_h[threadIdx.x * K + k] = h[k];
 #pragma unroll
                         for (int c = 0; c < C; ++c) s_b[threadIdx.x * C + c] = bv[c];
                     }
+#pragma unroll
+                    for (int k = 0; k < K; ++k) s_h[threadIdx.x * K + k] = h[k];
                     walk_begin(tr, rs, w);
                     ns_fwd = io.nsamp[ray];
                     ns = 0;
@@ -387,129 +402,131 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(min_wave
                     alive = true;
                 }
             }
-            continue;
         }
-        if (n_idle == kWave) break;
-        bool has = false;
-        int leaf = -1, my_rec = -1;
-        float gz0 = 0.0f, gz1 = 0.0f, gz2 = 0.0f, gx = 0.0f;
-        if (alive) {
-            float delta = 0.0f;
-            bool finish;
-            float x = 0.0f, c0 = 0.0f, c1 = 0.0f, c2 = 0.0f;
-            float sv[C];
-            float umid;
-            leaf = walk_next<kWalkBudget>(tr, rs, w, delta, umid);
-            finish = leaf == -1;
-            if (leaf >= 0) {
-                float wv[3 * K];
-                load_leaf<DT, 3 * K>(tr.hh, N, leaf, tr.layout, wv);
-                load_leaf<DT, C>(tr.wsig, N, leaf, tr.layout, sv);
-                const float* hl = s_h + threadIdx.x * K;
-                const float* bl = s_b + threadIdx.x * C;
+        if (!__ballot(alive)) break;
+        const int limit = more ? ra.refill_min : kWave;   // idle lanes that end the inner loop
+        do {
+            bool has = false;
+            int leaf = -1, my_rec = -1;
+            float gz0 = 0.0f, gz1 = 0.0f, gz2 = 0.0f, gx = 0.0f;
+            if (alive) {
+                float delta = 0.0f;
+                bool finish;
+                float x = 0.0f, c0 = 0.0f, c1 = 0.0f, c2 = 0.0f;
+                float sv[C];
+                float umid;
+                leaf = walk_next<kWalkBudget>(tr, rs, w, delta, umid);
+                finish = leaf == -1;
+                if (leaf >= 0) {
+                    float wv[3 * K];
+                    load_leaf<DT, 3 * K>(tr.hh, N, leaf, tr.layout, wv);
+                    load_leaf<DT, C>(tr.wsig, N, leaf, tr.layout, sv);
+                    const float* hl = s_h + threadIdx.x * K;
+                    const float* bl = per_ray_t ? s_b + threadIdx.x * C : s_ct.b;
 #pragma unroll
-                for (int c = 0; c < C; ++c) x = fmaf(sv[c], bl[c], x);
-                float z0 = 0.0f, z1 = 0.0f, z2 = 0.0f;
+                    for (int c = 0; c < C; ++c) x = fmaf(sv[c], bl[c], x);
+                    float z0 = 0.0f, z1 = 0.0f, z2 = 0.0f;
 #pragma unroll
-                for (int k = 0; k < K; ++k) {
-                    const float hk = hl[k];
-                    z0 = fmaf(wv[k], hk, z0);
-                    z1 = fmaf(wv[K + k], hk, z1);
-                    z2 = fmaf(wv[2 * K + k], hk, z2);
+                    for (int k = 0; k < K; ++k) {
+                        const float hk = hl[k];
+                        z0 = fmaf(wv[k], hk, z0);
+                        z1 = fmaf(wv[K + k], hk, z1);
+                        z2 = fmaf(wv[2 * K + k], hk, z2);
+                    }
+                    c0 = sigmoid_f(z0);
+                    c1 = sigmoid_f(z1);
+                    c2 = sigmoid_f(z2);
                 }
-                c0 = sigmoid_f(z0);
-                c1 = sigmoid_f(z1);
-                c2 = sigmoid_f(z2);
-            }
-            if (leaf >= 0) {
-                const float sig = density_f(x, tr.relu);
-                const float od = sig * delta;
-                float a, e;
-                absorb(od, a, e);
-                const float wt = Tr * a;
-                const float Tn = Tr * e;
-                p0 = fmaf(wt, c0, p0);
-                p1 = fmaf(wt, c1, p1);
-                p2 = fmaf(wt, c2, p2);
-                const float gdotc = g0 * c0 + g1 * c1 + g2 * c2;
-                const float gsuf = g0 * (F0 - p0) + g1 * (F1 - p1) + g2 * (F2 - p2);
-                // dL/dsigma = delta (T_{k+1} <g, c_k> - <g, rgb - rgb_<=k>) + g_a delta T_final
-                const float gsig = delta * (Tn * gdotc - gsuf) + ga * delta * Tfin;
-                gx = gsig * density_dx(x, tr.relu);
-                gz0 = g0 * wt * c0 * (1.0f - c0);
-                gz1 = g1 * wt * c1 * (1.0f - c1);
-                gz2 = g2 * wt * c2 * (1.0f - c2);
-                if (basis_here) {
+                if (leaf >= 0) {
+                    const float sig = density_f(x, tr.relu);
+                    const float od = sig * delta;
+                    float a, e;
+                    absorb(od, a, e);
+                    const float wt = Tr * a;
+                    const float Tn = Tr * e;
+                    p0 = fmaf(wt, c0, p0);
+                    p1 = fmaf(wt, c1, p1);
+                    p2 = fmaf(wt, c2, p2);
+                    const float gdotc = g0 * c0 + g1 * c1 + g2 * c2;
+                    const float gsuf = g0 * (F0 - p0) + g1 * (F1 - p1) + g2 * (F2 - p2);
+                    // dL/dsigma = delta (T_{k+1} <g, c_k> - <g, rgb - rgb_<=k>) + g_a delta T_final
+                    const float gsig = delta * (Tn * gdotc - gsuf) + ga * delta * Tfin;
+                    gx = gsig * density_dx(x, tr.relu);
+                    gz0 = g0 * wt * c0 * (1.0f - c0);
+                    gz1 = g1 * wt * c1 * (1.0f - c1);
+                    gz2 = g2 * wt * c2 * (1.0f - c2);
+                    if (basis_here) {
 #pragma unroll
-                    for (int c = 0; c < C; ++c) gb[c] = fmaf(gx, sv[c], gb[c]);
+                        for (int c = 0; c < C; ++c) gb[c] = fmaf(gx, sv[c], gb[c]);
+                    }
+                    has = true;
+                    Tr = Tn;
+                    ++ns;
+                    finish = ns >= ns_fwd;
                 }
-                has = true;
-                Tr = Tn;
-                ++ns;
-                finish = ns >= ns_fwd;
-            }
-            if (finish) {
-                if (io.grad_basis && per_ray_t) {
+                if (finish) {
+                    if (io.grad_basis && per_ray_t) {
 #pragma unroll
-                    for (int c = 0; c < C; ++c) {
-                        unsafeAtomicAdd(io.grad_basis + (int64_t)rs.i0 * C + c, (1.0f - rs.f) * gb[c]);
-                        if (rs.f != 0.0f) unsafeAtomicAdd(io.grad_basis + (int64_t)rs.i1 * C + c, rs.f * gb[c]);
+                        for (int c = 0; c < C; ++c) {
+                            unsafeAtomicAdd(io.grad_basis + (int64_t)rs.i0 * C + c, (1.0f - rs.f) * gb[c]);
+                            if (rs.f != 0.0f) unsafeAtomicAdd(io.grad_basis + (int64_t)rs.i1 * C + c, rs.f * gb[c]);
+                        }
+                    }
+                    alive = false;
+                }
+            }
+            if (rec.head) {
+                // this iteration's samples take consecutive records in lane order, so
+                // the record stores of the wavefront are contiguous
+                const uint64_t hm = __ballot(has);
+                const int n_has = __popcll(hm);
+                const int at = n_has > 0 ? take_items(rec.counter, rec.cap, n_has, wrec, wend) : -1;
+                if (at >= 0) {
+                    const RecordRun run = record_run(hm, has, leaf);
+                    if (has) {
+                        my_rec = (int)(at + lane_rank(hm));
+                        rec.rec[2 * (int64_t)my_rec] =
+                            make_int4(__float_as_int(gz0), __float_as_int(gz1), __float_as_int(gz2), __float_as_int(gx));
+                        const int nxt = run.count > 0 ? atomicExch(rec.head + leaf, my_rec + run.count - 1) : my_rec - 1;
+                        // one time for every ray: the record carries the ray's direction
+                        // (all the reduction needs of the ray), else the ray's index
+                        rec.rec[2 * (int64_t)my_rec + 1] =
+                            per_ray_t ? make_int4(nxt, (int)ray, 0, 0)
+                                      : make_int4(nxt, __float_as_int(dw0), __float_as_int(dw1), __float_as_int(dw2));
                     }
                 }
-                alive = false;
             }
-        }
-        if (rec.head) {
-            // this iteration's samples take consecutive records in lane order, so
-            // the record stores of the wavefront are contiguous
-            const uint64_t hm = __ballot(has);
-            const int n_has = __popcll(hm);
-            const int at = n_has > 0 ? take_items(rec.counter, rec.cap, n_has, wrec, wend) : -1;
-            if (at >= 0) {
-                const RecordRun run = record_run(hm, has, leaf);
-                if (has) {
-                    my_rec = (int)(at + lane_rank(hm));
-                    rec.rec[2 * (int64_t)my_rec] =
-                        make_int4(__float_as_int(gz0), __float_as_int(gz1), __float_as_int(gz2), __float_as_int(gx));
-                    const int nxt = run.count > 0 ? atomicExch(rec.head + leaf, my_rec + run.count - 1) : my_rec - 1;
-                    // one time for every ray: the record carries the ray's direction
-                    // (all the reduction needs of the ray), else the ray's index
-                    rec.rec[2 * (int64_t)my_rec + 1] =
-                        per_ray_t ? make_int4(nxt, (int)ray, 0, 0)
-                                  : make_int4(nxt, __float_as_int(dw0), __float_as_int(dw1), __float_as_int(dw2));
+            if (basis_late && io.grad_basis && has && my_rec < 0) {
+                // a sample without a record: its basis gradient stays here
+                float sw[C];
+                load_leaf<DT, C>(tr.wsig, N, leaf, tr.layout, sw);
+#pragma unroll
+                for (int c = 0; c < C; ++c) gb[c] = fmaf(gx, sw[c], gb[c]);
+            }
+            // samples without a record: every lane of the wavefront adds one
+            // component of each produced row
+            uint64_t m = __ballot(has && my_rec < 0);
+            __builtin_amdgcn_wave_barrier();
+            while (m) {
+                const int src = __builtin_ctzll(m);
+                m &= m - 1;
+                const int L = __builtin_amdgcn_readlane(leaf, src);
+                const float a0 = readlane_f(gz0, src), a1 = readlane_f(gz1, src), a2 = readlane_f(gz2, src);
+                const float ax = readlane_f(gx, src);
+                float* row = io.grad_leaf + (int64_t)L * ROW;
+#pragma unroll
+                for (int c0 = 0; c0 < 3 * K + C; c0 += kWave) {
+                    const int c = c0 + lane;
+                    if (c < 3 * K) {
+                        const int ch = c / K;
+                        const float gzc = ch == 0 ? a0 : (ch == 1 ? a1 : a2);
+                        unsafeAtomicAdd(row + c, gzc * s_h[(wbase + src) * K + (c - ch * K)]);
+                    } else if (c < 3 * K + C) {
+                        unsafeAtomicAdd(row + c, ax * (per_ray_t ? s_b[(wbase + src) * C + (c - 3 * K)] : s_ct.b[c - 3 * K]));
+                    }
                 }
             }
-        }
-        if (basis_late && io.grad_basis && has && my_rec < 0) {
-            // a sample without a record: its basis gradient stays here
-            float sw[C];
-            load_leaf<DT, C>(tr.wsig, N, leaf, tr.layout, sw);
-#pragma unroll
-            for (int c = 0; c < C; ++c) gb[c] = fmaf(gx, sw[c], gb[c]);
-        }
-        // samples without a record: every lane of the wavefront adds one
-        // component of each produced row
-        uint64_t m = __ballot(has && my_rec < 0);
-        __builtin_amdgcn_wave_barrier();
-        while (m) {
-            const int src = __builtin_ctzll(m);
-            m &= m - 1;
-            const int L = __builtin_amdgcn_readlane(leaf, src);
-            const float a0 = readlane_f(gz0, src), a1 = readlane_f(gz1, src), a2 = readlane_f(gz2, src);
-            const float ax = readlane_f(gx, src);
-            float* row = io.grad_leaf + (int64_t)L * ROW;
-#pragma unroll
-            for (int c0 = 0; c0 < 3 * K + C; c0 += kWave) {
-                const int c = c0 + lane;
-                if (c < 3 * K) {
-                    const int ch = c / K;
-                    const float gzc = ch == 0 ? a0 : (ch == 1 ? a1 : a2);
-                    unsafeAtomicAdd(row + c, gzc * s_h[(wbase + src) * K + (c - ch * K)]);
-                } else if (c < 3 * K + C) {
-                    unsafeAtomicAdd(row + c, ax * s_b[(wbase + src) * C + (c - 3 * K)]);
-                }
-            }
-        }
+        } while (__popcll(__ballot(!alive)) < limit);
     }
     // one shared time for every ray: reduce the basis gradient over the block
     if (io.grad_basis && !per_ray_t) {
@@ -570,9 +587,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(min_wave
     int wrec = 0, wend = 0;        // what is left of the wavefront's block of records (wave-uniform)
 
     for (;;) {
-        const uint64_t idle = __ballot(!alive);
-        const int n_idle = __popcll(idle);
-        if (more && (n_idle >= ra.refill_min || n_idle == kWave)) {
+        for (;;) {   // refill, until too few lanes are idle or no rays are left
+            const uint64_t idle = __ballot(!alive);
+            const int n_idle = __popcll(idle);
+            if (!more || n_idle < ra.refill_min) break;
             // idle lanes take the next rays (the list holds only rays with a trace)
             if (cc.pos == kWave && !next_chunk(ra, cc)) {
                 more = false;
@@ -609,121 +627,123 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(min_wave
                 }
             }
             cc.pos += take;
-            continue;
         }
-        if (n_idle == kWave) break;
-        bool has = false;
-        int leaf = -1, my_rec = -1;
-        float gz0 = 0.0f, gz1 = 0.0f, gz2 = 0.0f, gx = 0.0f;
-        if (alive) {
-            const int4 A = nA, B = nB;
-            const int tnext = B.z;
-            if (tnext >= 0) {
-                nA = io.trace.smp[2 * (int64_t)tnext];
-                nB = io.trace.smp[2 * (int64_t)tnext + 1];
-            }
-            leaf = A.x;
-            const float delta = __int_as_float(A.y), x = __int_as_float(A.z);
-            const float c0 = __int_as_float(A.w), c1 = __int_as_float(B.x), c2 = __int_as_float(B.y);
-            const float sig = density_f(x, tr.relu);
-            const float od = sig * delta;
-            float a, e;
-            absorb(od, a, e);
-            const float wt = Tr * a;
-            const float Tn = Tr * e;
-            p0 = fmaf(wt, c0, p0);
-            p1 = fmaf(wt, c1, p1);
-            p2 = fmaf(wt, c2, p2);
-            const float gdotc = g0 * c0 + g1 * c1 + g2 * c2;
-            const float gsuf = g0 * (F0 - p0) + g1 * (F1 - p1) + g2 * (F2 - p2);
-            // dL/dsigma = delta (T_{k+1} <g, c_k> - <g, rgb - rgb_<=k>) + g_a delta T_final
-            const float gsig = delta * (Tn * gdotc - gsuf) + ga * delta * Tfin;
-            gx = gsig * density_dx(x, tr.relu);
-            gz0 = g0 * wt * c0 * (1.0f - c0);
-            gz1 = g1 * wt * c1 * (1.0f - c1);
-            gz2 = g2 * wt * c2 * (1.0f - c2);
-            if constexpr (PER_T) {
-                if (io.grad_basis) {
-                    float sv[C];
-                    load_leaf<DT, C>(tr.wsig, tr.n_leaves, leaf, tr.layout, sv);
-#pragma unroll
-                    for (int c = 0; c < C; ++c) gb[c] = fmaf(gx, sv[c], gb[c]);
+        if (!__ballot(alive)) break;
+        const int limit = more ? ra.refill_min : kWave;   // idle lanes that end the inner loop
+        do {
+            bool has = false;
+            int leaf = -1, my_rec = -1;
+            float gz0 = 0.0f, gz1 = 0.0f, gz2 = 0.0f, gx = 0.0f;
+            if (alive) {
+                const int4 A = nA, B = nB;
+                const int tnext = B.z;
+                if (tnext >= 0) {
+                    nA = io.trace.smp[2 * (int64_t)tnext];
+                    nB = io.trace.smp[2 * (int64_t)tnext + 1];
                 }
-            }
-            has = true;
-            Tr = Tn;
-            if (--left == 0 || tnext < 0) {
+                leaf = A.x;
+                const float delta = __int_as_float(A.y), x = __int_as_float(A.z);
+                const float c0 = __int_as_float(A.w), c1 = __int_as_float(B.x), c2 = __int_as_float(B.y);
+                const float sig = density_f(x, tr.relu);
+                const float od = sig * delta;
+                float a, e;
+                absorb(od, a, e);
+                const float wt = Tr * a;
+                const float Tn = Tr * e;
+                p0 = fmaf(wt, c0, p0);
+                p1 = fmaf(wt, c1, p1);
+                p2 = fmaf(wt, c2, p2);
+                const float gdotc = g0 * c0 + g1 * c1 + g2 * c2;
+                const float gsuf = g0 * (F0 - p0) + g1 * (F1 - p1) + g2 * (F2 - p2);
+                // dL/dsigma = delta (T_{k+1} <g, c_k> - <g, rgb - rgb_<=k>) + g_a delta T_final
+                const float gsig = delta * (Tn * gdotc - gsuf) + ga * delta * Tfin;
+                gx = gsig * density_dx(x, tr.relu);
+                gz0 = g0 * wt * c0 * (1.0f - c0);
+                gz1 = g1 * wt * c1 * (1.0f - c1);
+                gz2 = g2 * wt * c2 * (1.0f - c2);
                 if constexpr (PER_T) {
                     if (io.grad_basis) {
-                        const int i1 = i0 + 1 < tr.T ? i0 + 1 : tr.T - 1;
+                        float sv[C];
+                        load_leaf<DT, C>(tr.wsig, tr.n_leaves, leaf, tr.layout, sv);
 #pragma unroll
-                        for (int c = 0; c < C; ++c) {
-                            unsafeAtomicAdd(io.grad_basis + (int64_t)i0 * C + c, (1.0f - f) * gb[c]);
-                            if (f != 0.0f) unsafeAtomicAdd(io.grad_basis + (int64_t)i1 * C + c, f * gb[c]);
-                        }
+                        for (int c = 0; c < C; ++c) gb[c] = fmaf(gx, sv[c], gb[c]);
                     }
                 }
-                alive = false;
-            }
-        }
-        if (rec.head) {
-            // this iteration's samples take consecutive records in lane order, so
-            // the record stores of the wavefront are contiguous
-            const uint64_t hm = __ballot(has);
-            const int at = take_items(rec.counter, rec.cap, __popcll(hm), wrec, wend);
-            if (at >= 0) {
-                const RecordRun run = record_run(hm, has, leaf);
-                if (has) {
-                    my_rec = at + lane_rank(hm);
-                    rec.rec[2 * (int64_t)my_rec] =
-                        make_int4(__float_as_int(gz0), __float_as_int(gz1), __float_as_int(gz2), __float_as_int(gx));
-                    const int nxt = run.count > 0 ? atomicExch(rec.head + leaf, my_rec + run.count - 1) : my_rec - 1;
-                    // one time for every ray: the record carries the ray's direction
-                    // (all the reduction needs of the ray), else the ray's index
-                    rec.rec[2 * (int64_t)my_rec + 1] =
-                        PER_T ? make_int4(nxt, ray, 0, 0)
-                              : make_int4(nxt, __float_as_int(dw.x), __float_as_int(dw.y), __float_as_int(dw.z));
+                has = true;
+                Tr = Tn;
+                if (--left == 0 || tnext < 0) {
+                    if constexpr (PER_T) {
+                        if (io.grad_basis) {
+                            const int i1 = i0 + 1 < tr.T ? i0 + 1 : tr.T - 1;
+#pragma unroll
+                            for (int c = 0; c < C; ++c) {
+                                unsafeAtomicAdd(io.grad_basis + (int64_t)i0 * C + c, (1.0f - f) * gb[c]);
+                                if (f != 0.0f) unsafeAtomicAdd(io.grad_basis + (int64_t)i1 * C + c, f * gb[c]);
+                            }
+                        }
+                    }
+                    alive = false;
                 }
             }
-        }
-        // samples without a record: every lane of the wavefront adds one
-        // component of each sample's row, whose basis its own lane makes first
-        uint64_t m = __ballot(has && my_rec < 0);
-        while (__builtin_expect_with_probability(m != 0, 0, 0.99999)) {
-            const int src = __builtin_ctzll(m);
-            m &= m - 1;
-            __builtin_amdgcn_wave_barrier();
-            if (lane == src) {
-                RaySetup rs;
-                float dmax, h[K], bv[C];
-                const float d[3] = {dw.x, dw.y, dw.z};
-                ray_direction<IDENT>(in, d, rs, dmax);
-                time_setup(tr, in, PER_T ? ra.t[ray] : ra.t_scalar, rs.i0, rs.i1, rs.f);
-                ray_basis<K, C>(tr, rs, h, bv);
-#pragma unroll
-                for (int k = 0; k < K; ++k) srow[k] = h[k];
-#pragma unroll
-                for (int c = 0; c < C; ++c) srow[K + c] = bv[c];
-            }
-            __builtin_amdgcn_wave_barrier();
-            const int L = __builtin_amdgcn_readlane(leaf, src);
-            const float a0 = readlane_f(gz0, src), a1 = readlane_f(gz1, src), a2 = readlane_f(gz2, src);
-            const float ax = readlane_f(gx, src);
-            float* row = io.grad_leaf + (int64_t)L * ROW;
-#pragma unroll
-            for (int c0 = 0; c0 < 3 * K + C; c0 += kWave) {
-                const int c = c0 + lane;
-                if (c < 3 * K) {
-                    const int ch = c / K;
-                    const float gzc = ch == 0 ? a0 : (ch == 1 ? a1 : a2);
-                    unsafeAtomicAdd(row + c, gzc * srow[c - ch * K]);
-                } else if (c < 3 * K + C) {
-                    unsafeAtomicAdd(row + c, ax * srow[K + c - 3 * K]);
+            if (rec.head) {
+                // this iteration's samples take consecutive records in lane order, so
+                // the record stores of the wavefront are contiguous
+                const uint64_t hm = __ballot(has);
+                const int at = take_items(rec.counter, rec.cap, __popcll(hm), wrec, wend);
+                if (at >= 0) {
+                    const RecordRun run = record_run(hm, has, leaf);
+                    if (has) {
+                        my_rec = at + lane_rank(hm);
+                        rec.rec[2 * (int64_t)my_rec] =
+                            make_int4(__float_as_int(gz0), __float_as_int(gz1), __float_as_int(gz2), __float_as_int(gx));
+                        const int nxt = run.count > 0 ? atomicExch(rec.head + leaf, my_rec + run.count - 1) : my_rec - 1;
+                        // one time for every ray: the record carries the ray's direction
+                        // (all the reduction needs of the ray), else the ray's index
+                        rec.rec[2 * (int64_t)my_rec + 1] =
+                            PER_T ? make_int4(nxt, ray, 0, 0)
+                                  : make_int4(nxt, __float_as_int(dw.x), __float_as_int(dw.y), __float_as_int(dw.z));
+                    }
                 }
             }
-            if (!PER_T && io.grad_basis && lane < C)   // (summed per leaf by the reduction for samples with records)
-                atomicAdd(&s_gb[lane], ax * leaf_elem<DT, C>(tr.wsig, tr.n_leaves, L, lane, tr.layout));
-        }
+            // samples without a record: every lane of the wavefront adds one
+            // component of each sample's row, whose basis its own lane makes first
+            uint64_t m = __ballot(has && my_rec < 0);
+            while (__builtin_expect_with_probability(m != 0, 0, 0.99999)) {
+                const int src = __builtin_ctzll(m);
+                m &= m - 1;
+                __builtin_amdgcn_wave_barrier();
+                if (lane == src) {
+                    RaySetup rs;
+                    float dmax, h[K], bv[C];
+                    const float d[3] = {dw.x, dw.y, dw.z};
+                    ray_direction<IDENT>(in, d, rs, dmax);
+                    time_setup(tr, in, PER_T ? ra.t[ray] : ra.t_scalar, rs.i0, rs.i1, rs.f);
+                    ray_basis<K, C>(tr, rs, h, bv);
+#pragma unroll
+                    for (int k = 0; k < K; ++k) srow[k] = h[k];
+#pragma unroll
+                    for (int c = 0; c < C; ++c) srow[K + c] = bv[c];
+                }
+                __builtin_amdgcn_wave_barrier();
+                const int L = __builtin_amdgcn_readlane(leaf, src);
+                const float a0 = readlane_f(gz0, src), a1 = readlane_f(gz1, src), a2 = readlane_f(gz2, src);
+                const float ax = readlane_f(gx, src);
+                float* row = io.grad_leaf + (int64_t)L * ROW;
+#pragma unroll
+                for (int c0 = 0; c0 < 3 * K + C; c0 += kWave) {
+                    const int c = c0 + lane;
+                    if (c < 3 * K) {
+                        const int ch = c / K;
+                        const float gzc = ch == 0 ? a0 : (ch == 1 ? a1 : a2);
+                        unsafeAtomicAdd(row + c, gzc * srow[c - ch * K]);
+                    } else if (c < 3 * K + C) {
+                        unsafeAtomicAdd(row + c, ax * srow[K + c - 3 * K]);
+                    }
+                }
+                if (!PER_T && io.grad_basis && lane < C)   // (summed per leaf by the reduction for samples with records)
+                    atomicAdd(&s_gb[lane], ax * leaf_elem<DT, C>(tr.wsig, tr.n_leaves, L, lane, tr.layout));
+            }
+        } while (__popcll(__ballot(!alive)) < limit);
     }
     if (!PER_T && io.grad_basis) {
         __syncthreads();
@@ -918,13 +938,11 @@ __global__ __launch_bounds__(kBlock) void reduce_records_kernel(TreeArgs tr, Ins
 template <int K, int C, int DT, bool EDIT, bool TRACE>
 static hipError_t fwd_e(const TreeArgs& tr, const InstArgs& in, const RayArgs& ra, float t_stop, const RenderOut& o,
                         hipStream_t st) {
-    if (in.identity) {
-        auto kern = render_fwd_kernel<K, C, DT, true, EDIT, TRACE>;
-        hipLaunchKernelGGL(kern, dim3(grid_for(kern, ra)), dim3(kBlock), 0, st, tr, in, ra, t_stop, o);
-    } else {
-        auto kern = render_fwd_kernel<K, C, DT, false, EDIT, TRACE>;
-        hipLaunchKernelGGL(kern, dim3(grid_for(kern, ra)), dim3(kBlock), 0, st, tr, in, ra, t_stop, o);
-    }
+    auto kern = ra.t ? (in.identity ? render_fwd_kernel<K, C, DT, true, EDIT, TRACE, true>
+                                    : render_fwd_kernel<K, C, DT, false, EDIT, TRACE, true>)
+                     : (in.identity ? render_fwd_kernel<K, C, DT, true, EDIT, TRACE, false>
+                                    : render_fwd_kernel<K, C, DT, false, EDIT, TRACE, false>);
+    hipLaunchKernelGGL(kern, dim3(grid_for(kern, ra)), dim3(kBlock), 0, st, tr, in, ra, t_stop, o);
     return hipGetLastError();
 }
 
@@ -948,7 +966,8 @@ static hipError_t fwd_t(const TreeArgs& tr, const InstArgs& in, const RayArgs& r
 template <int K, int C, int DT>
 static hipError_t bwd_walk(const TreeArgs& tr, const InstArgs& in, const RayArgs& ra, const BackwardIO& io,
                            const RecordArgs& rec, hipStream_t st) {
-    auto kern = in.identity ? render_bwd_kernel<K, C, DT, true> : render_bwd_kernel<K, C, DT, false>;
+    auto kern = ra.t ? (in.identity ? render_bwd_kernel<K, C, DT, true, true> : render_bwd_kernel<K, C, DT, false, true>)
+                     : (in.identity ? render_bwd_kernel<K, C, DT, true, false> : render_bwd_kernel<K, C, DT, false, false>);
     hipLaunchKernelGGL(kern, dim3(grid_for(kern, ra)), dim3(kBlock), 0, st, tr, in, ra, io, rec);
     return hipGetLastError();
 }

@@ -106,9 +106,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(L <= 3 ?
     int ns = 0;
 
     for (;;) {
-        const uint64_t idle = __ballot(!alive);
-        const int n_idle = __popcll(idle);
-        if (more && (n_idle >= ra.refill_min || n_idle == kWave)) {
+        for (;;) {   // refill, until too few lanes are idle or no rays are left
+            const uint64_t idle = __ballot(!alive);
+            const int n_idle = __popcll(idle);
+            if (!more || n_idle < ra.refill_min) break;
             bool cand = false;
             float o[3], d[3], t = 0.0f;
             for (;;) {
@@ -160,63 +161,65 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(L <= 3 ?
                     write_miss(out, ray);
                 }
             }
-            continue;
         }
-        if (n_idle == kWave) break;
-        if (alive) {
-            // next boundary of any instance, and the instances covering [u, nb)
-            double nb = 0.0;
-            bool have_nb = false;
-            float ksum = 0.0f, kc0 = 0.0f, kc1 = 0.0f, kc2 = 0.0f;
-#pragma unroll
-            for (int k = 0; k < L; ++k) {
-                if (!sg[k].has) continue;
-                const bool inside = !(u < sg[k].a);          // a <= u (< b)
-                const double e = inside ? sg[k].b : sg[k].a;
-                if (!have_nb || (e < nb)) { nb = e; have_nb = true; }
-                if (inside) {
-                    ksum += sg[k].kap;
-                    kc0 = fmaf(sg[k].kap, sg[k].c0, kc0);
-                    kc1 = fmaf(sg[k].kap, sg[k].c1, kc1);
-                    kc2 = fmaf(sg[k].kap, sg[k].c2, kc2);
-                }
-            }
-            bool finish = !have_nb;
-            if (have_nb && ksum > 0.0f) {
-                const float du = (float)(nb - u);
-                const float od = ksum * du;
-                float a, e_od;
-                absorb(od, a, e_od);
-                const float wt = Tr * a;
-                const float inv = 1.0f / ksum;
-                acc0 = fmaf(wt, kc0 * inv, acc0);
-                acc1 = fmaf(wt, kc1 * inv, acc1);
-                acc2 = fmaf(wt, kc2 * inv, acc2);
-                wsum += wt;
-                dsum = fmaf(wt, 0.5f * ((float)u + (float)nb) * dlen, dsum);
-                Tr *= e_od;
-                ++ns;
-                finish = t_stop > 0.0f && Tr < t_stop;
-            }
-            if (!finish) {
-                u = nb;
-                bool any = false;
+        if (!__ballot(alive)) break;
+        const int limit = more ? ra.refill_min : kWave;   // idle lanes that end the inner loop
+        do {
+            if (alive) {
+                // next boundary of any instance, and the instances covering [u, nb)
+                double nb = 0.0;
+                bool have_nb = false;
+                float ksum = 0.0f, kc0 = 0.0f, kc1 = 0.0f, kc2 = 0.0f;
 #pragma unroll
                 for (int k = 0; k < L; ++k) {
-                    if (sg[k].has && !(u < sg[k].b))        // this instance's segment ends here
-                        fetch_segment<DT>(ma.tr[k], rs[k], w[k], sg[k]);
-                    any = any || sg[k].has;
+                    if (!sg[k].has) continue;
+                    const bool inside = !(u < sg[k].a);          // a <= u (< b)
+                    const double e = inside ? sg[k].b : sg[k].a;
+                    if (!have_nb || (e < nb)) { nb = e; have_nb = true; }
+                    if (inside) {
+                        ksum += sg[k].kap;
+                        kc0 = fmaf(sg[k].kap, sg[k].c0, kc0);
+                        kc1 = fmaf(sg[k].kap, sg[k].c1, kc1);
+                        kc2 = fmaf(sg[k].kap, sg[k].c2, kc2);
+                    }
                 }
-                finish = !any;
+                bool finish = !have_nb;
+                if (have_nb && ksum > 0.0f) {
+                    const float du = (float)(nb - u);
+                    const float od = ksum * du;
+                    float a, e_od;
+                    absorb(od, a, e_od);
+                    const float wt = Tr * a;
+                    const float inv = 1.0f / ksum;
+                    acc0 = fmaf(wt, kc0 * inv, acc0);
+                    acc1 = fmaf(wt, kc1 * inv, acc1);
+                    acc2 = fmaf(wt, kc2 * inv, acc2);
+                    wsum += wt;
+                    dsum = fmaf(wt, 0.5f * ((float)u + (float)nb) * dlen, dsum);
+                    Tr *= e_od;
+                    ++ns;
+                    finish = t_stop > 0.0f && Tr < t_stop;
+                }
+                if (!finish) {
+                    u = nb;
+                    bool any = false;
+#pragma unroll
+                    for (int k = 0; k < L; ++k) {
+                        if (sg[k].has && !(u < sg[k].b))        // this instance's segment ends here
+                            fetch_segment<DT>(ma.tr[k], rs[k], w[k], sg[k]);
+                        any = any || sg[k].has;
+                    }
+                    finish = !any;
+                }
+                if (finish) {
+                    if (out.rgb) { out.rgb[3 * ray] = acc0; out.rgb[3 * ray + 1] = acc1; out.rgb[3 * ray + 2] = acc2; }
+                    if (out.alpha) out.alpha[ray] = 1.0f - Tr;
+                    if (out.depth) out.depth[ray] = wsum > 0.0f ? dsum / wsum : INFINITY;
+                    if (out.nsamp) out.nsamp[ray] = ns;
+                    alive = false;
+                }
             }
-            if (finish) {
-                if (out.rgb) { out.rgb[3 * ray] = acc0; out.rgb[3 * ray + 1] = acc1; out.rgb[3 * ray + 2] = acc2; }
-                if (out.alpha) out.alpha[ray] = 1.0f - Tr;
-                if (out.depth) out.depth[ray] = wsum > 0.0f ? dsum / wsum : INFINITY;
-                if (out.nsamp) out.nsamp[ray] = ns;
-                alive = false;
-            }
-        }
+        } while (__popcll(__ballot(!alive)) < limit);
     }
 }
 
@@ -262,12 +265,15 @@ __device__ __forceinline__ void store_entry(int4* ent, int slot, double b, float
     e[1] = make_int4(__float_as_int(c1), __float_as_int(c2), next, 0);
 }
 
-template <int DT, bool IDENT>
+template <int DT, bool IDENT, bool PER_T>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 8))) void merge_emit_kernel(
     TreeArgs tr, InstArgs in, RayArgs ra, float t_stop, MergeLists ml) {
     if (no_candidates(ra)) return;
     __shared__ float s_h[kBlock * 16];
-    __shared__ float s_b[kBlock * 8];
+    __shared__ float s_b[PER_T ? kBlock * 8 : 1];
+    __shared__ CommonTime<8> s_ct;
+    if constexpr (!PER_T) stage_common_time<8>(tr, in, ra.t_scalar, s_ct);
+    __syncthreads();
     ChunkCursor cc = chunk_cursor();
     bool more = true;
 
@@ -276,7 +282,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 8))) 
     RaySetup rs;
     Walk w;
     float* const hl = s_h + threadIdx.x * 16;
-    float* const bl = s_b + threadIdx.x * 8;
+    const float* const bl = PER_T ? s_b + threadIdx.x * 8 : s_ct.b;
     float Tr = 1.0f;
     int first = -1;               // the ray's first entry; -2: the room ran out
     int pslot = -1;               // the last segment's entry, stored once what follows it is known
@@ -285,9 +291,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 8))) 
     int tcur = 0, tend = 0;   // what is left of the wavefront's block of entries (wave-uniform)
 
     for (;;) {
-        const uint64_t idle = __ballot(!alive);
-        const int n_idle = __popcll(idle);
-        if (more && (n_idle >= ra.refill_min || n_idle == kWave)) {
+        for (;;) {   // refill, until too few lanes are idle or no rays are left
+            const uint64_t idle = __ballot(!alive);
+            const int n_idle = __popcll(idle);
+            if (!more || n_idle < ra.refill_min) break;
             bool cand = false;
             float o[3], d[3], t = 0.0f;
             for (;;) {
@@ -306,7 +313,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 8))) 
                         if (ray >= 0) {
                             o[0] = ra.o[3 * ray]; o[1] = ra.o[3 * ray + 1]; o[2] = ra.o[3 * ray + 2];
                             d[0] = ra.d[3 * ray]; d[1] = ra.d[3 * ray + 1]; d[2] = ra.d[3 * ray + 2];
-                            t = ra.t ? ra.t[ray] : ra.t_scalar;
+                            if constexpr (PER_T) t = ra.t[ray];
                             cand = ray_may_hit<IDENT>(tr, in, o, d);   // (the list holds rays of any instance)
                         }
                     }
@@ -314,17 +321,25 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 8))) 
                 cc.pos += take;
             }
             if (cand) {
-                ray_setup<IDENT>(tr, in, o, d, t, rs);
+                ray_geometry<IDENT>(tr, in, o, d, rs);
                 if (rs.hit) {
-                    float hall[30];
-                    const float gam = (1.0f - rs.f) * tr.gamma[rs.i0] + rs.f * tr.gamma[rs.i1];
-                    hh_all(rs.dir[0], rs.dir[1], rs.dir[2], gam, hall);
+                    float h[16];
+                    if constexpr (!PER_T) {
+                        common_basis<16, 8>(s_ct, rs.dir, h);
+                    } else {
+                        float hall[30];
+                        time_setup(tr, in, t, rs.i0, rs.i1, rs.f);
+                        const float gam = (1.0f - rs.f) * tr.gamma[rs.i0] + rs.f * tr.gamma[rs.i1];
+                        hh_all(rs.dir[0], rs.dir[1], rs.dir[2], gam, hall);
 #pragma unroll
-                    for (int k = 0; k < 16; ++k) hl[k] = hall[k];
-                    const float* b0 = tr.basis + (int64_t)rs.i0 * 8;
-                    const float* b1 = tr.basis + (int64_t)rs.i1 * 8;
+                        for (int k = 0; k < 16; ++k) h[k] = hall[k];
+                        const float* b0 = tr.basis + (int64_t)rs.i0 * 8;
+                        const float* b1 = tr.basis + (int64_t)rs.i1 * 8;
 #pragma unroll
-                    for (int c = 0; c < 8; ++c) bl[c] = (1.0f - rs.f) * b0[c] + rs.f * b1[c];
+                        for (int c = 0; c < 8; ++c) s_b[threadIdx.x * 8 + c] = (1.0f - rs.f) * b0[c] + rs.f * b1[c];
+                    }
+#pragma unroll
+                    for (int k = 0; k < 16; ++k) hl[k] = h[k];
                     walk_begin(tr, rs, w);
                     alive = true;
                     Tr = 1.0f;
@@ -332,65 +347,67 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 8))) 
                     pslot = -1;
                 }
             }
-            continue;
         }
-        if (n_idle == kWave) break;
-        bool finish = false;
-        int leaf = -1;
-        float delta = 0.0f, umid = 0.0f;
-        double a = 0.0, b = 0.0;
-        if (alive) {
-            leaf = walk_next<kWalkBudget>(tr, rs, w, delta, umid, a, b);
-            finish = leaf == -1;
-        }
-        // this iteration's entries: the segment, after a gap entry when it does
-        // not start where the previous one ended (always before the first)
-        const bool gap = leaf >= 0 && (pslot < 0 || (pb < a));
-        const uint64_t m1 = __ballot(leaf >= 0), m2 = __ballot(gap);
-        const int n_e = __popcll(m1) + __popcll(m2);
-        const int at = n_e > 0 ? take_items(ml.counter, ml.cap, n_e, tcur, tend) : -1;
-        if (leaf >= 0) {
-            if (at < 0) {
-                first = -2;   // the room ran out: the fused kernel renders this ray
-                finish = true;
-            } else {
-                const int e0 = (int)(at + lane_rank(m1) + lane_rank(m2));
-                const int seg = gap ? e0 + 1 : e0;
-                float wv[48], sv[8];
-                load_leaf<DT, 48>(tr.hh, tr.n_leaves, leaf, tr.layout, wv);
-                load_leaf<DT, 8>(tr.wsig, tr.n_leaves, leaf, tr.layout, sv);
-                if (pslot >= 0) store_entry(ml.ent, pslot, pb, pk, pc0, pc1, pc2, e0);
-                if (gap) store_entry(ml.ent, e0, a, 0.0f, 0.0f, 0.0f, 0.0f, seg);
-                if (first == -1) first = e0;
-                float x = 0.0f;
-#pragma unroll
-                for (int c = 0; c < 8; ++c) x = fmaf(sv[c], bl[c], x);
-                float z0 = 0.0f, z1 = 0.0f, z2 = 0.0f;
-#pragma unroll
-                for (int k = 0; k < 16; ++k) {
-                    const float hk = hl[k];
-                    z0 = fmaf(wv[k], hk, z0);
-                    z1 = fmaf(wv[16 + k], hk, z1);
-                    z2 = fmaf(wv[32 + k], hk, z2);
-                }
-                const float sig = density_f(x, tr.relu);
-                pslot = seg;
-                pb = b;
-                pk = sig * rs.len_local;
-                pc0 = sigmoid_f(z0);
-                pc1 = sigmoid_f(z1);
-                pc2 = sigmoid_f(z2);
-                float al, e_od;
-                absorb(sig * delta, al, e_od);
-                Tr *= e_od;
-                finish = t_stop > 0.0f && Tr < kEmitStop * t_stop;
+        if (!__ballot(alive)) break;
+        const int limit = more ? ra.refill_min : kWave;   // idle lanes that end the inner loop
+        do {
+            bool finish = false;
+            int leaf = -1;
+            float delta = 0.0f, umid = 0.0f;
+            double a = 0.0, b = 0.0;
+            if (alive) {
+                leaf = walk_next<kWalkBudget>(tr, rs, w, delta, umid, a, b);
+                finish = leaf == -1;
             }
-        }
-        if (alive && finish) {
-            if (first >= 0) store_entry(ml.ent, pslot, pb, pk, pc0, pc1, pc2, -1);
-            ml.head[ray] = first;
-            alive = false;
-        }
+            // this iteration's entries: the segment, after a gap entry when it does
+            // not start where the previous one ended (always before the first)
+            const bool gap = leaf >= 0 && (pslot < 0 || (pb < a));
+            const uint64_t m1 = __ballot(leaf >= 0), m2 = __ballot(gap);
+            const int n_e = __popcll(m1) + __popcll(m2);
+            const int at = n_e > 0 ? take_items(ml.counter, ml.cap, n_e, tcur, tend) : -1;
+            if (leaf >= 0) {
+                if (at < 0) {
+                    first = -2;   // the room ran out: the fused kernel renders this ray
+                    finish = true;
+                } else {
+                    const int e0 = (int)(at + lane_rank(m1) + lane_rank(m2));
+                    const int seg = gap ? e0 + 1 : e0;
+                    float wv[48], sv[8];
+                    load_leaf<DT, 48>(tr.hh, tr.n_leaves, leaf, tr.layout, wv);
+                    load_leaf<DT, 8>(tr.wsig, tr.n_leaves, leaf, tr.layout, sv);
+                    if (pslot >= 0) store_entry(ml.ent, pslot, pb, pk, pc0, pc1, pc2, e0);
+                    if (gap) store_entry(ml.ent, e0, a, 0.0f, 0.0f, 0.0f, 0.0f, seg);
+                    if (first == -1) first = e0;
+                    float x = 0.0f;
+#pragma unroll
+                    for (int c = 0; c < 8; ++c) x = fmaf(sv[c], bl[c], x);
+                    float z0 = 0.0f, z1 = 0.0f, z2 = 0.0f;
+#pragma unroll
+                    for (int k = 0; k < 16; ++k) {
+                        const float hk = hl[k];
+                        z0 = fmaf(wv[k], hk, z0);
+                        z1 = fmaf(wv[16 + k], hk, z1);
+                        z2 = fmaf(wv[32 + k], hk, z2);
+                    }
+                    const float sig = density_f(x, tr.relu);
+                    pslot = seg;
+                    pb = b;
+                    pk = sig * rs.len_local;
+                    pc0 = sigmoid_f(z0);
+                    pc1 = sigmoid_f(z1);
+                    pc2 = sigmoid_f(z2);
+                    float al, e_od;
+                    absorb(sig * delta, al, e_od);
+                    Tr *= e_od;
+                    finish = t_stop > 0.0f && Tr < kEmitStop * t_stop;
+                }
+            }
+            if (alive && finish) {
+                if (first >= 0) store_entry(ml.ent, pslot, pb, pk, pc0, pc1, pc2, -1);
+                ml.head[ray] = first;
+                alive = false;
+            }
+        } while (__popcll(__ballot(!alive)) < limit);
     }
 }
 
@@ -439,9 +456,10 @@ __global__ __launch_bounds__(kBlock) void merge_lists_kernel(RayArgs ra, const i
     const int64_t n = ra.n;
 
     for (;;) {
-        const uint64_t idle = __ballot(!alive);
-        const int n_idle = __popcll(idle);
-        if (more && (n_idle >= ra.refill_min || n_idle == kWave)) {
+        for (;;) {   // refill, until too few lanes are idle or no rays are left
+            const uint64_t idle = __ballot(!alive);
+            const int n_idle = __popcll(idle);
+            if (!more || n_idle < ra.refill_min) break;
             bool cand = false;
             int hd[L];
             for (;;) {
@@ -498,58 +516,60 @@ __global__ __launch_bounds__(kBlock) void merge_lists_kernel(RayArgs ra, const i
                 }
                 alive = true;
             }
-            continue;
         }
-        if (n_idle == kWave) break;
-        if (alive) {
-            // every instance whose entry ends here moves to its next entry
+        if (!__ballot(alive)) break;
+        const int limit = more ? ra.refill_min : kWave;   // idle lanes that end the inner loop
+        do {
+            if (alive) {
+                // every instance whose entry ends here moves to its next entry
 #pragma unroll
-            for (int k = 0; k < L; ++k) {
-                if (act[k] && !(u < cb[k])) {
-                    if (nx[k] >= 0) load_entry(ent, nx[k], cb[k], ck[k], cr[k], cg[k], cbl[k], nx[k]);
-                    else act[k] = false;
+                for (int k = 0; k < L; ++k) {
+                    if (act[k] && !(u < cb[k])) {
+                        if (nx[k] >= 0) load_entry(ent, nx[k], cb[k], ck[k], cr[k], cg[k], cbl[k], nx[k]);
+                        else act[k] = false;
+                    }
+                }
+                // the next entry end, and the extinction and colour over [u, nb)
+                double nb = 0.0;
+                bool any = false;
+                float ksum = 0.0f, kc0 = 0.0f, kc1 = 0.0f, kc2 = 0.0f;
+#pragma unroll
+                for (int k = 0; k < L; ++k) {
+                    if (!act[k]) continue;
+                    if (!any || (cb[k] < nb)) nb = cb[k];
+                    any = true;
+                    ksum += ck[k];
+                    kc0 = fmaf(ck[k], cr[k], kc0);
+                    kc1 = fmaf(ck[k], cg[k], kc1);
+                    kc2 = fmaf(ck[k], cbl[k], kc2);
+                }
+                bool finish = !any;
+                if (any && ksum > 0.0f) {
+                    const float du = (float)(nb - u);
+                    const float od = ksum * du;
+                    float a, e_od;
+                    absorb(od, a, e_od);
+                    const float wt = Tr * a;
+                    const float inv = 1.0f / ksum;
+                    acc0 = fmaf(wt, kc0 * inv, acc0);
+                    acc1 = fmaf(wt, kc1 * inv, acc1);
+                    acc2 = fmaf(wt, kc2 * inv, acc2);
+                    wsum += wt;
+                    dsum = fmaf(wt, 0.5f * ((float)u + (float)nb) * dlen, dsum);
+                    Tr *= e_od;
+                    ++ns;
+                    finish = t_stop > 0.0f && Tr < t_stop;
+                }
+                if (!finish) u = nb;
+                if (finish) {
+                    if (out.rgb) { out.rgb[3 * ray] = acc0; out.rgb[3 * ray + 1] = acc1; out.rgb[3 * ray + 2] = acc2; }
+                    if (out.alpha) out.alpha[ray] = 1.0f - Tr;
+                    if (out.depth) out.depth[ray] = wsum > 0.0f ? dsum / wsum : INFINITY;
+                    if (out.nsamp) out.nsamp[ray] = ns;
+                    alive = false;
                 }
             }
-            // the next entry end, and the extinction and colour over [u, nb)
-            double nb = 0.0;
-            bool any = false;
-            float ksum = 0.0f, kc0 = 0.0f, kc1 = 0.0f, kc2 = 0.0f;
-#pragma unroll
-            for (int k = 0; k < L; ++k) {
-                if (!act[k]) continue;
-                if (!any || (cb[k] < nb)) nb = cb[k];
-                any = true;
-                ksum += ck[k];
-                kc0 = fmaf(ck[k], cr[k], kc0);
-                kc1 = fmaf(ck[k], cg[k], kc1);
-                kc2 = fmaf(ck[k], cbl[k], kc2);
-            }
-            bool finish = !any;
-            if (any && ksum > 0.0f) {
-                const float du = (float)(nb - u);
-                const float od = ksum * du;
-                float a, e_od;
-                absorb(od, a, e_od);
-                const float wt = Tr * a;
-                const float inv = 1.0f / ksum;
-                acc0 = fmaf(wt, kc0 * inv, acc0);
-                acc1 = fmaf(wt, kc1 * inv, acc1);
-                acc2 = fmaf(wt, kc2 * inv, acc2);
-                wsum += wt;
-                dsum = fmaf(wt, 0.5f * ((float)u + (float)nb) * dlen, dsum);
-                Tr *= e_od;
-                ++ns;
-                finish = t_stop > 0.0f && Tr < t_stop;
-            }
-            if (!finish) u = nb;
-            if (finish) {
-                if (out.rgb) { out.rgb[3 * ray] = acc0; out.rgb[3 * ray + 1] = acc1; out.rgb[3 * ray + 2] = acc2; }
-                if (out.alpha) out.alpha[ray] = 1.0f - Tr;
-                if (out.depth) out.depth[ray] = wsum > 0.0f ? dsum / wsum : INFINITY;
-                if (out.nsamp) out.nsamp[ray] = ns;
-                alive = false;
-            }
-        }
+        } while (__popcll(__ballot(!alive)) < limit);
     }
 }
 
@@ -600,15 +620,10 @@ static hipError_t multi_lists(const MultiArgs& ma, const RayArgs& ra, float t_st
                     RayArgs rk = r;
                     rk.queue = q_emit + (size_t)k * 128;
                     const MergeLists ml{head + (int64_t)k * n, ent, counter, cap};
-                    if (ma.in[k].identity) {
-                        auto kern = merge_emit_kernel<DT, true>;
-                        hipLaunchKernelGGL(kern, dim3(grid_for(kern, rk)), dim3(kBlock), 0, st, ma.tr[k], ma.in[k],
-                                           rk, t_stop, ml);
-                    } else {
-                        auto kern = merge_emit_kernel<DT, false>;
-                        hipLaunchKernelGGL(kern, dim3(grid_for(kern, rk)), dim3(kBlock), 0, st, ma.tr[k], ma.in[k],
-                                           rk, t_stop, ml);
-                    }
+                    auto kern = rk.t ? (ma.in[k].identity ? merge_emit_kernel<DT, true, true> : merge_emit_kernel<DT, false, true>)
+                                     : (ma.in[k].identity ? merge_emit_kernel<DT, true, false> : merge_emit_kernel<DT, false, false>);
+                    hipLaunchKernelGGL(kern, dim3(grid_for(kern, rk)), dim3(kBlock), 0, st, ma.tr[k], ma.in[k], rk, t_stop,
+                                       ml);
                     le = hipGetLastError();
                 }
                 return le;

@@ -174,9 +174,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 8))) 
           pq2 = 0.0f;
 
     for (;;) {
-        const uint64_t idle = __ballot(!alive);
-        const int n_idle = __popcll(idle);
-        if (more && (n_idle >= ra.refill_min || n_idle == kWave)) {
+        for (;;) {   // refill, until too few lanes are idle or no rays are left
+            const uint64_t idle = __ballot(!alive);
+            const int n_idle = __popcll(idle);
+            if (!more || n_idle < ra.refill_min) break;
             bool cand = false;
             float o[3], d[3], t = 0.0f;
             for (;;) {
@@ -204,7 +205,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 8))) 
                 cc.pos += take;
             }
             if (cand) {
-                ray_setup<IDENT>(tr, in, o, d, t, rs);
+                ray_geometry<IDENT>(tr, in, o, d, rs);
+                if (!common_t) time_setup(tr, in, t, rs.i0, rs.i1, rs.f);
                 Tr = 1.0f; acc0 = acc1 = acc2 = 0.0f; wsum = dsum = 0.0f; ns = 0;
                 if (rs.hit) {
                     sh_deg2(rs.dir[0], rs.dir[1], rs.dir[2], Y);
@@ -216,83 +218,85 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 8))) 
                     write_miss(out, ray);
                 }
             }
-            continue;
         }
-        if (n_idle == kWave) break;
-        bool finish = false;
-        int leaf = -1;
-        float delta = 0.0f, umid = 0.0f;
-        if (alive) {
-            leaf = walk_next<kWalkBudget>(tr, rs, w, delta, umid);
-            finish = leaf == -1;
-        }
-        int cur = -1;
-        if constexpr (TRACE) {
-            const uint64_t hm = __ballot(leaf >= 0);
-            const int n_s = __popcll(hm);
-            const int at = n_s > 0 ? take_items(out.trace.counter, t_room, n_s, tcur, tend) : -1;
-            if (leaf >= 0) {
-                if (at >= 0 && t_first != -2) {
-                    cur = (int)(at + lane_rank(hm));
-                    if (t_first == -1) t_first = cur;
-                } else {
-                    t_first = -2;   // incomplete: the adjoint walks this ray
+        if (!__ballot(alive)) break;
+        const int limit = more ? ra.refill_min : kWave;   // idle lanes that end the inner loop
+        do {
+            bool finish = false;
+            int leaf = -1;
+            float delta = 0.0f, umid = 0.0f;
+            if (alive) {
+                leaf = walk_next<kWalkBudget>(tr, rs, w, delta, umid);
+                finish = leaf == -1;
+            }
+            int cur = -1;
+            if constexpr (TRACE) {
+                const uint64_t hm = __ballot(leaf >= 0);
+                const int n_s = __popcll(hm);
+                const int at = n_s > 0 ? take_items(out.trace.counter, t_room, n_s, tcur, tend) : -1;
+                if (leaf >= 0) {
+                    if (at >= 0 && t_first != -2) {
+                        cur = (int)(at + lane_rank(hm));
+                        if (t_first == -1) t_first = cur;
+                    } else {
+                        t_first = -2;   // incomplete: the adjoint walks this ray
+                    }
                 }
             }
-        }
-        if (leaf >= 0) {
-            PPSample<DT> p;
-            pp_load<DT>(tr, leaf, p);
-            if constexpr (TRACE) {
-                // the previous sample's entry, linked to this one; a ray's first
-                // sample stores a placeholder into its own slot (overwritten by this
-                // lane later), an incomplete trace into its last slot or the spare
-                // half of the trace header
-                const int tgt = pslot >= 0 ? pslot : cur;
-                int4* dst = tgt >= 0 ? out.trace.smp + kPPTraceInt4 * (int64_t)tgt
-                                     : reinterpret_cast<int4*>(reinterpret_cast<char*>(out.trace.counter) + 1024) +
-                                           kPPTraceInt4 * (threadIdx.x & 15);
-                dst[0] = make_int4(pleaf, __float_as_int(pdelta), __float_as_int(px), __float_as_int(py));
-                dst[1] = make_int4(__float_as_int(pc0), __float_as_int(pc1), __float_as_int(pc2), cur);
-                dst[2] = make_int4(__float_as_int(pq0), __float_as_int(pq1), __float_as_int(pq2), 0);
-            }
-            pp_compute<DT>(tr, rs, Y, s_b, s_bg, p);
-            const float sig = density_f(p.x, tr.relu);
-            const float od = sig * delta;
-            float a, e_od;
-            absorb(od, a, e_od);
-            const float wt = Tr * a;
-            const float c0 = sigmoid_f(p.z0), c1 = sigmoid_f(p.z1), c2 = sigmoid_f(p.z2);
-            acc0 = fmaf(wt, c0, acc0);
-            acc1 = fmaf(wt, c1, acc1);
-            acc2 = fmaf(wt, c2, acc2);
-            wsum += wt;
-            dsum = fmaf(wt, umid * rs.len_world, dsum);
-            Tr *= e_od;
-            ++ns;
-            finish = t_stop > 0.0f && Tr < t_stop;
-            if constexpr (TRACE) {
-                if (cur >= 0) pslot = cur;
-                pleaf = leaf; pdelta = delta; px = p.x; py = p.y; pc0 = c0; pc1 = c1; pc2 = c2;
-                pp_dz_dgamma<DT>(p, Y, pq0, pq1, pq2);
-            }
-        }
-        if (alive && finish) {
-            out.rgb[3 * ray] = acc0; out.rgb[3 * ray + 1] = acc1; out.rgb[3 * ray + 2] = acc2;
-            out.alpha[ray] = 1.0f - Tr;
-            if (out.depth) out.depth[ray] = wsum > 0.0f ? dsum / wsum : INFINITY;
-            out.nsamp[ray] = ns;
-            if constexpr (TRACE) {
-                if (t_first >= 0) {
-                    int4* dst = out.trace.smp + kPPTraceInt4 * (int64_t)pslot;
+            if (leaf >= 0) {
+                PPSample<DT> p;
+                pp_load<DT>(tr, leaf, p);
+                if constexpr (TRACE) {
+                    // the previous sample's entry, linked to this one; a ray's first
+                    // sample stores a placeholder into its own slot (overwritten by this
+                    // lane later), an incomplete trace into its last slot or the spare
+                    // half of the trace header
+                    const int tgt = pslot >= 0 ? pslot : cur;
+                    int4* dst = tgt >= 0 ? out.trace.smp + kPPTraceInt4 * (int64_t)tgt
+                                         : reinterpret_cast<int4*>(reinterpret_cast<char*>(out.trace.counter) + 1024) +
+                                               kPPTraceInt4 * (threadIdx.x & 15);
                     dst[0] = make_int4(pleaf, __float_as_int(pdelta), __float_as_int(px), __float_as_int(py));
-                    dst[1] = make_int4(__float_as_int(pc0), __float_as_int(pc1), __float_as_int(pc2), -1);
+                    dst[1] = make_int4(__float_as_int(pc0), __float_as_int(pc1), __float_as_int(pc2), cur);
                     dst[2] = make_int4(__float_as_int(pq0), __float_as_int(pq1), __float_as_int(pq2), 0);
                 }
-                out.trace.head[ray] = t_first >= 0 ? t_first : -1;
+                pp_compute<DT>(tr, rs, Y, s_b, s_bg, p);
+                const float sig = density_f(p.x, tr.relu);
+                const float od = sig * delta;
+                float a, e_od;
+                absorb(od, a, e_od);
+                const float wt = Tr * a;
+                const float c0 = sigmoid_f(p.z0), c1 = sigmoid_f(p.z1), c2 = sigmoid_f(p.z2);
+                acc0 = fmaf(wt, c0, acc0);
+                acc1 = fmaf(wt, c1, acc1);
+                acc2 = fmaf(wt, c2, acc2);
+                wsum += wt;
+                dsum = fmaf(wt, umid * rs.len_world, dsum);
+                Tr *= e_od;
+                ++ns;
+                finish = t_stop > 0.0f && Tr < t_stop;
+                if constexpr (TRACE) {
+                    if (cur >= 0) pslot = cur;
+                    pleaf = leaf; pdelta = delta; px = p.x; py = p.y; pc0 = c0; pc1 = c1; pc2 = c2;
+                    pp_dz_dgamma<DT>(p, Y, pq0, pq1, pq2);
+                }
             }
-            alive = false;
-        }
+            if (alive && finish) {
+                out.rgb[3 * ray] = acc0; out.rgb[3 * ray + 1] = acc1; out.rgb[3 * ray + 2] = acc2;
+                out.alpha[ray] = 1.0f - Tr;
+                if (out.depth) out.depth[ray] = wsum > 0.0f ? dsum / wsum : INFINITY;
+                out.nsamp[ray] = ns;
+                if constexpr (TRACE) {
+                    if (t_first >= 0) {
+                        int4* dst = out.trace.smp + kPPTraceInt4 * (int64_t)pslot;
+                        dst[0] = make_int4(pleaf, __float_as_int(pdelta), __float_as_int(px), __float_as_int(py));
+                        dst[1] = make_int4(__float_as_int(pc0), __float_as_int(pc1), __float_as_int(pc2), -1);
+                        dst[2] = make_int4(__float_as_int(pq0), __float_as_int(pq1), __float_as_int(pq2), 0);
+                    }
+                    out.trace.head[ray] = t_first >= 0 ? t_first : -1;
+                }
+                alive = false;
+            }
+        } while (__popcll(__ballot(!alive)) < limit);
     }
 }
 
@@ -352,9 +356,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(REPLAY ?
     int wrec = 0, wend = 0;
 
     for (;;) {
-        const uint64_t idle = __ballot(!alive);
-        const int n_idle = __popcll(idle);
-        if (more && (n_idle >= ra.refill_min || n_idle == kWave)) {
+        for (;;) {   // refill, until too few lanes are idle or no rays are left
+            const uint64_t idle = __ballot(!alive);
+            const int n_idle = __popcll(idle);
+            if (!more || n_idle < ra.refill_min) break;
             bool cand = false;
             for (;;) {
                 const uint64_t need = __ballot(!alive && !cand);
@@ -377,8 +382,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(REPLAY ?
             if (cand) {
                 const float o[3] = {ra.o[3 * ray], ra.o[3 * ray + 1], ra.o[3 * ray + 2]};
                 const float d[3] = {ra.d[3 * ray], ra.d[3 * ray + 1], ra.d[3 * ray + 2]};
-                const float t = ra.t ? ra.t[ray] : ra.t_scalar;
-                ray_setup<IDENT>(tr, in, o, d, t, rs);
+                ray_geometry<IDENT>(tr, in, o, d, rs);
+                if (!common_t) time_setup(tr, in, ra.t[ray], rs.i0, rs.i1, rs.f);
                 if (rs.hit) {
                     sh_deg2(rs.dir[0], rs.dir[1], rs.dir[2], Y);
                     if constexpr (REPLAY) tnext = io.trace.head[ray];
@@ -394,182 +399,184 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(REPLAY ?
                     alive = true;
                 }
             }
-            continue;
         }
-        if (n_idle == kWave) break;
-        bool has = false;
-        int leaf = -1, my_rec = -1;
-        float gz0 = 0.0f, gz1 = 0.0f, gz2 = 0.0f, gx = 0.0f, gy = 0.0f, y = 0.0f;
-        if (alive) {
-            float delta = 0.0f, x = 0.0f, c0 = 0.0f, c1 = 0.0f, c2 = 0.0f, q0 = 0.0f, q1 = 0.0f, q2 = 0.0f;
-            bool finish;
-            if constexpr (REPLAY) {
-                // replay the forward's sample
-                if (tnext >= 0) {
-                    const int4* e = io.trace.smp + kPPTraceInt4 * (int64_t)tnext;
-                    const int4 A = e[0], B = e[1], Q = e[2];
-                    leaf = A.x;
-                    delta = __int_as_float(A.y);
-                    x = __int_as_float(A.z);
-                    y = __int_as_float(A.w);
-                    c0 = __int_as_float(B.x);
-                    c1 = __int_as_float(B.y);
-                    c2 = __int_as_float(B.z);
-                    tnext = B.w;
-                    q0 = __int_as_float(Q.x);
-                    q1 = __int_as_float(Q.y);
-                    q2 = __int_as_float(Q.z);
+        if (!__ballot(alive)) break;
+        const int limit = more ? ra.refill_min : kWave;   // idle lanes that end the inner loop
+        do {
+            bool has = false;
+            int leaf = -1, my_rec = -1;
+            float gz0 = 0.0f, gz1 = 0.0f, gz2 = 0.0f, gx = 0.0f, gy = 0.0f, y = 0.0f;
+            if (alive) {
+                float delta = 0.0f, x = 0.0f, c0 = 0.0f, c1 = 0.0f, c2 = 0.0f, q0 = 0.0f, q1 = 0.0f, q2 = 0.0f;
+                bool finish;
+                if constexpr (REPLAY) {
+                    // replay the forward's sample
+                    if (tnext >= 0) {
+                        const int4* e = io.trace.smp + kPPTraceInt4 * (int64_t)tnext;
+                        const int4 A = e[0], B = e[1], Q = e[2];
+                        leaf = A.x;
+                        delta = __int_as_float(A.y);
+                        x = __int_as_float(A.z);
+                        y = __int_as_float(A.w);
+                        c0 = __int_as_float(B.x);
+                        c1 = __int_as_float(B.y);
+                        c2 = __int_as_float(B.z);
+                        tnext = B.w;
+                        q0 = __int_as_float(Q.x);
+                        q1 = __int_as_float(Q.y);
+                        q2 = __int_as_float(Q.z);
+                    }
+                    finish = leaf < 0;
+                } else {
+                    float umid;
+                    leaf = walk_next<kWalkBudgetBwd>(tr, rs, w, delta, umid);
+                    finish = leaf == -1;
+                    if (leaf >= 0) {
+                        PPSample<DT> p;
+                        pp_load<DT>(tr, leaf, p);
+                        pp_compute<DT>(tr, rs, Y, s_b, s_bg, p);
+                        x = p.x;
+                        y = p.y;
+                        c0 = sigmoid_f(p.z0);
+                        c1 = sigmoid_f(p.z1);
+                        c2 = sigmoid_f(p.z2);
+                        pp_dz_dgamma<DT>(p, Y, q0, q1, q2);
+#pragma unroll
+                        for (int k = 0; k < K; ++k) s_h[threadIdx.x * K + k] = p.h[k];
+                    }
                 }
-                finish = leaf < 0;
-            } else {
-                float umid;
-                leaf = walk_next<kWalkBudgetBwd>(tr, rs, w, delta, umid);
-                finish = leaf == -1;
                 if (leaf >= 0) {
-                    PPSample<DT> p;
-                    pp_load<DT>(tr, leaf, p);
-                    pp_compute<DT>(tr, rs, Y, s_b, s_bg, p);
-                    x = p.x;
-                    y = p.y;
-                    c0 = sigmoid_f(p.z0);
-                    c1 = sigmoid_f(p.z1);
-                    c2 = sigmoid_f(p.z2);
-                    pp_dz_dgamma<DT>(p, Y, q0, q1, q2);
-#pragma unroll
-                    for (int k = 0; k < K; ++k) s_h[threadIdx.x * K + k] = p.h[k];
+                    const float sig = density_f(x, tr.relu);
+                    const float od = sig * delta;
+                    float a, e;
+                    absorb(od, a, e);
+                    const float wt = Tr * a;
+                    const float Tn = Tr * e;
+                    p0 = fmaf(wt, c0, p0);
+                    p1 = fmaf(wt, c1, p1);
+                    p2 = fmaf(wt, c2, p2);
+                    const float gdotc = g0 * c0 + g1 * c1 + g2 * c2;
+                    const float gsuf = g0 * (F0 - p0) + g1 * (F1 - p1) + g2 * (F2 - p2);
+                    const float gsig = delta * (Tn * gdotc - gsuf) + ga * delta * Tfin;
+                    gx = gsig * density_dx(x, tr.relu);
+                    gz0 = g0 * wt * c0 * (1.0f - c0);
+                    gz1 = g1 * wt * c1 * (1.0f - c1);
+                    gz2 = g2 * wt * c2 * (1.0f - c2);
+                    // dL/dgamma through every h_k = g_nl(gamma) Y_k
+                    const float ggam = gz0 * q0 + gz1 * q1 + gz2 * q2;
+                    const float sg = sigmoid_f(y);
+                    gy = ggam * kPi * sg * (1.0f - sg);
+                    has = true;
+                    Tr = Tn;
+                    ++ns;
+                    finish = ns >= ns_fwd;
                 }
+                if (finish) alive = false;
             }
-            if (leaf >= 0) {
-                const float sig = density_f(x, tr.relu);
-                const float od = sig * delta;
-                float a, e;
-                absorb(od, a, e);
-                const float wt = Tr * a;
-                const float Tn = Tr * e;
-                p0 = fmaf(wt, c0, p0);
-                p1 = fmaf(wt, c1, p1);
-                p2 = fmaf(wt, c2, p2);
-                const float gdotc = g0 * c0 + g1 * c1 + g2 * c2;
-                const float gsuf = g0 * (F0 - p0) + g1 * (F1 - p1) + g2 * (F2 - p2);
-                const float gsig = delta * (Tn * gdotc - gsuf) + ga * delta * Tfin;
-                gx = gsig * density_dx(x, tr.relu);
-                gz0 = g0 * wt * c0 * (1.0f - c0);
-                gz1 = g1 * wt * c1 * (1.0f - c1);
-                gz2 = g2 * wt * c2 * (1.0f - c2);
-                // dL/dgamma through every h_k = g_nl(gamma) Y_k
-                const float ggam = gz0 * q0 + gz1 * q1 + gz2 * q2;
-                const float sg = sigmoid_f(y);
-                gy = ggam * kPi * sg * (1.0f - sg);
-                has = true;
-                Tr = Tn;
-                ++ns;
-                finish = ns >= ns_fwd;
-            }
-            if (finish) alive = false;
-        }
-        if (rec.head) {
-            // records: this iteration's samples take consecutive records in lane
-            // order; their leaf rows and basis gradients are summed per leaf later
-            const uint64_t hm = __ballot(has);
-            const int n_has = __popcll(hm);
-            const int at = n_has > 0 ? take_items(rec.counter, rec.cap, n_has, wrec, wend) : -1;
-            if (at >= 0) {
-                const RecordRun run = record_run(hm, has, leaf);
-                if (has) {
-                    my_rec = (int)(at + lane_rank(hm));
-                    rec.rec[2 * (int64_t)my_rec] =
-                        make_int4(__float_as_int(gz0), __float_as_int(gz1), __float_as_int(gz2), __float_as_int(gx));
-                    const int nxt = run.count > 0 ? atomicExch(rec.head + leaf, my_rec + run.count - 1) : my_rec - 1;
-                    rec.rec[2 * (int64_t)my_rec + 1] = make_int4(nxt, (int)ray, __float_as_int(gy), 0);
-                }
-            }
-        }
-        // samples without a record: basis gradients and the atomic row scatter
-        has = has && my_rec < 0;
-        if constexpr (REPLAY) {
-            if (has) {
-                // the sample's basis h, for the scatter below (Eq. 2-4, 6)
-                float g[6], dg[6], h[K], sn, cs;
-                sincosf(kPi * sigmoid_f(y), &sn, &cs);
-                radial_n2(sn, cs, g, dg);
-                hh14(g, Y, h);
-#pragma unroll
-                for (int k = 0; k < K; ++k) s_h[threadIdx.x * K + k] = h[k];
-            }
-        }
-        uint64_t m = __ballot(has);
-        if (common_t && m) {
-            // basis gradients of this step: sum over the wavefront's samples of
-            // gx wsig_c and gy wgam_c (butterfly), lane c keeping component c;
-            // the weights are read again here (from cache) rather than held
-            float sv[C], gv[CG];
-            if (has) {
-                load_leaf<DT, C>(tr.wsig, N, leaf, tr.layout, sv);
-                load_leaf<DT, CG>(tr.wgam, N, leaf, tr.layout, gv);
-            } else {
-#pragma unroll
-                for (int c = 0; c < C; ++c) sv[c] = 0.0f;
-#pragma unroll
-                for (int c = 0; c < CG; ++c) gv[c] = 0.0f;
-            }
-#pragma unroll
-            for (int c = 0; c < C; ++c) {
-                float v = gx * sv[c];
-#pragma unroll
-                for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-                if (lane == c) bacc[0] += v;
-            }
-#pragma unroll
-            for (int c = 0; c < CG; ++c) {
-                float v = gy * gv[c];
-#pragma unroll
-                for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-                if (lane == c) bacc[1] += v;
-            }
-        }
-        __builtin_amdgcn_wave_barrier();
-        while (m) {
-            const int src = __builtin_ctzll(m);
-            m &= m - 1;
-            const int L = __builtin_amdgcn_readlane(leaf, src);
-            const float a0 = readlane_f(gz0, src), a1 = readlane_f(gz1, src), a2 = readlane_f(gz2, src);
-            const float ax = readlane_f(gx, src), ay = readlane_f(gy, src);
-            int i0 = 0, i1 = 0;
-            float f = 0.0f;
-            if (!common_t) {
-                i0 = __builtin_amdgcn_readlane(rs.i0, src);
-                i1 = __builtin_amdgcn_readlane(rs.i1, src);
-                f = readlane_f(rs.f, src);
-            }
-            float* row = io.grad_leaf + (int64_t)L * ROW;
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const int c = pp_component(j, lane);
-                if (c < 3 * K) {
-                    const int ch = c / K;
-                    const float gzc = ch == 0 ? a0 : (ch == 1 ? a1 : a2);
-                    unsafeAtomicAdd(row + c, gzc * s_h[(wbase + src) * K + (c - ch * K)]);
-                } else if (c < 3 * K + C + CG) {
-                    const bool dens = c < 3 * K + C;
-                    const int e = dens ? c - 3 * K : c - 3 * K - C;
-                    const float gsrc = dens ? ax : ay;
-                    const float* B = dens ? tr.basis : tr.basis_g;
-                    const int R = dens ? C : CG;
-                    const float be = common_t ? (dens ? s_brow[e] : s_bgrow[e])
-                                              : (1.0f - f) * B[(int64_t)i0 * R + e] + f * B[(int64_t)i1 * R + e];
-                    unsafeAtomicAdd(row + c, gsrc * be);
-                    float* gB = dens ? io.grad_basis : io.grad_basis_g;
-                    if (!common_t && gB) {
-                        // a time per ray: this sample's rows of the basis gradient
-                        const float wl = dens ? leaf_elem<DT, C>(tr.wsig, N, L, e, tr.layout)
-                                              : leaf_elem<DT, CG>(tr.wgam, N, L, e, tr.layout);
-                        const float v = gsrc * wl;
-                        unsafeAtomicAdd(gB + (int64_t)i0 * R + e, (1.0f - f) * v);
-                        if (f != 0.0f) unsafeAtomicAdd(gB + (int64_t)i1 * R + e, f * v);
+            if (rec.head) {
+                // records: this iteration's samples take consecutive records in lane
+                // order; their leaf rows and basis gradients are summed per leaf later
+                const uint64_t hm = __ballot(has);
+                const int n_has = __popcll(hm);
+                const int at = n_has > 0 ? take_items(rec.counter, rec.cap, n_has, wrec, wend) : -1;
+                if (at >= 0) {
+                    const RecordRun run = record_run(hm, has, leaf);
+                    if (has) {
+                        my_rec = (int)(at + lane_rank(hm));
+                        rec.rec[2 * (int64_t)my_rec] =
+                            make_int4(__float_as_int(gz0), __float_as_int(gz1), __float_as_int(gz2), __float_as_int(gx));
+                        const int nxt = run.count > 0 ? atomicExch(rec.head + leaf, my_rec + run.count - 1) : my_rec - 1;
+                        rec.rec[2 * (int64_t)my_rec + 1] = make_int4(nxt, (int)ray, __float_as_int(gy), 0);
                     }
                 }
             }
-        }
+            // samples without a record: basis gradients and the atomic row scatter
+            has = has && my_rec < 0;
+            if constexpr (REPLAY) {
+                if (has) {
+                    // the sample's basis h, for the scatter below (Eq. 2-4, 6)
+                    float g[6], dg[6], h[K], sn, cs;
+                    sincosf(kPi * sigmoid_f(y), &sn, &cs);
+                    radial_n2(sn, cs, g, dg);
+                    hh14(g, Y, h);
+#pragma unroll
+                    for (int k = 0; k < K; ++k) s_h[threadIdx.x * K + k] = h[k];
+                }
+            }
+            uint64_t m = __ballot(has);
+            if (common_t && m) {
+                // basis gradients of this step: sum over the wavefront's samples of
+                // gx wsig_c and gy wgam_c (butterfly), lane c keeping component c;
+                // the weights are read again here (from cache) rather than held
+                float sv[C], gv[CG];
+                if (has) {
+                    load_leaf<DT, C>(tr.wsig, N, leaf, tr.layout, sv);
+                    load_leaf<DT, CG>(tr.wgam, N, leaf, tr.layout, gv);
+                } else {
+#pragma unroll
+                    for (int c = 0; c < C; ++c) sv[c] = 0.0f;
+#pragma unroll
+                    for (int c = 0; c < CG; ++c) gv[c] = 0.0f;
+                }
+#pragma unroll
+                for (int c = 0; c < C; ++c) {
+                    float v = gx * sv[c];
+#pragma unroll
+                    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+                    if (lane == c) bacc[0] += v;
+                }
+#pragma unroll
+                for (int c = 0; c < CG; ++c) {
+                    float v = gy * gv[c];
+#pragma unroll
+                    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+                    if (lane == c) bacc[1] += v;
+                }
+            }
+            __builtin_amdgcn_wave_barrier();
+            while (m) {
+                const int src = __builtin_ctzll(m);
+                m &= m - 1;
+                const int L = __builtin_amdgcn_readlane(leaf, src);
+                const float a0 = readlane_f(gz0, src), a1 = readlane_f(gz1, src), a2 = readlane_f(gz2, src);
+                const float ax = readlane_f(gx, src), ay = readlane_f(gy, src);
+                int i0 = 0, i1 = 0;
+                float f = 0.0f;
+                if (!common_t) {
+                    i0 = __builtin_amdgcn_readlane(rs.i0, src);
+                    i1 = __builtin_amdgcn_readlane(rs.i1, src);
+                    f = readlane_f(rs.f, src);
+                }
+                float* row = io.grad_leaf + (int64_t)L * ROW;
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    const int c = pp_component(j, lane);
+                    if (c < 3 * K) {
+                        const int ch = c / K;
+                        const float gzc = ch == 0 ? a0 : (ch == 1 ? a1 : a2);
+                        unsafeAtomicAdd(row + c, gzc * s_h[(wbase + src) * K + (c - ch * K)]);
+                    } else if (c < 3 * K + C + CG) {
+                        const bool dens = c < 3 * K + C;
+                        const int e = dens ? c - 3 * K : c - 3 * K - C;
+                        const float gsrc = dens ? ax : ay;
+                        const float* B = dens ? tr.basis : tr.basis_g;
+                        const int R = dens ? C : CG;
+                        const float be = common_t ? (dens ? s_brow[e] : s_bgrow[e])
+                                                  : (1.0f - f) * B[(int64_t)i0 * R + e] + f * B[(int64_t)i1 * R + e];
+                        unsafeAtomicAdd(row + c, gsrc * be);
+                        float* gB = dens ? io.grad_basis : io.grad_basis_g;
+                        if (!common_t && gB) {
+                            // a time per ray: this sample's rows of the basis gradient
+                            const float wl = dens ? leaf_elem<DT, C>(tr.wsig, N, L, e, tr.layout)
+                                                  : leaf_elem<DT, CG>(tr.wgam, N, L, e, tr.layout);
+                            const float v = gsrc * wl;
+                            unsafeAtomicAdd(gB + (int64_t)i0 * R + e, (1.0f - f) * v);
+                            if (f != 0.0f) unsafeAtomicAdd(gB + (int64_t)i1 * R + e, f * v);
+                        }
+                    }
+                }
+            }
+        } while (__popcll(__ballot(!alive)) < limit);
     }
     // one shared time: sum the wavefronts' components over the block, then
     // spread them over the two interpolated rows
@@ -623,9 +630,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) 
     int wrec = 0, wend = 0;    // what is left of the wavefront's block of records (wave-uniform)
 
     for (;;) {
-        const uint64_t idle = __ballot(!alive);
-        const int n_idle = __popcll(idle);
-        if (more && (n_idle >= ra.refill_min || n_idle == kWave)) {
+        for (;;) {   // refill, until too few lanes are idle or no rays are left
+            const uint64_t idle = __ballot(!alive);
+            const int n_idle = __popcll(idle);
+            if (!more || n_idle < ra.refill_min) break;
             // idle lanes take the next rays (the list holds only rays with a trace)
             if (cc.pos == kWave && !next_chunk(ra, cc)) {
                 more = false;
@@ -655,103 +663,105 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) 
                 }
             }
             cc.pos += take;
-            continue;
         }
-        if (n_idle == kWave) break;
-        bool has = false;
-        int leaf = -1, my_rec = -1;
-        float gz0 = 0.0f, gz1 = 0.0f, gz2 = 0.0f, gx = 0.0f, gy = 0.0f, y = 0.0f;
-        if (alive) {
-            const int4 A = nA, B = nB, Q = nQ;
-            if (B.w >= 0) {
-                const int4* e = io.trace.smp + kPPTraceInt4 * (int64_t)B.w;
-                nA = e[0];
-                nB = e[1];
-                nQ = e[2];
+        if (!__ballot(alive)) break;
+        const int limit = more ? ra.refill_min : kWave;   // idle lanes that end the inner loop
+        do {
+            bool has = false;
+            int leaf = -1, my_rec = -1;
+            float gz0 = 0.0f, gz1 = 0.0f, gz2 = 0.0f, gx = 0.0f, gy = 0.0f, y = 0.0f;
+            if (alive) {
+                const int4 A = nA, B = nB, Q = nQ;
+                if (B.w >= 0) {
+                    const int4* e = io.trace.smp + kPPTraceInt4 * (int64_t)B.w;
+                    nA = e[0];
+                    nB = e[1];
+                    nQ = e[2];
+                }
+                leaf = A.x;
+                const float delta = __int_as_float(A.y), x = __int_as_float(A.z);
+                y = __int_as_float(A.w);
+                const float c0 = __int_as_float(B.x), c1 = __int_as_float(B.y), c2 = __int_as_float(B.z);
+                const float sig = density_f(x, tr.relu);
+                const float od = sig * delta;
+                float a, e;
+                absorb(od, a, e);
+                const float wt = Tr * a;
+                const float Tn = Tr * e;
+                p0 = fmaf(wt, c0, p0);
+                p1 = fmaf(wt, c1, p1);
+                p2 = fmaf(wt, c2, p2);
+                const float gdotc = g0 * c0 + g1 * c1 + g2 * c2;
+                const float gsuf = g0 * (F0 - p0) + g1 * (F1 - p1) + g2 * (F2 - p2);
+                const float gsig = delta * (Tn * gdotc - gsuf) + ga * delta * Tfin;
+                gx = gsig * density_dx(x, tr.relu);
+                gz0 = g0 * wt * c0 * (1.0f - c0);
+                gz1 = g1 * wt * c1 * (1.0f - c1);
+                gz2 = g2 * wt * c2 * (1.0f - c2);
+                // dL/dgamma through every h_k = g_nl(gamma) Y_k, from the traced dz/dgamma
+                const float ggam = gz0 * __int_as_float(Q.x) + gz1 * __int_as_float(Q.y) + gz2 * __int_as_float(Q.z);
+                const float sg = sigmoid_f(y);
+                gy = ggam * kPi * sg * (1.0f - sg);
+                has = true;
+                Tr = Tn;
+                if (--left == 0 || B.w < 0) alive = false;
             }
-            leaf = A.x;
-            const float delta = __int_as_float(A.y), x = __int_as_float(A.z);
-            y = __int_as_float(A.w);
-            const float c0 = __int_as_float(B.x), c1 = __int_as_float(B.y), c2 = __int_as_float(B.z);
-            const float sig = density_f(x, tr.relu);
-            const float od = sig * delta;
-            float a, e;
-            absorb(od, a, e);
-            const float wt = Tr * a;
-            const float Tn = Tr * e;
-            p0 = fmaf(wt, c0, p0);
-            p1 = fmaf(wt, c1, p1);
-            p2 = fmaf(wt, c2, p2);
-            const float gdotc = g0 * c0 + g1 * c1 + g2 * c2;
-            const float gsuf = g0 * (F0 - p0) + g1 * (F1 - p1) + g2 * (F2 - p2);
-            const float gsig = delta * (Tn * gdotc - gsuf) + ga * delta * Tfin;
-            gx = gsig * density_dx(x, tr.relu);
-            gz0 = g0 * wt * c0 * (1.0f - c0);
-            gz1 = g1 * wt * c1 * (1.0f - c1);
-            gz2 = g2 * wt * c2 * (1.0f - c2);
-            // dL/dgamma through every h_k = g_nl(gamma) Y_k, from the traced dz/dgamma
-            const float ggam = gz0 * __int_as_float(Q.x) + gz1 * __int_as_float(Q.y) + gz2 * __int_as_float(Q.z);
-            const float sg = sigmoid_f(y);
-            gy = ggam * kPi * sg * (1.0f - sg);
-            has = true;
-            Tr = Tn;
-            if (--left == 0 || B.w < 0) alive = false;
-        }
-        if (rec.head) {
-            const uint64_t hm = __ballot(has);
-            const int at = take_items(rec.counter, rec.cap, __popcll(hm), wrec, wend);
-            if (at >= 0) {
-                const RecordRun run = record_run(hm, has, leaf);
-                if (has) {
-                    my_rec = at + lane_rank(hm);
-                    rec.rec[2 * (int64_t)my_rec] =
-                        make_int4(__float_as_int(gz0), __float_as_int(gz1), __float_as_int(gz2), __float_as_int(gx));
-                    const int nxt = run.count > 0 ? atomicExch(rec.head + leaf, my_rec + run.count - 1) : my_rec - 1;
-                    rec.rec[2 * (int64_t)my_rec + 1] = make_int4(nxt, ray, __float_as_int(gy), 0);
+            if (rec.head) {
+                const uint64_t hm = __ballot(has);
+                const int at = take_items(rec.counter, rec.cap, __popcll(hm), wrec, wend);
+                if (at >= 0) {
+                    const RecordRun run = record_run(hm, has, leaf);
+                    if (has) {
+                        my_rec = at + lane_rank(hm);
+                        rec.rec[2 * (int64_t)my_rec] =
+                            make_int4(__float_as_int(gz0), __float_as_int(gz1), __float_as_int(gz2), __float_as_int(gx));
+                        const int nxt = run.count > 0 ? atomicExch(rec.head + leaf, my_rec + run.count - 1) : my_rec - 1;
+                        rec.rec[2 * (int64_t)my_rec + 1] = make_int4(nxt, ray, __float_as_int(gy), 0);
+                    }
                 }
             }
-        }
-        // samples without a record: their row, one component per lane, and their basis gradients
-        uint64_t m = __ballot(has && my_rec < 0);
-        while (__builtin_expect_with_probability(m != 0, 0, 0.99999)) {
-            const int src = __builtin_ctzll(m);
-            m &= m - 1;
-            __builtin_amdgcn_wave_barrier();
-            if (lane == src) {
-                RaySetup rs;
-                float dmax, Y[8], g[6], dg[6], h[K], sn, cs;
-                const f3v dv = load3(ra.d + 3 * (int64_t)ray);
-                const float d[3] = {dv.x, dv.y, dv.z};
-                ray_direction<IDENT>(in, d, rs, dmax);
-                sh_deg2(rs.dir[0], rs.dir[1], rs.dir[2], Y);
-                sincosf(kPi * sigmoid_f(y), &sn, &cs);
-                radial_n2(sn, cs, g, dg);
-                hh14(g, Y, h);
+            // samples without a record: their row, one component per lane, and their basis gradients
+            uint64_t m = __ballot(has && my_rec < 0);
+            while (__builtin_expect_with_probability(m != 0, 0, 0.99999)) {
+                const int src = __builtin_ctzll(m);
+                m &= m - 1;
+                __builtin_amdgcn_wave_barrier();
+                if (lane == src) {
+                    RaySetup rs;
+                    float dmax, Y[8], g[6], dg[6], h[K], sn, cs;
+                    const f3v dv = load3(ra.d + 3 * (int64_t)ray);
+                    const float d[3] = {dv.x, dv.y, dv.z};
+                    ray_direction<IDENT>(in, d, rs, dmax);
+                    sh_deg2(rs.dir[0], rs.dir[1], rs.dir[2], Y);
+                    sincosf(kPi * sigmoid_f(y), &sn, &cs);
+                    radial_n2(sn, cs, g, dg);
+                    hh14(g, Y, h);
 #pragma unroll
-                for (int k = 0; k < K; ++k) srow[k] = h[k];
-            }
-            __builtin_amdgcn_wave_barrier();
-            const int L = __builtin_amdgcn_readlane(leaf, src);
-            const float a0 = readlane_f(gz0, src), a1 = readlane_f(gz1, src), a2 = readlane_f(gz2, src);
-            const float ax = readlane_f(gx, src), ay = readlane_f(gy, src);
-            float* row = io.grad_leaf + (int64_t)L * ROW;
+                    for (int k = 0; k < K; ++k) srow[k] = h[k];
+                }
+                __builtin_amdgcn_wave_barrier();
+                const int L = __builtin_amdgcn_readlane(leaf, src);
+                const float a0 = readlane_f(gz0, src), a1 = readlane_f(gz1, src), a2 = readlane_f(gz2, src);
+                const float ax = readlane_f(gx, src), ay = readlane_f(gy, src);
+                float* row = io.grad_leaf + (int64_t)L * ROW;
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const int c = pp_component(j, lane);
-                if (c < 3 * K) {
-                    const int ch = c / K;
-                    const float gzc = ch == 0 ? a0 : (ch == 1 ? a1 : a2);
-                    unsafeAtomicAdd(row + c, gzc * srow[c - ch * K]);
-                } else if (c < 3 * K + C + CG) {
-                    const bool dens = c < 3 * K + C;
-                    const int e = dens ? c - 3 * K : c - 3 * K - C;
-                    unsafeAtomicAdd(row + c, dens ? ax * s_brow[e] : ay * s_bgrow[e]);
-                    const float wl = dens ? leaf_elem<DT, C>(tr.wsig, tr.n_leaves, L, e, tr.layout)
-                                          : leaf_elem<DT, CG>(tr.wgam, tr.n_leaves, L, e, tr.layout);
-                    atomicAdd(&s_acc[dens ? e : kWave + e], (dens ? ax : ay) * wl);
+                for (int j = 0; j < 2; ++j) {
+                    const int c = pp_component(j, lane);
+                    if (c < 3 * K) {
+                        const int ch = c / K;
+                        const float gzc = ch == 0 ? a0 : (ch == 1 ? a1 : a2);
+                        unsafeAtomicAdd(row + c, gzc * srow[c - ch * K]);
+                    } else if (c < 3 * K + C + CG) {
+                        const bool dens = c < 3 * K + C;
+                        const int e = dens ? c - 3 * K : c - 3 * K - C;
+                        unsafeAtomicAdd(row + c, dens ? ax * s_brow[e] : ay * s_bgrow[e]);
+                        const float wl = dens ? leaf_elem<DT, C>(tr.wsig, tr.n_leaves, L, e, tr.layout)
+                                              : leaf_elem<DT, CG>(tr.wgam, tr.n_leaves, L, e, tr.layout);
+                        atomicAdd(&s_acc[dens ? e : kWave + e], (dens ? ax : ay) * wl);
+                    }
                 }
             }
-        }
+        } while (__popcll(__ballot(!alive)) < limit);
     }
     // (the basis gradients of samples with records are summed per leaf by the reduction)
     __syncthreads();
