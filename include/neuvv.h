@@ -357,9 +357,8 @@ int neuvv_render_noalloc(const neuvv_tree* tree, const neuvv_instance* inst, int
  * 2^31 - 1 (the environment
  * variable NEUVV_BWD_RECORDS, read at every call, sets it; 0 turns records
  * off); samples beyond it are added per sample in the same call. Records
- * are used with image_width or not, for n_rays and n_leaves below 2^31, and
- * with Cg > 0 only when ray_t is NULL (one time for all rays). Summation
- * order follows the atomics, so results may differ between runs in the last
+ * are used with image_width or not, for n_rays and n_leaves below 2^31.
+ * Summation order follows the atomics, so results may differ between runs in the last
  * bits, as with any atomic accumulation.
  * Arguments as neuvv_render, plus
  * rgb, alpha, nsamp  device forward outputs for the same rays and inputs.

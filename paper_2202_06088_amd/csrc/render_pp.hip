@@ -314,13 +314,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 8))) 
 // Component of lane slot j (0, 1) of the gradient row.
 __device__ __forceinline__ int pp_component(int j, int lane) { return j * kWave + lane; }
 
-// REPLAY (a time per ray; replay_pp_kernel below takes one time for every ray):
-// every ray of the launch has a trace in io.trace (the forward's samples) and
-// replays it without walking the tree or reading the leaf payload: dL/dgamma =
-// sum_ch gz_ch dz_ch/dgamma comes from the traced derivatives, and h is
-// recomputed from y.
-template <int DT, bool IDENT, bool REPLAY>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(REPLAY ? 3 : 2, 8))) void render_pp_bwd_kernel(
+template <int DT, bool IDENT>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 8))) void render_pp_bwd_kernel(
     TreeArgs tr, InstArgs in, RayArgs ra, BackwardIO io, RecordArgs rec) {
     if (no_candidates(ra)) return;
     using namespace pp;
@@ -336,7 +331,6 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(REPLAY ?
     ChunkCursor cc = chunk_cursor();
     bool more = true;
     const int64_t N = tr.n_leaves;
-    int tnext = -1;   // replay: the ray's next sample
     const int lane = threadIdx.x & 63;
     const int wbase = threadIdx.x - lane;
 
@@ -351,7 +345,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(REPLAY ?
     // scalar time: lane c < C holds component c of the density-basis gradient
     // (bacc[0]) and, c < CG, of the hyperangle-basis gradient (bacc[1])
     float bacc[2] = {0.0f, 0.0f};
-    // records (scalar time only): [wrec, wend) is what is left of the
+    // records: [wrec, wend) is what is left of the
     // wavefront's current block of records (wave-uniform)
     int wrec = 0, wend = 0;
 
@@ -386,8 +380,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(REPLAY ?
                 if (!common_t) time_setup(tr, in, ra.t[ray], rs.i0, rs.i1, rs.f);
                 if (rs.hit) {
                     sh_deg2(rs.dir[0], rs.dir[1], rs.dir[2], Y);
-                    if constexpr (REPLAY) tnext = io.trace.head[ray];
-                    else walk_begin(tr, rs, w);
+                    walk_begin(tr, rs, w);
                     ns_fwd = io.nsamp[ray];
                     ns = 0;
                     Tr = 1.0f;
@@ -409,41 +402,21 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(REPLAY ?
             if (alive) {
                 float delta = 0.0f, x = 0.0f, c0 = 0.0f, c1 = 0.0f, c2 = 0.0f, q0 = 0.0f, q1 = 0.0f, q2 = 0.0f;
                 bool finish;
-                if constexpr (REPLAY) {
-                    // replay the forward's sample
-                    if (tnext >= 0) {
-                        const int4* e = io.trace.smp + kPPTraceInt4 * (int64_t)tnext;
-                        const int4 A = e[0], B = e[1], Q = e[2];
-                        leaf = A.x;
-                        delta = __int_as_float(A.y);
-                        x = __int_as_float(A.z);
-                        y = __int_as_float(A.w);
-                        c0 = __int_as_float(B.x);
-                        c1 = __int_as_float(B.y);
-                        c2 = __int_as_float(B.z);
-                        tnext = B.w;
-                        q0 = __int_as_float(Q.x);
-                        q1 = __int_as_float(Q.y);
-                        q2 = __int_as_float(Q.z);
-                    }
-                    finish = leaf < 0;
-                } else {
-                    float umid;
-                    leaf = walk_next<kWalkBudgetBwd>(tr, rs, w, delta, umid);
-                    finish = leaf == -1;
-                    if (leaf >= 0) {
-                        PPSample<DT> p;
-                        pp_load<DT>(tr, leaf, p);
-                        pp_compute<DT>(tr, rs, Y, s_b, s_bg, p);
-                        x = p.x;
-                        y = p.y;
-                        c0 = sigmoid_f(p.z0);
-                        c1 = sigmoid_f(p.z1);
-                        c2 = sigmoid_f(p.z2);
-                        pp_dz_dgamma<DT>(p, Y, q0, q1, q2);
+                float umid;
+                leaf = walk_next<kWalkBudgetBwd>(tr, rs, w, delta, umid);
+                finish = leaf == -1;
+                if (leaf >= 0) {
+                    PPSample<DT> p;
+                    pp_load<DT>(tr, leaf, p);
+                    pp_compute<DT>(tr, rs, Y, s_b, s_bg, p);
+                    x = p.x;
+                    y = p.y;
+                    c0 = sigmoid_f(p.z0);
+                    c1 = sigmoid_f(p.z1);
+                    c2 = sigmoid_f(p.z2);
+                    pp_dz_dgamma<DT>(p, Y, q0, q1, q2);
 #pragma unroll
-                        for (int k = 0; k < K; ++k) s_h[threadIdx.x * K + k] = p.h[k];
-                    }
+                    for (int k = 0; k < K; ++k) s_h[threadIdx.x * K + k] = p.h[k];
                 }
                 if (leaf >= 0) {
                     const float sig = density_f(x, tr.relu);
@@ -486,23 +459,12 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(REPLAY ?
                         rec.rec[2 * (int64_t)my_rec] =
                             make_int4(__float_as_int(gz0), __float_as_int(gz1), __float_as_int(gz2), __float_as_int(gx));
                         const int nxt = run.count > 0 ? atomicExch(rec.head + leaf, my_rec + run.count - 1) : my_rec - 1;
-                        rec.rec[2 * (int64_t)my_rec + 1] = make_int4(nxt, (int)ray, __float_as_int(gy), 0);
+                        rec.rec[2 * (int64_t)my_rec + 1] = make_int4(nxt, (int)ray, __float_as_int(gy), __float_as_int(y));
                     }
                 }
             }
             // samples without a record: basis gradients and the atomic row scatter
             has = has && my_rec < 0;
-            if constexpr (REPLAY) {
-                if (has) {
-                    // the sample's basis h, for the scatter below (Eq. 2-4, 6)
-                    float g[6], dg[6], h[K], sn, cs;
-                    sincosf(kPi * sigmoid_f(y), &sn, &cs);
-                    radial_n2(sn, cs, g, dg);
-                    hh14(g, Y, h);
-#pragma unroll
-                    for (int k = 0; k < K; ++k) s_h[threadIdx.x * K + k] = h[k];
-                }
-            }
             uint64_t m = __ballot(has);
             if (common_t && m) {
                 // basis gradients of this step: sum over the wavefront's samples of
@@ -601,11 +563,11 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(REPLAY ?
     }
 }
 
-// The adjoint of rays with a trace and one time for every ray, as
-// replay_bwd_kernel of the global form: only what a sample with a record
+// The adjoint of rays with a trace, as replay_bwd_kernel of the global form: only what a sample with a record
 // needs, the ray's next entry on its way while one is replayed, and the basis
 // of a sample without a record made when it is scattered.
-template <int DT, bool IDENT>
+// PER_T: a time per ray.
+template <int DT, bool IDENT, bool PER_T>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) void replay_pp_kernel(
     TreeArgs tr, InstArgs in, RayArgs ra, BackwardIO io, RecordArgs rec) {
     if (no_candidates(ra)) return;
@@ -613,7 +575,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) 
     __shared__ float s_row[kBlock / kWave][K];   // basis h of the sample being scattered
     __shared__ float s_brow[C], s_bgrow[CG];
     __shared__ float s_acc[2 * kWave];           // block sum of the basis gradients of scattered samples
-    stage_common_rows(tr, in, ra.t_scalar, s_brow, s_bgrow);
+    if constexpr (!PER_T) stage_common_rows(tr, in, ra.t_scalar, s_brow, s_bgrow);
     if (threadIdx.x < 2 * kWave) s_acc[threadIdx.x] = 0.0f;
     __syncthreads();
     ChunkCursor cc = chunk_cursor();
@@ -716,7 +678,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) 
                         rec.rec[2 * (int64_t)my_rec] =
                             make_int4(__float_as_int(gz0), __float_as_int(gz1), __float_as_int(gz2), __float_as_int(gx));
                         const int nxt = run.count > 0 ? atomicExch(rec.head + leaf, my_rec + run.count - 1) : my_rec - 1;
-                        rec.rec[2 * (int64_t)my_rec + 1] = make_int4(nxt, ray, __float_as_int(gy), 0);
+                        rec.rec[2 * (int64_t)my_rec + 1] = make_int4(nxt, ray, __float_as_int(gy), __float_as_int(y));
                     }
                 }
             }
@@ -726,6 +688,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) 
                 const int src = __builtin_ctzll(m);
                 m &= m - 1;
                 __builtin_amdgcn_wave_barrier();
+                int i0 = 0, i1 = 0;   // PER_T: the frames of the source ray
+                float f = 0.0f;
+                if constexpr (PER_T) time_setup(tr, in, ra.t[__builtin_amdgcn_readlane(ray, src)], i0, i1, f);
                 if (lane == src) {
                     RaySetup rs;
                     float dmax, Y[8], g[6], dg[6], h[K], sn, cs;
@@ -754,15 +719,28 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) 
                     } else if (c < 3 * K + C + CG) {
                         const bool dens = c < 3 * K + C;
                         const int e = dens ? c - 3 * K : c - 3 * K - C;
-                        unsafeAtomicAdd(row + c, dens ? ax * s_brow[e] : ay * s_bgrow[e]);
+                        const float gs = dens ? ax : ay;
                         const float wl = dens ? leaf_elem<DT, C>(tr.wsig, tr.n_leaves, L, e, tr.layout)
                                               : leaf_elem<DT, CG>(tr.wgam, tr.n_leaves, L, e, tr.layout);
-                        atomicAdd(&s_acc[dens ? e : kWave + e], (dens ? ax : ay) * wl);
+                        if constexpr (PER_T) {
+                            const float* B = dens ? tr.basis : tr.basis_g;
+                            float* gB = dens ? io.grad_basis : io.grad_basis_g;
+                            const int64_t r0 = (int64_t)i0 * (dens ? C : CG) + e, r1 = (int64_t)i1 * (dens ? C : CG) + e;
+                            unsafeAtomicAdd(row + c, gs * ((1.0f - f) * B[r0] + f * B[r1]));
+                            if (gB) {
+                                unsafeAtomicAdd(gB + r0, (1.0f - f) * (gs * wl));
+                                if (f != 0.0f) unsafeAtomicAdd(gB + r1, f * (gs * wl));
+                            }
+                        } else {
+                            unsafeAtomicAdd(row + c, gs * (dens ? s_brow[e] : s_bgrow[e]));
+                            atomicAdd(&s_acc[dens ? e : kWave + e], gs * wl);
+                        }
                     }
                 }
             }
         } while (__popcll(__ballot(!alive)) < limit);
     }
+    if constexpr (PER_T) return;
     // (the basis gradients of samples with records are summed per leaf by the reduction)
     __syncthreads();
     const int c = threadIdx.x;
@@ -932,6 +910,98 @@ __global__ __launch_bounds__(kBlock) void reduce_pp_records_kernel(TreeArgs tr, 
     }
 }
 
+// The same with a time per ray. Records of one leaf then share neither gamma
+// nor the basis rows, so a wavefront takes a leaf, a lane one or two components
+// of its row (component c of slot j as in the scatter), and the list is followed
+// by all lanes together: a record's basis, frames and weights are the same for
+// every lane, its basis rows one coalesced read per frame. The density and
+// hyperangle components also add the record's share of the basis gradients.
+// Bound by latency: three dependent reads per record (the record, its ray, the
+// basis rows). Without records such samples took the per-sample scatter, whose
+// reads are as many but one lane's after the other's: 15,360 rays of 31,484
+// samples took 3.6 ms.
+template <int DT, bool IDENT>
+__global__ __launch_bounds__(kBlock) void reduce_pp_timed_kernel(TreeArgs tr, InstArgs in, RayArgs ra, RecordArgs rec,
+                                                                 BackwardIO io) {
+    using namespace pp;
+    __shared__ float s_h[kBlock / kWave][K];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int64_t N = tr.n_leaves, n_waves = (int64_t)gridDim.x * (kBlock / kWave);
+    for (int64_t b = (int64_t)blockIdx.x * (kBlock / kWave) + wv; b * kWave < N; b += n_waves) {
+        const int64_t own = b * kWave + lane;
+        const int first = own < N ? rec.head[own] : -1;
+        for (uint64_t m = __ballot(first >= 0); m; m &= m - 1) {
+            const int src = __builtin_ctzll(m);
+            const int64_t L = b * kWave + src;
+            int r = __builtin_amdgcn_readlane(first, src);
+            float wl[2] = {0.0f, 0.0f}, acc[2] = {0.0f, 0.0f};   // the component's weight, its sum
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const int c = pp_component(j, lane);
+                if (c >= 3 * K && c < 3 * K + C) wl[j] = leaf_elem<DT, C>(tr.wsig, N, L, c - 3 * K, tr.layout);
+                else if (c >= 3 * K + C && c < 3 * K + C + CG) wl[j] = leaf_elem<DT, CG>(tr.wgam, N, L, c - 3 * K - C, tr.layout);
+            }
+            int4 A = rec.rec[2 * (int64_t)r], B = rec.rec[2 * (int64_t)r + 1];
+            for (;;) {
+                const int nxt = B.x;
+                int4 nA = A, nB = B;
+                if (nxt >= 0) {
+                    nA = rec.rec[2 * (int64_t)nxt];
+                    nB = rec.rec[2 * (int64_t)nxt + 1];
+                }
+                const f3v dv = load3(ra.d + 3 * (int64_t)B.y);
+                const float d[3] = {dv.x, dv.y, dv.z};
+                RaySetup rs;
+                float dmax, Y[8], g[6], dg[6], h[K], sn, cs;
+                time_setup(tr, in, ra.t[B.y], rs.i0, rs.i1, rs.f);
+                ray_direction<IDENT>(in, d, rs, dmax);
+                sh_deg2(rs.dir[0], rs.dir[1], rs.dir[2], Y);
+                sincosf(kPi * sigmoid_f(__int_as_float(B.w)), &sn, &cs);
+                radial_n2(sn, cs, g, dg);
+                hh14(g, Y, h);
+                __builtin_amdgcn_wave_barrier();
+                if (lane == 0) {
+#pragma unroll
+                    for (int k = 0; k < K; ++k) s_h[wv][k] = h[k];
+                }
+                __builtin_amdgcn_wave_barrier();
+                const float gx = __int_as_float(A.w), gy = __int_as_float(B.z);
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    const int c = pp_component(j, lane);
+                    if (c < 3 * K) {
+                        const int ch = c / K;
+                        const float gz = __int_as_float(ch == 0 ? A.x : (ch == 1 ? A.y : A.z));
+                        acc[j] = fmaf(gz, s_h[wv][c - ch * K], acc[j]);
+                    } else if (c < 3 * K + C + CG) {
+                        const bool dens = c < 3 * K + C;
+                        const int e = dens ? c - 3 * K : c - 3 * K - C, R = dens ? C : CG;
+                        const float gs = dens ? gx : gy;
+                        const float* T = dens ? tr.basis : tr.basis_g;
+                        float* gB = dens ? io.grad_basis : io.grad_basis_g;
+                        const int64_t r0 = (int64_t)rs.i0 * R + e, r1 = (int64_t)rs.i1 * R + e;
+                        acc[j] = fmaf(gs, (1.0f - rs.f) * T[r0] + rs.f * T[r1], acc[j]);
+                        if (gB) {
+                            const float v = gs * wl[j];
+                            unsafeAtomicAdd(gB + r0, (1.0f - rs.f) * v);
+                            if (rs.f != 0.0f) unsafeAtomicAdd(gB + r1, rs.f * v);
+                        }
+                    }
+                }
+                if (nxt < 0) break;
+                A = nA;
+                B = nB;
+            }
+            float* row = io.grad_leaf + L * ROW;
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const int c = pp_component(j, lane);
+                if (c < 3 * K + C + CG) unsafeAtomicAdd(row + c, acc[j]);
+            }
+        }
+    }
+}
+
 // ----------------------------------------------------------------------------
 // launchers
 
@@ -954,11 +1024,19 @@ static hipError_t pp_fwd_t(const TreeArgs& tr, const InstArgs& in, const RayArgs
     return o.trace.head ? pp_fwd_e<DT, true>(tr, in, ra, t_stop, o, st) : pp_fwd_e<DT, false>(tr, in, ra, t_stop, o, st);
 }
 
-template <int DT, bool REPLAY>
-static hipError_t pp_bwd_k(const TreeArgs& tr, const InstArgs& in, const RayArgs& ra, const BackwardIO& io,
-                           const RecordArgs& rec, hipStream_t st) {
-    auto kern = REPLAY && !ra.t ? (in.identity ? replay_pp_kernel<DT, true> : replay_pp_kernel<DT, false>)
-                                : (in.identity ? render_pp_bwd_kernel<DT, true, REPLAY> : render_pp_bwd_kernel<DT, false, REPLAY>);
+template <int DT>
+static hipError_t pp_bwd_walk(const TreeArgs& tr, const InstArgs& in, const RayArgs& ra, const BackwardIO& io,
+                              const RecordArgs& rec, hipStream_t st) {
+    auto kern = in.identity ? render_pp_bwd_kernel<DT, true> : render_pp_bwd_kernel<DT, false>;
+    hipLaunchKernelGGL(kern, dim3(grid_for(kern, ra)), dim3(kBlock), 0, st, tr, in, ra, io, rec);
+    return hipGetLastError();
+}
+
+template <int DT>
+static hipError_t pp_bwd_replay(const TreeArgs& tr, const InstArgs& in, const RayArgs& ra, const BackwardIO& io,
+                                const RecordArgs& rec, hipStream_t st) {
+    auto kern = ra.t ? (in.identity ? replay_pp_kernel<DT, true, true> : replay_pp_kernel<DT, false, true>)
+                     : (in.identity ? replay_pp_kernel<DT, true, false> : replay_pp_kernel<DT, false, false>);
     hipLaunchKernelGGL(kern, dim3(grid_for(kern, ra)), dim3(kBlock), 0, st, tr, in, ra, io, rec);
     return hipGetLastError();
 }
@@ -966,26 +1044,20 @@ static hipError_t pp_bwd_k(const TreeArgs& tr, const InstArgs& in, const RayArgs
 template <int DT>
 static hipError_t pp_bwd_t(const TreeArgs& tr, const InstArgs& in, const RayArgs& ra, const BackwardIO& io,
                            hipStream_t st) {
-    // records with one time for every ray (the per-leaf sums rely on it)
-    const int64_t cap = ra.t == nullptr && ra.n <= (int64_t)INT32_MAX && tr.n_leaves > 0 &&
-                                tr.n_leaves <= (int64_t)INT32_MAX
-                            ? io.record_cap
-                            : 0;
+    const int64_t cap =
+        ra.n <= (int64_t)INT32_MAX && tr.n_leaves > 0 && tr.n_leaves <= (int64_t)INT32_MAX ? io.record_cap : 0;
     AdjointScratch sc;
     hipError_t e = adjoint_begin(tr, ra, io.nsamp, io.trace.head, cap, st, sc);
     const RecordArgs& rec = sc.rec;
-    if (e == hipSuccess) e = pp_bwd_k<DT, false>(tr, in, sc.walk, io, rec, st);
-    if (e == hipSuccess && io.trace.head) e = pp_bwd_k<DT, true>(tr, in, sc.replay, io, rec, st);
+    if (e == hipSuccess) e = pp_bwd_walk<DT>(tr, in, sc.walk, io, rec, st);
+    if (e == hipSuccess && io.trace.head) e = pp_bwd_replay<DT>(tr, in, sc.replay, io, rec, st);
     if (e == hipSuccess && cap > 0) {
         int64_t blocks = (tr.n_leaves + kBlock - 1) / kBlock;
-        const int64_t lim = (int64_t)device_cu_count() * 4;
+        const int64_t lim = (int64_t)device_cu_count() * (ra.t ? 8 : 4);
         if (blocks > lim) blocks = lim;
-        if (in.identity)
-            hipLaunchKernelGGL((reduce_pp_records_kernel<DT, true>), dim3((unsigned)blocks), dim3(kBlock), 0, st, tr,
-                               in, ra, rec, io);
-        else
-            hipLaunchKernelGGL((reduce_pp_records_kernel<DT, false>), dim3((unsigned)blocks), dim3(kBlock), 0, st,
-                               tr, in, ra, rec, io);
+        auto kern = ra.t ? (in.identity ? reduce_pp_timed_kernel<DT, true> : reduce_pp_timed_kernel<DT, false>)
+                         : (in.identity ? reduce_pp_records_kernel<DT, true> : reduce_pp_records_kernel<DT, false>);
+        hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(kBlock), 0, st, tr, in, ra, rec, io);
         e = hipGetLastError();
     }
     return adjoint_end(sc, e, st);

@@ -9,7 +9,7 @@ import torch
 from gpu_util import announce, oracle_render, rel_err, stop_ambiguous, tdev, tiny_camera, upload
 from oracle import core as OC
 from paper_2202_06088_amd import _lib, ops
-from workloads import make_scene, scene_for_workload
+from workloads import make_scene_per_point, scene_for_workload
 
 pytestmark = pytest.mark.gpu
 
@@ -76,3 +76,32 @@ def test_unpack_grad_rows_edges(n, K, C, Cg, layout):
         if layout == _lib.LAYOUT_VEC_SOA:
             want = want.view(n, -1, 4).permute(1, 0, 2)
         assert torch.equal(got, want.reshape(-1))
+
+
+@pytest.mark.parametrize("records", [None, "1", "300"])
+@pytest.mark.parametrize("cap", [0, 300, None])
+def test_per_point_timed_reduction(cap, records, monkeypatch):
+    """Per-point leaves with a time per ray: traced, partly traced and walked rays, with room for every record, for
+    some and for one, on a tree whose leaf count is no multiple of a batch; against the oracle."""
+    if records is None:
+        monkeypatch.delenv("NEUVV_BWD_RECORDS", raising=False)
+    else:
+        monkeypatch.setenv("NEUVV_BWD_RECORDS", records)
+    sc = make_scene_per_point(5, 3000, "random", T=12, seed=7)
+    cam = tiny_camera(sc)
+    o, d = OC.pinhole_rays(64, 64, cam.intr(), cam.c2w)
+    n, rng = o.shape[0], np.random.default_rng(71)
+    t = rng.uniform(0, sc.T - 1, n).astype(np.float32)
+    g = rng.normal(size=(n, 3)).astype(np.float32)
+    g[stop_ambiguous(oracle_render(sc, o, d, t, 0.0, 1e-4, g_rgb=g), label="per-point timed")] = 0.0
+    ref = oracle_render(sc, o, d, t, 0.0, 1e-4, g_rgb=g)
+    tree, oo, dd, tt = upload(sc), tdev(o), tdev(d), tdev(t)
+    trace = ops.Trace(n, 32 * n if cap is None else cap, oo.device)
+    rgb, alpha, _, nsamp = ops.render(tree, oo, dd, tt, None, 1e-4, 64, trace=trace)
+    out = ops.render_backward(tree, oo, dd, rgb, alpha, nsamp, tdev(g), None, tt, None, 1e-4, 64, trace=trace)
+    torch.cuda.synchronize()
+    hh, ws, wg = tree.unpack_grad(out[0])
+    got = dict(grad_hh=hh, grad_wsig=ws, grad_wgam=wg, grad_basis=out[1], grad_basis_g=out[2])
+    e = {k: rel_err(v.cpu().numpy(), ref[k]) for k, v in got.items()}
+    announce(f"per-point timed cap={cap} records={records}: grad rel errors {e}")
+    assert int(nsamp.sum()) > 1000 and max(e.values()) <= 1e-4, e
