@@ -20,10 +20,11 @@
  *     the adjoints also take the records of their two-phase reduction (4
  *     bytes per leaf plus 32 bytes per record of room, see there), and
  *     neuvv_render_multi the segment lists of its instances (see there). Scratch
- *     is taken in stream order on the call's stream from a memory pool the
- *     library keeps per device (it keeps freed memory for later calls) and
- *     freed in stream order after the kernels; each call has its own, so
- *     calls on different streams do not interfere.
+ *     is taken in stream order on the call's stream, from blocks the library
+ *     keeps for that stream (scratch up to 64 MiB; see neuvv_release_scratch)
+ *     or from a memory pool it keeps per device (which keeps freed memory for
+ *     later calls), and freed in stream order after the kernels; each call has
+ *     its own, so calls on different streams do not interfere.
  *   - "stream" is a hipStream_t (NULL = the null stream). GPU work is queued
  *     on it asynchronously; the caller synchronises. Argument errors are
  *     detected on the host before anything is queued.
@@ -571,6 +572,16 @@ int neuvv_blur(int32_t height, int32_t width, const float* in, float sigma, floa
  */
 int neuvv_shade(const neuvv_light* light, const float* shadow_map, int64_t n, const float* ray_o, const float* ray_d,
                 const float* rgb, const float* alpha, const float* depth, float* out_rgb, void* stream);
+
+/*
+ * neuvv_release_scratch - frees the scratch the library keeps on the current
+ * device between calls (at most 32 blocks and 256 MiB, each kept for the
+ * stream that last used it): waits for the calls that used it and returns it
+ * to the pool. Scratch of calls that run in other threads meanwhile is left
+ * alone. Not to be called while a stream of the device is captured.
+ * Errors: HIP.
+ */
+int neuvv_release_scratch(void);
 
 /* Library ABI version (major * 100 + minor). */
 int neuvv_version(void);

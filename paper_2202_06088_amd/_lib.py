@@ -74,6 +74,7 @@ _SIGNATURES = {
     "neuvv_grad_row_elems": [_I32, _I32, _I32],
     "neuvv_pack_rows": [_I32, _I32, _I32, _I64, _P, _P, _P, _P],
     "neuvv_unpack_grad_rows": [_I32, _I32, _I32, _I32, _I64, _P, _P, _P, _P, _P],
+    "neuvv_release_scratch": [],
     "neuvv_blur": [_I32, _I32, _P, _F, _P, _P],
     "neuvv_find_terminal_leaves": [ctypes.POINTER(neuvv_tree), ctypes.POINTER(neuvv_instance), _I64, _P, _P, _P, _F,
                                    _I32, _F, _P, _P],
@@ -187,6 +188,10 @@ def neuvv_pack_leaves(K, C, dtype, layout, n_leaves, hh_in, wsig_in, slot_of_inp
 def neuvv_pack_rows(R, dtype, layout, n_leaves, rows_in, slot_of_input, out, stream=None):
     _check("neuvv_pack_rows", load().neuvv_pack_rows(int(R), int(dtype), int(layout), int(n_leaves), _ptr(rows_in),
                                                      _ptr(slot_of_input), _ptr(out), _stream(stream)))
+
+
+def neuvv_release_scratch():
+    _check("neuvv_release_scratch", load().neuvv_release_scratch())
 
 
 def neuvv_unpack_grad_rows(K, C, Cg, layout, n_leaves, grad_leaf, hh_out, wsig_out, wgam_out=None, stream=None):

@@ -196,6 +196,12 @@ neuvv::TreeArgs tree_args(const neuvv_tree* t) {
 
 extern "C" {
 
+int neuvv_release_scratch(void) {
+    NEUVV_GUARD_BEGIN
+    return hip_status(neuvv::release_kept(), "releasing the kept scratch");
+    NEUVV_GUARD_END
+}
+
 int neuvv_version(void) { return 200; }
 
 const char* neuvv_last_error(void) { return g_err.c_str(); }

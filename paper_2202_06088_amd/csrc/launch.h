@@ -150,10 +150,13 @@ constexpr size_t kFixedScratchBytes = kListHeaderBytes + (size_t)kFixedScratchSl
 // device; the array's host-side name is not a device address).
 hipError_t fixed_scratch(void** p);
 
-// Stream-ordered scratch of a launch (work-queue counters, candidate lists):
-// taken from a memory pool the library keeps per device, which holds on to
-// its memory between calls instead of returning it at every synchronisation.
+// Stream-ordered scratch of a call (work-queue counters, candidate lists,
+// records): from the blocks kept for its stream when it is small, else from a
+// memory pool the library keeps per device, which holds on to its memory
+// between calls instead of returning it at every synchronisation.
+// release_kept frees the kept blocks of the current device that no call holds.
 hipError_t work_alloc(void** p, size_t bytes, hipStream_t stream);
 hipError_t work_free(void* p, hipStream_t stream);
+hipError_t release_kept();
 
 }  // namespace neuvv

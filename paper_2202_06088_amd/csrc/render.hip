@@ -32,10 +32,7 @@ hipMemPool_t g_pool[64] = {};
 bool g_pool_tried[64] = {};
 }  // namespace
 
-hipError_t work_alloc(void** p, size_t bytes, hipStream_t stream) {
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess) return e;
+static hipError_t pool_alloc(void** p, size_t bytes, int dev, hipStream_t stream) {
     hipMemPool_t pool = nullptr;
     if (dev >= 0 && dev < 64) {
         std::lock_guard<std::mutex> lk(g_pool_mu);
@@ -59,7 +56,131 @@ hipError_t work_alloc(void** p, size_t bytes, hipStream_t stream) {
     return pool ? hipMallocFromPoolAsync(p, bytes, pool, stream) : hipMallocAsync(p, bytes, stream);
 }
 
-hipError_t work_free(void* p, hipStream_t stream) { return hipFreeAsync(p, stream); }
+// Small scratch is kept by the library between calls: a stream-ordered
+// allocation and its release cost the host 36 us together, more than the three
+// launches of a small render (11 us). A block belongs to one call at a time, and
+// afterwards to the stream of that call: the next call on the stream takes it
+// behind the event recorded at its release, so that stream order protects it as
+// it would a stream-ordered allocation (the event also covers a new stream that
+// the runtime gives the handle of a destroyed one). Calls on other streams, and
+// further calls of other threads on the same stream, have blocks of their own;
+// beyond kKeepBlocks blocks or kKeepBytes a device, for larger scratch, under
+// stream capture (the graph owns its allocations then) and on the per-thread
+// stream (one handle for many streams), the pool serves the call alone.
+namespace {
+constexpr size_t kKeepLargest = (size_t)64 << 20, kKeepSmallest = (size_t)64 << 10, kKeepBytes = (size_t)256 << 20;
+constexpr int kKeepBlocks = 32;
+struct KeptBlock {
+    void* p;
+    size_t bytes;
+    hipStream_t stream;
+    hipEvent_t done;
+    bool used;
+};
+struct KeptBlocks {
+    std::mutex mu;
+    KeptBlock b[kKeepBlocks];
+    int n = 0;
+    size_t bytes = 0;
+};
+// (never destroyed: calls may still run while static objects are)
+KeptBlocks* kept_blocks(int dev) {
+    static KeptBlocks* all = new KeptBlocks[64];
+    return dev >= 0 && dev < 64 ? all + dev : nullptr;
+}
+bool may_keep(hipStream_t stream) {
+    if (stream == hipStreamPerThread) return false;
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &st) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return st == hipStreamCaptureStatusNone;
+}
+}  // namespace
+
+hipError_t work_alloc(void** p, size_t bytes, hipStream_t stream) {
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    KeptBlocks* k = bytes <= kKeepLargest ? kept_blocks(dev) : nullptr;
+    if (!k || !may_keep(stream)) return pool_alloc(p, bytes, dev, stream);
+    size_t want = kKeepSmallest;
+    while (want < bytes) want *= 2;
+    std::lock_guard<std::mutex> lk(k->mu);
+    KeptBlock* best = nullptr;
+    for (int i = 0; i < k->n; ++i) {
+        KeptBlock& b = k->b[i];
+        if (!b.used && b.stream == stream && b.bytes >= bytes && (!best || b.bytes < best->bytes)) best = &b;
+    }
+    if (best) {
+        e = hipStreamWaitEvent(stream, best->done, 0);
+        if (e != hipSuccess) return e;
+        best->used = true;
+        *p = best->p;
+        return hipSuccess;
+    }
+    if (k->n == kKeepBlocks || k->bytes + want > kKeepBytes) return pool_alloc(p, bytes, dev, stream);
+    KeptBlock b{nullptr, want, stream, nullptr, true};
+    e = hipEventCreateWithFlags(&b.done, hipEventDisableTiming);
+    if (e != hipSuccess) return e;
+    e = pool_alloc(&b.p, want, dev, stream);
+    if (e != hipSuccess) {
+        (void)hipEventDestroy(b.done);
+        return e;
+    }
+    k->b[k->n++] = b;
+    k->bytes += want;
+    *p = b.p;
+    return hipSuccess;
+}
+
+hipError_t work_free(void* p, hipStream_t stream) {
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    if (KeptBlocks* k = kept_blocks(dev)) {
+        std::lock_guard<std::mutex> lk(k->mu);
+        for (int i = 0; i < k->n; ++i) {
+            if (k->b[i].p != p || !k->b[i].used) continue;
+            e = hipEventRecord(k->b[i].done, stream);
+            if (e == hipSuccess) {
+                k->b[i].used = false;
+                return e;
+            }
+            // (cannot be handed on behind the event: back to the pool in stream order)
+            (void)hipEventDestroy(k->b[i].done);
+            k->bytes -= k->b[i].bytes;
+            k->b[i] = k->b[--k->n];
+            (void)hipFreeAsync(p, stream);
+            return e;
+        }
+    }
+    return hipFreeAsync(p, stream);
+}
+
+hipError_t release_kept() {
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    KeptBlocks* k = kept_blocks(dev);
+    if (!k) return hipSuccess;
+    std::lock_guard<std::mutex> lk(k->mu);
+    for (int i = 0; i < k->n;) {
+        KeptBlock& b = k->b[i];
+        if (b.used) {
+            ++i;
+            continue;
+        }
+        e = hipEventSynchronize(b.done);
+        if (e == hipSuccess) e = hipFreeAsync(b.p, nullptr);
+        if (e != hipSuccess) return e;
+        (void)hipEventDestroy(b.done);
+        k->bytes -= b.bytes;
+        b = k->b[--k->n];
+    }
+    return hipSuccess;
+}
 
 size_t trace_bytes(int64_t n, int64_t cap) {
     const size_t head_b = ((size_t)(n > 0 ? n : 0) * sizeof(int32_t) + 255) & ~(size_t)255;

@@ -2,6 +2,8 @@
 block and room edges, remainders, smallest launches. Bars as in the other GPU
 tests: 1e-5 of the largest value for renders, 1e-4 for gradients, against the
 FP64 oracle."""
+import threading
+
 import numpy as np
 import pytest
 import torch
@@ -105,3 +107,48 @@ def test_per_point_timed_reduction(cap, records, monkeypatch):
     e = {k: rel_err(v.cpu().numpy(), ref[k]) for k, v in got.items()}
     announce(f"per-point timed cap={cap} records={records}: grad rel errors {e}")
     assert int(nsamp.sum()) > 1000 and max(e.values()) <= 1e-4, e
+
+
+def test_kept_scratch(tiny):
+    """Scratch kept between calls: growing and shrinking calls on two streams whose work overlaps, streams made and
+    dropped beyond the kept blocks, calls of four threads, and calls after a release all give the one-call results."""
+    sc, o, d, g, _ = tiny
+    tree, oo, dd, gg = upload(sc), tdev(o), tdev(d), tdev(g)
+
+    def once(m, stream):
+        with torch.cuda.stream(stream):
+            rgb, alpha, _, ns = ops.render(tree, oo[:m], dd[:m], 4.0, None, 1e-4, 64, want_depth=False)
+            grads = ops.render_backward(tree, oo[:m], dd[:m], rgb, alpha, ns, gg[:m], None, 4.0, None, 1e-4, 64)
+        return rgb, ns, grads[0]
+
+    def same(got, want):
+        return torch.equal(got[0], want[0]) and torch.equal(got[1], want[1]) and \
+            rel_err(got[2].cpu().numpy(), want[2].cpu().numpy()) <= 1e-5   # summation order of float32 atomics
+
+    sizes = [64, 4096, 640, 2048, 64, 4096]
+    main = torch.cuda.current_stream()
+    want = {m: once(m, main) for m in set(sizes)}
+    torch.cuda.synchronize()
+    two = [torch.cuda.Stream(), torch.cuda.Stream()]
+    got = [(m, once(m, s)) for _ in range(5) for m in sizes for s in two]
+    torch.cuda.synchronize()
+    assert all(same(r, want[m]) for m, r in got)
+    got = [(m, once(m, torch.cuda.Stream())) for k in range(40) for m in (64, 4096)]
+    torch.cuda.synchronize()
+    assert all(same(r, want[m]) for m, r in got)
+    results = []
+
+    def worker(stream):
+        results.extend((m, once(m, stream)) for m in sizes)
+
+    threads = [threading.Thread(target=worker, args=(s,)) for s in (main, main, two[0], two[1])]
+    for th in threads:
+        th.start()
+    for th in threads:
+        th.join()
+    torch.cuda.synchronize()
+    assert len(results) == 4 * len(sizes) and all(same(r, want[m]) for m, r in results)
+    _lib.neuvv_release_scratch()
+    r = once(4096, main)
+    torch.cuda.synchronize()
+    assert same(r, want[4096])
