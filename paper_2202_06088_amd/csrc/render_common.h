@@ -312,11 +312,13 @@ static __global__ void zero_queue_kernel(unsigned long long* q, unsigned long lo
 // list, and only the others on the first. The
 // pass is bound by the 24 bytes of ray per slot it reads; at high occupancy
 // it runs near HBM bandwidth, where the render kernel's refill rounds would
-// take one memory latency per round for every ray. Launches of fewer than
-// kCullSmall chunks that are not images use groups of kCullGroupSmall chunks,
-// so that they still spread over many wavefronts (each group is a chain of
-// dependent loads).
-constexpr int kCullGroup = 32;
+// take one memory latency per round for every ray. A group is a chain of
+// dependent steps (loads, tests, one atomic, list stores), so it is kept to what
+// a lane can hold in flight: 8 rays (a segment of an image), 4 in launches of
+// fewer than kCullSmall chunks that are not images. With 32 chunks to a group,
+// whose loads waited one by one behind the stores of the test before, 518,400
+// rays took 25 us and 867,000 took 31 us; now 9.5 and 16 us.
+constexpr int kCullGroup = 8;
 constexpr int kCullGroupSmall = 4;
 constexpr int64_t kCullSmall = 16384;
 
@@ -338,22 +340,42 @@ struct CullAdjoint {
     unsigned long long* count2;
 };
 
+// The cull of one ray in two halves, so that the loads of all rays of a lane's
+// group are in flight before the first test (a test's miss stores would keep
+// the later loads behind them).
+template <int MODE>
+struct CullIn {
+    f3v o, d;         // MODE 0
+    int ns, head;     // MODE 1 (head: -1 without a trace)
+    bool keep;        // MODE 4
+};
 template <int MODE, class Hit>
-__device__ __forceinline__ void cull_test(const Hit& hit, const RayArgs& ra, const RenderOut& out,
-                                          const CullAdjoint& adj, int64_t ray, bool& k, bool& k2) {
+__device__ __forceinline__ void cull_load(const Hit& hit, const RayArgs& ra, const CullAdjoint& adj, int64_t ray,
+                                          CullIn<MODE>& in) {
     if constexpr (MODE == 0) {
-        const f3v ov = load3(ra.o + 3 * ray), dv = load3(ra.d + 3 * ray);
-        const float o[3] = {ov.x, ov.y, ov.z};
-        const float d[3] = {dv.x, dv.y, dv.z};
+        in.o = load3(ra.o + 3 * ray);
+        in.d = load3(ra.d + 3 * ray);
+    } else if constexpr (MODE == 1) {
+        in.ns = adj.nsamp[ray];
+        in.head = adj.head ? adj.head[ray] : -1;
+    } else {
+        in.keep = hit.keep(ray);
+    }
+}
+template <int MODE, class Hit>
+__device__ __forceinline__ void cull_test(const Hit& hit, const RenderOut& out, const CullIn<MODE>& in, int64_t ray,
+                                          bool& k, bool& k2) {
+    if constexpr (MODE == 0) {
+        const float o[3] = {in.o.x, in.o.y, in.o.z};
+        const float d[3] = {in.d.x, in.d.y, in.d.z};
         k = hit(o, d);
         if (!k) write_miss(out, ray);
-    } else if constexpr (MODE == 4) {
-        k = hit.keep(ray);
-        if (!k) write_miss(out, ray);
+    } else if constexpr (MODE == 1) {
+        k = in.ns > 0 && in.head < 0;
+        k2 = in.ns > 0 && in.head >= 0;
     } else {
-        const bool s = adj.nsamp[ray] > 0, traced = adj.head && adj.head[ray] >= 0;
-        k = s && !traced;
-        k2 = s && traced;
+        k = in.keep;
+        if (!k) write_miss(out, ray);
     }
 }
 
@@ -381,28 +403,35 @@ static __global__ __launch_bounds__(kBlock) void cull_kernel(Hit hit, RayArgs ra
         // its ray loads and miss stores are contiguous; the rays kept are then
         // listed tile by tile in slot order from the per-row ballots.
         if (hi <= lo) return;
-        const int64_t tiles_x = ra.tiles_x;
-        const int64_t ty_lo = lo / tiles_x, ty_hi = (hi - 1) / tiles_x;
-        const int64_t nseg = (tiles_x + 7) / 8;
-        const int64_t n_seg = (ty_hi - ty_lo + 1) * nseg;
+        // (list form: fewer than 2^31 rays, so tile and segment indices fit 32 bits)
+        const uint32_t tiles_x = (uint32_t)ra.tiles_x;
+        const uint32_t ty_lo = (uint32_t)lo / tiles_x, ty_hi = (uint32_t)(hi - 1) / tiles_x;
+        const uint32_t nseg = (tiles_x + 7) / 8;
+        const uint32_t n_seg = (ty_hi - ty_lo + 1) * nseg;
         const int jt = lane >> 3;   // tile of the lane within the segment
-        for (int64_t sg = wi; sg < n_seg; sg += nw) {
-            const int64_t ty = ty_lo + sg / nseg, j = sg - (sg / nseg) * nseg;
-            const int64_t row0 = ty * tiles_x;
-            int64_t kx0 = 8 * j, kx1 = 8 * j + 8 < tiles_x ? 8 * j + 8 : tiles_x;
+        for (uint32_t sg = (uint32_t)wi; sg < n_seg; sg += (uint32_t)nw) {
+            const uint32_t ty = ty_lo + sg / nseg, j = sg - (sg / nseg) * nseg;
+            const int64_t row0 = (int64_t)ty * tiles_x;
+            int64_t kx0 = 8 * (int64_t)j, kx1 = kx0 + 8 < tiles_x ? kx0 + 8 : tiles_x;
             if (kx0 < lo - row0) kx0 = lo - row0;
             if (kx1 > hi - row0) kx1 = hi - row0;
             if (kx0 >= kx1) continue;   // wave-uniform
-            const int64_t tx = 8 * j + jt;
+            const int64_t tx = 8 * (int64_t)j + jt;
             const int64_t px = 8 * tx + (lane & 7);
             const bool lane_ok = tx >= kx0 && tx < kx1 && px < ra.img_w;
             uint64_t keep[8], keep2[8];
             int total = 0, total2 = 0;
+            CullIn<MODE> in[8];
 #pragma unroll
             for (int r = 0; r < 8; ++r) {
-                const int64_t ray = (8 * ty + r) * ra.img_w + px;
+                const int64_t ray = (8 * (int64_t)ty + r) * ra.img_w + px;
+                if (lane_ok && ray < ra.n) cull_load<MODE>(hit, ra, adj, ray, in[r]);
+            }
+#pragma unroll
+            for (int r = 0; r < 8; ++r) {
+                const int64_t ray = (8 * (int64_t)ty + r) * ra.img_w + px;
                 bool k = false, k2 = false;
-                if (lane_ok && ray < ra.n) cull_test<MODE>(hit, ra, out, adj, ray, k, k2);
+                if (lane_ok && ray < ra.n) cull_test<MODE>(hit, out, in[r], ray, k, k2);
                 keep[r] = __ballot(k);
                 total += __popcll(keep[r]);
                 if constexpr (MODE == 1) {
@@ -426,7 +455,7 @@ static __global__ __launch_bounds__(kBlock) void cull_kernel(Hit hit, RayArgs ra
                 for (int r = 0; r < 8; ++r) {
                     if ((kp[r] >> lane) & 1ull) {
                         const int within = 8 * r + (lane & 7);
-                        const int64_t ray = (8 * ty + r) * ra.img_w + px;
+                        const int64_t ray = (8 * (int64_t)ty + r) * ra.img_w + px;
                         ls[at + before + __popcll(tm & ((1ull << within) - 1ull))] = (int32_t)ray;
                     }
                 }
@@ -441,14 +470,18 @@ static __global__ __launch_bounds__(kBlock) void cull_kernel(Hit hit, RayArgs ra
         uint64_t keep[GROUP], keep2[GROUP];
         int32_t rays[GROUP];
         int total = 0, total2 = 0;
+        CullIn<MODE> in[GROUP];
 #pragma unroll
         for (int j = 0; j < GROUP; ++j) {
-            const int64_t c = c0 + j;
-            const int64_t ray = c < hi ? slot_to_ray(ra, c * 64 + lane) : -1;
-            bool k = false, k2 = false;
-            if (ray >= 0) cull_test<MODE>(hit, ra, out, adj, ray, k, k2);
-            keep[j] = __ballot(k);
+            const int64_t ray = c0 + j < hi ? slot_to_ray(ra, (c0 + j) * 64 + lane) : -1;
             rays[j] = (int32_t)ray;
+            if (ray >= 0) cull_load<MODE>(hit, ra, adj, ray, in[j]);
+        }
+#pragma unroll
+        for (int j = 0; j < GROUP; ++j) {
+            bool k = false, k2 = false;
+            if (rays[j] >= 0) cull_test<MODE>(hit, out, in[j], rays[j], k, k2);
+            keep[j] = __ballot(k);
             total += __popcll(keep[j]);
             if constexpr (MODE == 1) {
                 keep2[j] = __ballot(k2);

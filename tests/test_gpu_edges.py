@@ -152,3 +152,24 @@ def test_kept_scratch(tiny):
     r = once(4096, main)
     torch.cuda.synchronize()
     assert same(r, want[4096])
+
+
+@pytest.mark.parametrize("traced", [False, True])
+@pytest.mark.parametrize("width,n", [(1, 333), (7, 400), (8, 512), (9, 513), (63, 4000), (64, 4096), (65, 3999),
+                                     (513, 4096), (4096, 4096), (5000, 4096)])
+def test_cull_segments(tiny, width, n, traced):
+    """Images whose rows and columns end inside a tile, a segment of tiles and an XCD's part: the outputs are those of
+    the same rays as a list, bit for bit, and so are the gradients up to summation order."""
+    sc, o, d, g, _ = tiny
+    tree, oo, dd, gg = upload(sc), tdev(o[:n]), tdev(d[:n]), tdev(g[:n])
+    got = []
+    for w in (0, width):
+        trace = ops.Trace(n, 4 * n, oo.device) if traced else None
+        out = ops.render(tree, oo, dd, 4.0, None, 1e-4, w, trace=trace)
+        got.append(out + ops.render_backward(tree, oo, dd, out[0], out[1], out[3], gg, None, 4.0, None, 1e-4, w,
+                                             trace=trace))
+    torch.cuda.synchronize()
+    for a, b in zip(got[0][:4], got[1][:4]):
+        assert torch.equal(a, b)
+    for a, b in zip(got[0][4:], got[1][4:]):
+        assert rel_err(a.cpu().numpy(), b.cpu().numpy()) <= 1e-5
