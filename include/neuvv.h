@@ -353,9 +353,9 @@ int neuvv_render_noalloc(const neuvv_tree* tree, const neuvv_instance* inst, int
  * Two-phase adjoint: each sample's dL/dz and dL/dsigma (and dL/dy, Cg > 0)
  * are written once as a 32-byte record linked into its leaf's list; a second
  * kernel sums every list and adds each touched leaf's row once. The room for
- * records is 2 per ray, or the trace's room (trace_cap) in
- * neuvv_render_backward_trace when that is more, at least 2^20, at most
- * 2^31 - 1 (the environment
+ * records is 2 per ray, 16 per ray up to 2^24, or the trace's room
+ * (trace_cap) in neuvv_render_backward_trace, whichever is most; at least
+ * 2^20, at most 2^31 - 1 (the environment
  * variable NEUVV_BWD_RECORDS, read at every call, sets it; 0 turns records
  * off); samples beyond it are added per sample in the same call. Records
  * are used with image_width or not, for n_rays and n_leaves below 2^31.
@@ -411,6 +411,23 @@ int neuvv_render_trace(const neuvv_tree* tree, const neuvv_instance* inst, int64
                        float* rgb, float* alpha, float* depth, int32_t* nsamp, void* trace, int64_t trace_cap,
                        void* stream);
 int neuvv_render_backward_trace(const neuvv_tree* tree, const neuvv_instance* inst, int64_t n_rays,
+                                const float* ray_o, const float* ray_d, const float* ray_t, float t_scalar,
+                                int32_t image_width, float t_stop, const float* rgb, const float* alpha,
+                                const int32_t* nsamp, const float* grad_rgb, const float* grad_alpha,
+                                float* grad_leaf, float* grad_basis, float* grad_basis_g, const void* trace,
+                                int64_t trace_cap, void* stream);
+
+/*
+ * neuvv_render_backward_fresh - neuvv_render_backward (trace NULL) or
+ * neuvv_render_backward_trace whose grad_leaf is an output: every row is
+ * written, zero where a leaf has no gradient, whatever the buffer held. It
+ * saves clearing the buffer beforehand and adding to it: the reduction stores
+ * each row once. grad_leaf must be 16-byte aligned and used by nothing else
+ * until the call's work is done; grad_basis and grad_basis_g are accumulated
+ * as in the other calls.
+ * Errors: those of neuvv_render_backward_trace, ARG (alignment).
+ */
+int neuvv_render_backward_fresh(const neuvv_tree* tree, const neuvv_instance* inst, int64_t n_rays,
                                 const float* ray_o, const float* ray_d, const float* ray_t, float t_scalar,
                                 int32_t image_width, float t_stop, const float* rgb, const float* alpha,
                                 const int32_t* nsamp, const float* grad_rgb, const float* grad_alpha,

@@ -142,13 +142,17 @@ int make_rays(int64_t n, const float* o, const float* d, const float* t, float t
 }
 
 // Sample records of the two-phase adjoint: NEUVV_BWD_RECORDS overrides (0
-// turns the records off); by default room for two samples per ray or, after a
-// traced forward, for as many samples as the trace has room for if that is
-// more (every replayed sample has a trace entry); at least 2^20, at most
-// 2^31 - 1. Samples beyond the room take per-sample atomics.
+// turns the records off); by default room for two samples per ray, for sixteen
+// up to 2^24 in all (rays of a close view may all hit, thirteen samples each on
+// average; scattering 2.7 M samples of 427,000 rays one by one cost 1.7 ms) or,
+// after a traced forward, for as many samples as the trace has room for,
+// whichever is most; at least 2^20, at most 2^31 - 1. Samples beyond the room
+// take per-sample atomics.
 int64_t record_cap(int64_t n_rays, int64_t trace_cap) {
     const char* e = getenv("NEUVV_BWD_RECORDS");
+    const int64_t many = n_rays < ((int64_t)1 << 20) ? 16 * n_rays : (int64_t)1 << 24;
     int64_t cap = 2 * n_rays > trace_cap ? 2 * n_rays : trace_cap;
+    if (cap < many) cap = many;
     if (cap < (int64_t)1 << 20) cap = (int64_t)1 << 20;
     if (e && *e) cap = atoll(e);
     if (cap < 0) cap = 0;
@@ -355,7 +359,7 @@ static int backward_impl(const neuvv_tree* tree, const neuvv_instance* inst, int
                   const float* ray_d, const float* ray_t, float t_scalar, int32_t image_width, float t_stop,
                   const float* rgb, const float* alpha, const int32_t* nsamp, const float* grad_rgb,
                   const float* grad_alpha, float* grad_leaf, float* grad_basis, float* grad_basis_g,
-                  const void* trace, int64_t trace_cap, void* stream) {
+                  const void* trace, int64_t trace_cap, void* stream, bool fresh = false) {
     int rc = check_tree(tree);
     if (rc) return rc;
     neuvv::InstArgs in;
@@ -368,7 +372,16 @@ static int backward_impl(const neuvv_tree* tree, const neuvv_instance* inst, int
     if (tree->n_leaves > 0 && !grad_leaf) return fail(NEUVV_ERR_ARG, "grad_leaf is NULL");
     if (tree->edit) return fail(NEUVV_ERR_UNSUPPORTED, "no adjoint through appearance edits");
     neuvv::BackwardIO io{rgb, alpha, nsamp, grad_rgb, grad_alpha, grad_leaf, grad_basis,
-                         tree->Cg > 0 ? grad_basis_g : nullptr, record_cap(n_rays, trace ? trace_cap : 0)};
+                         tree->Cg > 0 ? grad_basis_g : nullptr, fresh ? 1 : 0,
+                         record_cap(n_rays, trace ? trace_cap : 0)};
+    if (fresh) {
+        if ((uintptr_t)grad_leaf & 15) return fail(NEUVV_ERR_ARG, "grad_leaf must be 16-byte aligned");
+        if (ra.n_slots <= 0)
+            return hip_status(neuvv::launch_zero_rows(grad_leaf,
+                                                      tree->n_leaves * (int64_t)neuvv::grad_row_elems(tree->K, tree->C, tree->Cg),
+                                                      (hipStream_t)stream),
+                              "clearing the gradient rows");
+    }
     if (trace) io.trace = neuvv::trace_layout(const_cast<void*>(trace), n_rays, trace_cap);
     const hipError_t e = tree->Cg > 0
                              ? neuvv::launch_render_pp_bwd(tree->dtype, tree_args(tree), in, ra, io,
@@ -404,6 +417,21 @@ int neuvv_render_backward(const neuvv_tree* tree, const neuvv_instance* inst, in
     NEUVV_GUARD_BEGIN
     return backward_impl(tree, inst, n_rays, ray_o, ray_d, ray_t, t_scalar, image_width, t_stop, rgb, alpha, nsamp,
                          grad_rgb, grad_alpha, grad_leaf, grad_basis, grad_basis_g, nullptr, 0, stream);
+    NEUVV_GUARD_END
+}
+
+int neuvv_render_backward_fresh(const neuvv_tree* tree, const neuvv_instance* inst, int64_t n_rays,
+                                const float* ray_o, const float* ray_d, const float* ray_t, float t_scalar,
+                                int32_t image_width, float t_stop, const float* rgb, const float* alpha,
+                                const int32_t* nsamp, const float* grad_rgb, const float* grad_alpha,
+                                float* grad_leaf, float* grad_basis, float* grad_basis_g, const void* trace,
+                                int64_t trace_cap, void* stream) {
+    NEUVV_GUARD_BEGIN
+    int rc = check_tree(tree);
+    if (rc) return rc;
+    if (trace && (rc = check_trace(n_rays, trace, trace_cap))) return rc;
+    return backward_impl(tree, inst, n_rays, ray_o, ray_d, ray_t, t_scalar, image_width, t_stop, rgb, alpha, nsamp,
+                         grad_rgb, grad_alpha, grad_leaf, grad_basis, grad_basis_g, trace, trace_cap, stream, true);
     NEUVV_GUARD_END
 }
 

@@ -43,6 +43,7 @@ struct BackwardIO {
     float* grad_leaf;    // [n_leaves][grad_row_elems(K, C, Cg)]
     float* grad_basis;
     float* grad_basis_g;   // per-point hyperangle basis gradient (Cg > 0), or nullptr
+    int32_t fresh;         // grad_leaf is written, not added to: rows of leaves without a gradient become zero
     int64_t record_cap;    // two-phase adjoint: sample records at most (0: per-sample atomics only)
     TraceArgs trace;       // head == nullptr: walk every ray (K = 16, C = 8 form only)
 };
@@ -58,6 +59,10 @@ struct RecordArgs {
                                    // K = 16, C = 8 form with one time for every ray: {next, ray
                                    // direction (world, float bits)} instead
     unsigned long long* counter;   // records handed out so far (take_items)
+    const unsigned long long* counts;   // per XCD part, kQueueStride apart: {rays that walk, their samples}, then the
+                                        // same for the rays that replay (the cull pass fills them)
+    double* basis_sum;             // [64] the reduction's basis gradients (one time for every ray)
+    int32_t max_waves;             // wavefronts that one kernel of the call can have on the device at once
     int64_t cap;
 };
 
@@ -155,6 +160,7 @@ hipError_t fixed_scratch(void** p);
 // memory pool the library keeps per device, which holds on to its memory
 // between calls instead of returning it at every synchronisation.
 // release_kept frees the kept blocks of the current device that no call holds.
+hipError_t launch_zero_rows(float* rows, int64_t n, hipStream_t stream);
 hipError_t work_alloc(void** p, size_t bytes, hipStream_t stream);
 hipError_t work_free(void* p, hipStream_t stream);
 hipError_t release_kept();

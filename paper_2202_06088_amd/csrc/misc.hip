@@ -276,6 +276,19 @@ hipError_t launch_eval_hh(int K, int64_t n, const float* dirs, const float* gam,
     return hipGetLastError();
 }
 
+__global__ __launch_bounds__(kEwBlock) void zero_rows_kernel(float4* rows, int64_t n) {
+    for (int64_t i = blockIdx.x * (int64_t)kEwBlock + threadIdx.x; i < n; i += (int64_t)gridDim.x * kEwBlock)
+        rows[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+}
+
+// Clears n floats (a multiple of 4, 16-byte aligned).
+hipError_t launch_zero_rows(float* rows, int64_t n, hipStream_t stream) {
+    if (n <= 0) return hipSuccess;
+    hipLaunchKernelGGL(zero_rows_kernel, dim3(ew_grid(n / 4)), dim3(kEwBlock), 0, stream, reinterpret_cast<float4*>(rows),
+                       n / 4);
+    return hipGetLastError();
+}
+
 // ----------------------------------------------------------------------------
 // gradient rows -> the float32 payload layout
 

@@ -388,6 +388,12 @@ __device__ __forceinline__ int64_t list_room(unsigned long long* count, int x, i
     return (int64_t)(((uint64_t)b_hi << 32) | b_lo);
 }
 
+// Adds the lanes' samples to a counter, one atomic per wavefront.
+__device__ __forceinline__ void add_samples(unsigned long long* total, int64_t v) {
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+    if ((threadIdx.x & 63) == 0) atomicAdd(total, (unsigned long long)v);
+}
+
 template <int MODE, class Hit, int GROUP = kCullGroup>
 static __global__ __launch_bounds__(kBlock) void cull_kernel(Hit hit, RayArgs ra, RenderOut out, CullAdjoint adj,
                                                               int32_t* list, unsigned long long* count) {
@@ -421,6 +427,7 @@ static __global__ __launch_bounds__(kBlock) void cull_kernel(Hit hit, RayArgs ra
             const bool lane_ok = tx >= kx0 && tx < kx1 && px < ra.img_w;
             uint64_t keep[8], keep2[8];
             int total = 0, total2 = 0;
+            int64_t samples = 0;   // MODE 1: the lane's
             CullIn<MODE> in[8];
 #pragma unroll
             for (int r = 0; r < 8; ++r) {
@@ -435,6 +442,7 @@ static __global__ __launch_bounds__(kBlock) void cull_kernel(Hit hit, RayArgs ra
                 keep[r] = __ballot(k);
                 total += __popcll(keep[r]);
                 if constexpr (MODE == 1) {
+                    if (k || k2) samples += in[r].ns;
                     keep2[r] = __ballot(k2);
                     total2 += __popcll(keep2[r]);
                 }
@@ -461,8 +469,10 @@ static __global__ __launch_bounds__(kBlock) void cull_kernel(Hit hit, RayArgs ra
                 }
             };
             if (total) emit(keep, total, list, count);   // wave-uniform
-            if constexpr (MODE == 1)
+            if constexpr (MODE == 1) {
                 if (total2) emit(keep2, total2, adj.list2, adj.count2);
+                if (total + total2) add_samples(count + x * kQueueStride + 1, samples);
+            }
         }
         return;
     }
@@ -470,6 +480,7 @@ static __global__ __launch_bounds__(kBlock) void cull_kernel(Hit hit, RayArgs ra
         uint64_t keep[GROUP], keep2[GROUP];
         int32_t rays[GROUP];
         int total = 0, total2 = 0;
+        int64_t samples = 0;   // MODE 1: the lane's
         CullIn<MODE> in[GROUP];
 #pragma unroll
         for (int j = 0; j < GROUP; ++j) {
@@ -484,6 +495,7 @@ static __global__ __launch_bounds__(kBlock) void cull_kernel(Hit hit, RayArgs ra
             keep[j] = __ballot(k);
             total += __popcll(keep[j]);
             if constexpr (MODE == 1) {
+                if (k || k2) samples += in[j].ns;
                 keep2[j] = __ballot(k2);
                 total2 += __popcll(keep2[j]);
             }
@@ -497,8 +509,10 @@ static __global__ __launch_bounds__(kBlock) void cull_kernel(Hit hit, RayArgs ra
             }
         };
         if (total) emit(keep, total, list, count);   // wave-uniform
-        if constexpr (MODE == 1)
+        if constexpr (MODE == 1) {
             if (total2) emit(keep2, total2, adj.list2, adj.count2);
+            if (total + total2) add_samples(count + x * kQueueStride + 1, samples);
+        }
     }
 }
 
@@ -666,6 +680,67 @@ __device__ __forceinline__ RecordRun record_run(uint64_t hm, bool has, int leaf)
     return r;
 }
 
+// Whether every sample of the call is sure to get a record: the samples and
+// rays the cull pass counted, an unused block for every wavefront that takes
+// rays (of the persistent grids of the walk and the replay: no more than chunks
+// of rays), and the up to 63 items that a request leaves behind at a block's end. Then nothing is scattered, and a call that
+// writes its gradient rows (fresh) may leave them uninitialised until the
+// reduction stores them, each once; else they are cleared before anything is
+// added. The same answer for every thread of the call's kernels.
+__device__ __forceinline__ bool records_fit(const RecordArgs& rec) {
+    if (!rec.head) return false;
+    int64_t samples = 0, waves = 0;
+#pragma unroll
+    for (int list = 0; list < 2; ++list) {
+        int64_t chunks = 0;
+#pragma unroll
+        for (int x = 0; x < kQueues; ++x) {   // (the replaying rays' counts lie two groups of lines on)
+            const unsigned long long* c = rec.counts + (list * 2 * kQueues + x) * kQueueStride;
+            chunks += ((int64_t)c[0] + 63) >> 6;
+            samples += (int64_t)c[1];
+        }
+        waves += chunks < rec.max_waves ? chunks : rec.max_waves;
+    }
+    const int64_t block = item_block(rec.cap);
+    return samples >= 0 && (samples / (block - 63) + 1 + waves) * block <= rec.cap;
+}
+
+// Clears the n float4 of a fresh call's gradient rows unless the reduction will
+// write every one of them.
+static __global__ __launch_bounds__(kBlock) void fresh_clear_kernel(RecordArgs rec, float4* rows, int64_t n) {
+    if (records_fit(rec)) return;
+    for (int64_t i = blockIdx.x * (int64_t)kBlock + threadIdx.x; i < n; i += (int64_t)gridDim.x * kBlock)
+        rows[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+}
+
+// Basis gradients of a reduction with one time for every ray: n components per
+// wavefront (lane c: component c) are summed in float64 over the block and the
+// grid, and basis_finish_kernel adds the sums to the two frames' rows. (They
+// are sums over all leaves of terms of either sign: added to the rows block by
+// block in float32, their last bits differed by up to 4e-7 from run to run.)
+// s: n doubles of LDS, zero and synchronised; at: the components' place in
+// basis_sum. Call with the whole block.
+__device__ __forceinline__ void basis_add(const RecordArgs& rec, double* s, int at, int n, double v) {
+    if ((int)(threadIdx.x & 63) < n) atomicAdd(s + (threadIdx.x & 63), v);
+    __syncthreads();
+    if ((int)threadIdx.x < n) unsafeAtomicAdd(rec.basis_sum + at + threadIdx.x, s[threadIdx.x]);
+}
+// One block: adds the sums of C density and Cg hyperangle components.
+static __global__ void basis_finish_kernel(TreeArgs tr, InstArgs in, float t, RecordArgs rec, int C, float* grad_basis,
+                                           int Cg, float* grad_basis_g) {
+    const int c = threadIdx.x;
+    const bool dens = c < C;
+    float* grad = dens ? grad_basis : grad_basis_g;
+    if (c >= C + Cg || !grad) return;
+    int i0, i1;
+    float f;
+    time_setup(tr, in, t, i0, i1, f);
+    const int n = dens ? C : Cg, e = dens ? c : c - C;
+    const double v = rec.basis_sum[c];
+    unsafeAtomicAdd(grad + (int64_t)i0 * n + e, (float)((1.0 - (double)f) * v));
+    if (f != 0.0f) unsafeAtomicAdd(grad + (int64_t)i1 * n + e, (float)((double)f * v));
+}
+
 // Hands leaves with records to the idle lanes of a reduction wavefront.
 // Wavefront w takes 64-leaf batches w, w + W, ...; a batch's heads are read in
 // one load (lane = leaf) and its leaves with records are compacted into a
@@ -687,10 +762,22 @@ __device__ __forceinline__ LeafFeeder leaf_feeder(int wave_in_block) {
     return f;
 }
 
+// Writes zero rows of ROW floats for the leaves of the batch at b0 whose bit is
+// set in m: sixteen bytes per lane, whole rows per instruction.
+template <int ROW>
+__device__ __forceinline__ void zero_batch_rows(float* rows, int64_t b0, uint64_t m) {
+    constexpr int per = ROW / 4;   // float4 per row
+    float4* p = reinterpret_cast<float4*>(rows + b0 * ROW);
+    for (int i = threadIdx.x & 63; i < kWave * per; i += kWave)
+        if ((m >> (i / per)) & 1ull) p[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+}
+
 // Gives idle lanes (leaf < 0) a leaf and its first record while leaves are left.
-// q: this wavefront's LDS queue of kWave entries. Call with every lane active.
+// q: this wavefront's LDS queue of kWave entries. fresh: the rows (of ROW floats)
+// of leaves without records are written here, as zeros. Call with every lane active.
+template <int ROW>
 __device__ __forceinline__ void feed_leaves(LeafFeeder& f, const RecordArgs& rec, int64_t n_leaves, int2* q,
-                                            int& leaf, int& first) {
+                                            int& leaf, int& first, bool fresh, float* rows) {
     const int lane = threadIdx.x & 63;
     for (;;) {
         const uint64_t idle = __ballot(leaf < 0);
@@ -705,6 +792,7 @@ __device__ __forceinline__ void feed_leaves(LeafFeeder& f, const RecordArgs& rec
             const int64_t L = b0 + lane;
             const int h = L < n_leaves ? rec.head[L] : -1;
             const uint64_t m = __ballot(h >= 0);
+            if (fresh) zero_batch_rows<ROW>(rows, b0, __ballot(L < n_leaves) & ~m);
             __builtin_amdgcn_wave_barrier();
             if (h >= 0) q[lane_rank(m)] = make_int2((int)L, h);
             __builtin_amdgcn_wave_barrier();
@@ -744,7 +832,7 @@ static hipError_t adjoint_begin(const TreeArgs& tr, const RayArgs& ra, const int
     const bool listed = ra.n <= (int64_t)INT32_MAX;   // else the slot form: the walking kernel tests every ray
     if (trace_head && !listed) return hipErrorInvalidValue;
     constexpr int kCounters = kQueues * kQueueStride;
-    constexpr int n_hdr = 4 * kCounters + kQueueStride;
+    constexpr int n_hdr = 4 * kCounters + kQueueStride + 64;   // (the last 64 start as the float64 zeros of basis_sum)
     constexpr size_t hdr = ((size_t)n_hdr * sizeof(unsigned long long) + 255) & ~(size_t)255;
     const size_t list_b = listed ? (size_t)((ra.n_slots + 63) >> 6) * 64 * sizeof(int32_t) : 0;
     const size_t lists = trace_head ? 2 * list_b : list_b;
@@ -762,6 +850,9 @@ static hipError_t adjoint_begin(const TreeArgs& tr, const RayArgs& ra, const int
     s.replay.queue = counters + 2 * kCounters;
     if (cap > 0) {
         s.rec.counter = counters + 4 * kCounters;
+        s.rec.counts = counters + kCounters;
+        s.rec.basis_sum = reinterpret_cast<double*>(counters + 4 * kCounters + kQueueStride);
+        s.rec.max_waves = device_cu_count() * 32;
         s.rec.head = reinterpret_cast<int32_t*>(p + hdr + lists);
         s.rec.rec = reinterpret_cast<int4*>(p + hdr + lists + head_b);
         s.rec.cap = cap;
@@ -779,6 +870,16 @@ static hipError_t adjoint_begin(const TreeArgs& tr, const RayArgs& ra, const int
         e = launch_cull_hit<1>(NoHit{}, ra, RenderOut{}, adj, list, counters + kCounters, st);
     }
     return e;
+}
+// Before a fresh call's rays: its rows of `row` floats are cleared where the
+// reduction cannot be relied on to write them.
+static hipError_t fresh_begin(const TreeArgs& tr, const BackwardIO& io, int row, const RecordArgs& rec, hipStream_t st) {
+    const int64_t n = tr.n_leaves * (int64_t)(row / 4);
+    if (n <= 0) return hipSuccess;
+    const int64_t want = (n + kBlock - 1) / kBlock, cap = (int64_t)device_cu_count() * 4;
+    hipLaunchKernelGGL(fresh_clear_kernel, dim3((unsigned)(want < cap ? want : cap)), dim3(kBlock), 0, st, rec,
+                       reinterpret_cast<float4*>(io.grad_leaf), n);
+    return hipGetLastError();
 }
 static hipError_t adjoint_end(const AdjointScratch& s, hipError_t e, hipStream_t st) {
     const hipError_t f = s.mem ? work_free(s.mem, st) : hipSuccess;

@@ -784,13 +784,15 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(min_wave
 // and basis, and the basis gradient stays with the adjoint.
 template <int K, int C, int DT, bool IDENT, bool COMMON_T>
 __global__ __launch_bounds__(kBlock) void reduce_records_kernel(TreeArgs tr, InstArgs in, RayArgs ra,
-                                                                RecordArgs rec, float* grad_leaf, float* grad_basis) {
+                                                                RecordArgs rec, float* grad_leaf, float* grad_basis,
+                                                                int32_t fresh_call) {
     constexpr int ROW = grad_row<K, C>();
+    const bool fresh = fresh_call && records_fit(rec);   // rows are stored; else added to
     constexpr int R = 3 * K + C;
     constexpr int NA = COMMON_T ? 3 * K : R;   // row sums a lane holds; acc[NA] = sum gx
     // a finished leaf's slot: its sums, sum gx, its w^sigma
     __shared__ float s_row[kBlock / kWave][kFlushSlots][NA + 1 + C + 1];
-    __shared__ float s_gb[C];
+    __shared__ double s_gb[C];
     __shared__ float s_bc[C];
     // scalar time: radial factors and density row of the common frame (the
     // arithmetic of ray_basis, so the values are the adjoint's)
@@ -805,11 +807,11 @@ __global__ __launch_bounds__(kBlock) void reduce_records_kernel(TreeArgs tr, Ins
             s_bc[threadIdx.x] = (1.0f - cf) * tr.basis[(int64_t)ci0 * C + threadIdx.x] +
                                 cf * tr.basis[(int64_t)ci1 * C + threadIdx.x];
     }
-    if (threadIdx.x < C) s_gb[threadIdx.x] = 0.0f;
+    if (threadIdx.x < C) s_gb[threadIdx.x] = 0.0;
     __syncthreads();
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int N = (int)tr.n_leaves;
-    float bacc = 0.0f;   // lane c < C: component c of the basis gradient
+    double bacc = 0.0;   // lane c < C: component c of the basis gradient
 
     int leaf = -1;                // this lane's leaf; -1: idle
     int4 ra0 = make_int4(0, 0, 0, 0), ra1 = make_int4(-1, 0, 0, 0);   // its current record
@@ -822,7 +824,7 @@ __global__ __launch_bounds__(kBlock) void reduce_records_kernel(TreeArgs tr, Ins
     for (;;) {
         // hand leaves with records to idle lanes; a lane that got one loads its first record
         int first = -1;
-        feed_leaves(feeder, rec, tr.n_leaves, s_q[wv], leaf, first);
+        feed_leaves<ROW>(feeder, rec, tr.n_leaves, s_q[wv], leaf, first, fresh, grad_leaf);
         if (first >= 0) {
             ra0 = rec.rec[2 * (int64_t)first];
             ra1 = rec.rec[2 * (int64_t)first + 1];
@@ -906,33 +908,23 @@ __global__ __launch_bounds__(kBlock) void reduce_records_kernel(TreeArgs tr, Ins
                 const int L = __builtin_amdgcn_readlane(leaf, j);
                 const float sgx = s_row[wv][q][NA];
 #pragma unroll
-                for (int c0 = 0; c0 < R; c0 += kWave) {   // one atomic instruction per 64 values
+                for (int c0 = 0; c0 < ROW; c0 += kWave) {   // one instruction per 64 values
                     const int c = c0 + lane;
-                    if (c < 3 * K || (!COMMON_T && c < R)) {
-                        unsafeAtomicAdd(grad_leaf + (int64_t)L * ROW + c, s_row[wv][q][c]);
-                    } else if (COMMON_T && c < R) {
-                        unsafeAtomicAdd(grad_leaf + (int64_t)L * ROW + c, sgx * s_bc[c - 3 * K]);
-                    }
+                    float v = 0.0f;
+                    if (c < 3 * K || (!COMMON_T && c < R)) v = s_row[wv][q][c];
+                    else if (COMMON_T && c < R) v = sgx * s_bc[c - 3 * K];
+                    float* at = grad_leaf + (int64_t)L * ROW + c;
+                    if (fresh) *at = v;
+                    else if (c < R) unsafeAtomicAdd(at, v);
                 }
-                if (grad_basis && lane < C) bacc = fmaf(sgx, s_row[wv][q][NA + 1 + lane], bacc);
+                if (grad_basis && lane < C) bacc = fma((double)sgx, (double)s_row[wv][q][NA + 1 + lane], bacc);
             }
             __builtin_amdgcn_wave_barrier();
             if (mine) leaf = -1;
             dm = __ballot(done && leaf >= 0);
         }
     }
-    if (grad_basis) {
-        if (lane < C) atomicAdd(&s_gb[lane], bacc);
-        __syncthreads();
-        if (threadIdx.x < C) {
-            int i0, i1;
-            float f;
-            time_setup(tr, in, ra.t_scalar, i0, i1, f);
-            const float v = s_gb[threadIdx.x];
-            unsafeAtomicAdd(grad_basis + (int64_t)i0 * C + threadIdx.x, (1.0f - f) * v);
-            if (f != 0.0f) unsafeAtomicAdd(grad_basis + (int64_t)i1 * C + threadIdx.x, f * v);
-        }
-    }
+    if (grad_basis) basis_add(rec, s_gb, 0, C, bacc);
 }
 
 template <int K, int C, int DT, bool EDIT, bool TRACE>
@@ -990,6 +982,7 @@ static hipError_t bwd_t(const TreeArgs& tr, const InstArgs& in, const RayArgs& r
     AdjointScratch sc;
     hipError_t e = adjoint_begin(tr, ra, io.nsamp, io.trace.head, cap, st, sc);
     const RecordArgs& rec = sc.rec;
+    if (e == hipSuccess && io.fresh) e = fresh_begin(tr, io, grad_row<K, C>(), rec, st);
     if (e == hipSuccess) e = bwd_walk<K, C, DT>(tr, in, sc.walk, io, rec, st);
     if (e == hipSuccess && io.trace.head) e = bwd_replay<K, C, DT>(tr, in, sc.replay, io, rec, st);
     if (e == hipSuccess && cap > 0) {
@@ -1001,18 +994,21 @@ static hipError_t bwd_t(const TreeArgs& tr, const InstArgs& in, const RayArgs& r
         if (ra.t == nullptr) {
             if (in.identity)
                 hipLaunchKernelGGL((reduce_records_kernel<K, C, DT, true, true>), grid, dim3(kBlock), 0, st, tr, in,
-                                   ra, rec, io.grad_leaf, io.grad_basis);
+                                   ra, rec, io.grad_leaf, io.grad_basis, io.fresh);
             else
                 hipLaunchKernelGGL((reduce_records_kernel<K, C, DT, false, true>), grid, dim3(kBlock), 0, st, tr, in,
-                                   ra, rec, io.grad_leaf, io.grad_basis);
+                                   ra, rec, io.grad_leaf, io.grad_basis, io.fresh);
         } else {
             if (in.identity)
                 hipLaunchKernelGGL((reduce_records_kernel<K, C, DT, true, false>), grid, dim3(kBlock), 0, st, tr, in,
-                                   ra, rec, io.grad_leaf, nullptr);
+                                   ra, rec, io.grad_leaf, nullptr, io.fresh);
             else
                 hipLaunchKernelGGL((reduce_records_kernel<K, C, DT, false, false>), grid, dim3(kBlock), 0, st, tr,
-                                   in, ra, rec, io.grad_leaf, nullptr);
+                                   in, ra, rec, io.grad_leaf, nullptr, io.fresh);
         }
+        if (ra.t == nullptr && io.grad_basis)
+            hipLaunchKernelGGL(basis_finish_kernel, dim3(1), dim3(kWave), 0, st, tr, in, ra.t_scalar, rec, C,
+                               io.grad_basis, 0, nullptr);
         e = hipGetLastError();
     }
     return adjoint_end(sc, e, st);

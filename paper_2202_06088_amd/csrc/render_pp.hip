@@ -776,13 +776,14 @@ template <int DT, bool IDENT>
 __global__ __launch_bounds__(kBlock) void reduce_pp_records_kernel(TreeArgs tr, InstArgs in, RayArgs ra,
                                                                    RecordArgs rec, BackwardIO io) {
     using namespace pp;
+    const bool fresh = io.fresh && records_fit(rec);   // rows are stored; else added to
     constexpr int R = 3 * K + 2;   // HH sums, sum gx, sum gy
     // a finished leaf's slot: its sums, then its w^sigma and w^gamma rows
     __shared__ float s_row[kBlock / kWave][kFlushSlots][R + C + CG + 1];
     __shared__ float s_brow[C], s_bgrow[CG];
-    __shared__ float s_acc[2 * kWave];
+    __shared__ double s_acc[2 * kWave];
     stage_common_rows(tr, in, ra.t_scalar, s_brow, s_bgrow);
-    if (threadIdx.x < 2 * kWave) s_acc[threadIdx.x] = 0.0f;
+    if (threadIdx.x < 2 * kWave) s_acc[threadIdx.x] = 0.0;
     __syncthreads();
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
 
@@ -794,7 +795,7 @@ __global__ __launch_bounds__(kBlock) void reduce_pp_records_kernel(TreeArgs tr, 
     float acc[R];
 #pragma unroll
     for (int c = 0; c < R; ++c) acc[c] = 0.0f;
-    float bacc[2] = {0.0f, 0.0f};   // lane c: components c of the two basis gradients
+    double bacc[2] = {0.0, 0.0};   // lane c: components c of the two basis gradients
     LeafFeeder feeder = leaf_feeder(wv);
     __shared__ int2 s_q[kBlock / kWave][kWave];
 
@@ -802,7 +803,7 @@ __global__ __launch_bounds__(kBlock) void reduce_pp_records_kernel(TreeArgs tr, 
         // hand leaves with records to idle lanes; a lane that got one loads its
         // first record and computes the leaf's radial factors
         int first = -1;
-        feed_leaves(feeder, rec, tr.n_leaves, s_q[wv], leaf, first);
+        feed_leaves<ROW>(feeder, rec, tr.n_leaves, s_q[wv], leaf, first, fresh, io.grad_leaf);
         if (first >= 0) {
             ra0 = rec.rec[2 * (int64_t)first];
             ra1 = rec.rec[2 * (int64_t)first + 1];
@@ -878,36 +879,23 @@ __global__ __launch_bounds__(kBlock) void reduce_pp_records_kernel(TreeArgs tr, 
 #pragma unroll
                 for (int jj = 0; jj < 2; ++jj) {
                     const int c = pp_component(jj, lane);
-                    if (c < 3 * K) unsafeAtomicAdd(row + c, s_row[wv][q][c]);
-                    else if (c < 3 * K + C) unsafeAtomicAdd(row + c, sgx * s_brow[c - 3 * K]);
-                    else if (c < 3 * K + C + CG) unsafeAtomicAdd(row + c, sgy * s_bgrow[c - 3 * K - C]);
+                    float v = 0.0f;
+                    if (c < 3 * K) v = s_row[wv][q][c];
+                    else if (c < 3 * K + C) v = sgx * s_brow[c - 3 * K];
+                    else if (c < 3 * K + C + CG) v = sgy * s_bgrow[c - 3 * K - C];
+                    if (fresh) row[c] = v;
+                    else if (c < 3 * K + C + CG) unsafeAtomicAdd(row + c, v);
                 }
-                if (lane < C) bacc[0] = fmaf(sgx, s_row[wv][q][R + lane], bacc[0]);
-                if (lane < CG) bacc[1] = fmaf(sgy, s_row[wv][q][R + C + lane], bacc[1]);
+                if (lane < C) bacc[0] = fma((double)sgx, (double)s_row[wv][q][R + lane], bacc[0]);
+                if (lane < CG) bacc[1] = fma((double)sgy, (double)s_row[wv][q][R + C + lane], bacc[1]);
             }
             __builtin_amdgcn_wave_barrier();
             if (mine) leaf = -1;
             dm = __ballot(done && leaf >= 0);
         }
     }
-    // basis gradients: sum over the block, spread over the two interpolated rows
-    if (lane < C) atomicAdd(&s_acc[lane], bacc[0]);
-    if (lane < CG) atomicAdd(&s_acc[kWave + lane], bacc[1]);
-    __syncthreads();
-    const int c = threadIdx.x;
-    const bool dens = c < C;
-    const bool gam = c >= kWave && c < kWave + CG;
-    float* gB = dens ? io.grad_basis : io.grad_basis_g;
-    if ((dens || gam) && gB) {
-        const int e = dens ? c : c - kWave;
-        const int Rb = dens ? C : CG;
-        int i0, i1;
-        float f;
-        time_setup(tr, in, ra.t_scalar, i0, i1, f);
-        const float v = s_acc[c];
-        unsafeAtomicAdd(gB + (int64_t)i0 * Rb + e, (1.0f - f) * v);
-        if (f != 0.0f) unsafeAtomicAdd(gB + (int64_t)i1 * Rb + e, f * v);
-    }
+    basis_add(rec, s_acc, 0, C, bacc[0]);
+    basis_add(rec, s_acc + kWave, C, CG, bacc[1]);
 }
 
 // The same with a time per ray. Records of one leaf then share neither gamma
@@ -927,10 +915,13 @@ __global__ __launch_bounds__(kBlock) void reduce_pp_timed_kernel(TreeArgs tr, In
     __shared__ float s_h[kBlock / kWave][K];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int64_t N = tr.n_leaves, n_waves = (int64_t)gridDim.x * (kBlock / kWave);
+    const bool fresh = io.fresh && records_fit(rec);   // rows are stored; else added to
     for (int64_t b = (int64_t)blockIdx.x * (kBlock / kWave) + wv; b * kWave < N; b += n_waves) {
         const int64_t own = b * kWave + lane;
         const int first = own < N ? rec.head[own] : -1;
-        for (uint64_t m = __ballot(first >= 0); m; m &= m - 1) {
+        const uint64_t listed = __ballot(first >= 0);
+        if (fresh) zero_batch_rows<ROW>(io.grad_leaf, b * kWave, __ballot(own < N) & ~listed);
+        for (uint64_t m = listed; m; m &= m - 1) {
             const int src = __builtin_ctzll(m);
             const int64_t L = b * kWave + src;
             int r = __builtin_amdgcn_readlane(first, src);
@@ -996,7 +987,8 @@ __global__ __launch_bounds__(kBlock) void reduce_pp_timed_kernel(TreeArgs tr, In
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
                 const int c = pp_component(j, lane);
-                if (c < 3 * K + C + CG) unsafeAtomicAdd(row + c, acc[j]);
+                if (fresh) row[c] = acc[j];   // (acc is 0 in the padding)
+                else if (c < 3 * K + C + CG) unsafeAtomicAdd(row + c, acc[j]);
             }
         }
     }
@@ -1049,6 +1041,7 @@ static hipError_t pp_bwd_t(const TreeArgs& tr, const InstArgs& in, const RayArgs
     AdjointScratch sc;
     hipError_t e = adjoint_begin(tr, ra, io.nsamp, io.trace.head, cap, st, sc);
     const RecordArgs& rec = sc.rec;
+    if (e == hipSuccess && io.fresh) e = fresh_begin(tr, io, pp::ROW, rec, st);
     if (e == hipSuccess) e = pp_bwd_walk<DT>(tr, in, sc.walk, io, rec, st);
     if (e == hipSuccess && io.trace.head) e = pp_bwd_replay<DT>(tr, in, sc.replay, io, rec, st);
     if (e == hipSuccess && cap > 0) {
@@ -1058,6 +1051,9 @@ static hipError_t pp_bwd_t(const TreeArgs& tr, const InstArgs& in, const RayArgs
         auto kern = ra.t ? (in.identity ? reduce_pp_timed_kernel<DT, true> : reduce_pp_timed_kernel<DT, false>)
                          : (in.identity ? reduce_pp_records_kernel<DT, true> : reduce_pp_records_kernel<DT, false>);
         hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(kBlock), 0, st, tr, in, ra, rec, io);
+        if (!ra.t && (io.grad_basis || io.grad_basis_g))
+            hipLaunchKernelGGL(basis_finish_kernel, dim3(1), dim3(kWave), 0, st, tr, in, ra.t_scalar, rec, pp::C,
+                               io.grad_basis, pp::CG, io.grad_basis_g);
         e = hipGetLastError();
     }
     return adjoint_end(sc, e, st);

@@ -99,8 +99,9 @@ def render_backward(tree: VOctree, ray_o, ray_d, rgb, alpha, nsamp, grad_rgb, gr
     _arg("nsamp", nsamp, torch.int32, shape=(n,))
     _arg("grad_rgb", grad_rgb, shape=(n, 3))
     _arg("grad_alpha", grad_alpha, shape=(n,), optional=True)
-    if grads is None:
-        grads = tree.zero_grads()
+    fresh = grads is None
+    if fresh:   # the call writes every leaf row; only the basis gradients start at zero
+        grads = tree.zero_grads(leaf_rows=False)
     gl, gb = grads[0], grads[1]
     gbg = grads[2] if tree.Cg > 0 else None
     _arg("grad_leaf", gl, shape=(tree.n_leaves, tree.grad_row))
@@ -111,6 +112,12 @@ def render_backward(tree: VOctree, ray_o, ray_d, rgb, alpha, nsamp, grad_rgb, gr
     if trace is not None:
         if trace.n_rays != n:
             raise ValueError(f"the trace was made for {trace.n_rays} rays, not {n}")
+    if fresh:
+        _lib.neuvv_render_backward_fresh(tree.struct(), inst, n, ray_o, ray_d, ray_t, t_scalar, image_width, t_stop, rgb,
+                                         alpha, nsamp, grad_rgb, grad_alpha, gl, gb if want_basis else None,
+                                         gbg if want_basis else None, None if trace is None else trace.buf,
+                                         0 if trace is None else trace.cap, stream)
+    elif trace is not None:
         _lib.neuvv_render_backward_trace(tree.struct(), inst, ray_o.shape[0], ray_o, ray_d, ray_t, t_scalar,
                                          image_width, t_stop, rgb, alpha, nsamp, grad_rgb, grad_alpha, gl,
                                          gb if want_basis else None, gbg if want_basis else None, trace.buf,

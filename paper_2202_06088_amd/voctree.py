@@ -148,11 +148,12 @@ class VOctree:
     def grad_row(self) -> int:
         return _lib.neuvv_grad_row_elems(self.K, self.C, self.Cg)
 
-    def zero_grads(self):
+    def zero_grads(self, leaf_rows: bool = True):
         """Zeroed float32 gradient buffers: leaf rows [N, ROW] and the basis [T, C] (and the
-        hyperangle basis [T, Cg] for the per-point form)."""
+        hyperangle basis [T, Cg] for the per-point form). leaf_rows=False leaves the rows
+        uninitialised, for a call that writes every one."""
         dev = self.nodes.device
-        g = (torch.zeros(self.n_leaves, self.grad_row, dtype=torch.float32, device=dev),
+        g = ((torch.zeros if leaf_rows else torch.empty)(self.n_leaves, self.grad_row, dtype=torch.float32, device=dev),
              torch.zeros(self.T, self.C, dtype=torch.float32, device=dev))
         if self.Cg > 0:
             g = g + (torch.zeros(self.T, self.Cg, dtype=torch.float32, device=dev),)

@@ -11,7 +11,7 @@ import torch
 from gpu_util import announce, oracle_render, rel_err, stop_ambiguous, tdev, tiny_camera, upload
 from oracle import core as OC
 from paper_2202_06088_amd import _lib, ops
-from workloads import make_scene_per_point, scene_for_workload
+from workloads import make_scene, make_scene_per_point, scene_for_workload
 
 pytestmark = pytest.mark.gpu
 
@@ -173,3 +173,37 @@ def test_cull_segments(tiny, width, n, traced):
         assert torch.equal(a, b)
     for a, b in zip(got[0][4:], got[1][4:]):
         assert rel_err(a.cpu().numpy(), b.cpu().numpy()) <= 1e-5
+
+
+@pytest.mark.parametrize("form", ["global", "wide", "per_point"])
+@pytest.mark.parametrize("timed", [False, True])
+@pytest.mark.parametrize("records", [None, "0", "1", "9000"])
+def test_fresh_gradients(form, timed, records, monkeypatch):
+    """Gradient rows written by the call itself (the buffer starts as NaN) are those that a call adds to a cleared
+    buffer, with room for every record, for some and for none, traced, partly traced and walked, and for no rays."""
+    if records is None:
+        monkeypatch.delenv("NEUVV_BWD_RECORDS", raising=False)
+    else:
+        monkeypatch.setenv("NEUVV_BWD_RECORDS", records)
+    sc = make_scene_per_point(5, 3000, "random", T=12, seed=7) if form == "per_point" else \
+        make_scene(5, 3001, "random", K=30 if form == "wide" else 16, C=31 if form == "wide" else 8, T=12, seed=8)
+    tree, cam = upload(sc), tiny_camera(sc)
+    o, d = (tdev(v) for v in OC.pinhole_rays(64, 64, cam.intr(), cam.c2w))
+    n, rng = o.shape[0], np.random.default_rng(81)
+    t = tdev(rng.uniform(0, sc.T - 1, n)) if timed else 3.25
+    g = tdev(rng.normal(size=(n, 3)))
+    for m, cap in ((n, None), (n, 0), (n, 900), (n, 64 * n), (0, None)):
+        tt = t[:m].contiguous() if timed else t
+        trace = None if cap is None else ops.Trace(m, cap, o.device)
+        rgb, alpha, _, ns = ops.render(tree, o[:m], d[:m], tt, None, 1e-4, 64, trace=trace)
+        want = ops.render_backward(tree, o[:m], d[:m], rgb, alpha, ns, g[:m], None, tt, None, 1e-4, 64,
+                                   grads=tree.zero_grads(), trace=trace)
+        got = tree.zero_grads()
+        got[0].fill_(float("nan"))
+        _lib.neuvv_render_backward_fresh(tree.struct(), None, m, o, d, tt if timed else None, 0.0 if timed else tt, 64,
+                                         1e-4, rgb, alpha, ns, g, None, got[0], got[1], got[2] if tree.Cg else None,
+                                         None if trace is None else trace.buf, 0 if trace is None else trace.cap)
+        torch.cuda.synchronize()
+        for a, b in zip(got, want):
+            assert rel_err(a.cpu().numpy(), b.cpu().numpy()) <= 1e-5   # summation order of float32 atomics
+        assert m == 0 or float(want[0].abs().max()) > 0
