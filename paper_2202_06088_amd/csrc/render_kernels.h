@@ -914,7 +914,7 @@ __global__ __launch_bounds__(kBlock) void reduce_records_kernel(TreeArgs tr, Ins
                     if (c < 3 * K || (!COMMON_T && c < R)) v = s_row[wv][q][c];
                     else if (COMMON_T && c < R) v = sgx * s_bc[c - 3 * K];
                     float* at = grad_leaf + (int64_t)L * ROW + c;
-                    if (fresh) *at = v;
+                    if (fresh) store_row_value(at, v);
                     else if (c < R) unsafeAtomicAdd(at, v);
                 }
                 if (grad_basis && lane < C) bacc = fma((double)sgx, (double)s_row[wv][q][NA + 1 + lane], bacc);
@@ -986,27 +986,14 @@ static hipError_t bwd_t(const TreeArgs& tr, const InstArgs& in, const RayArgs& r
     if (e == hipSuccess) e = bwd_walk<K, C, DT>(tr, in, sc.walk, io, rec, st);
     if (e == hipSuccess && io.trace.head) e = bwd_replay<K, C, DT>(tr, in, sc.replay, io, rec, st);
     if (e == hipSuccess && cap > 0) {
-        // persistent: four blocks per CU
-        int64_t blocks = (tr.n_leaves + kBlock - 1) / kBlock;
-        const int64_t lim = (int64_t)device_cu_count() * 4;
-        if (blocks > lim) blocks = lim;
-        const dim3 grid((unsigned)blocks);
-        if (ra.t == nullptr) {
-            if (in.identity)
-                hipLaunchKernelGGL((reduce_records_kernel<K, C, DT, true, true>), grid, dim3(kBlock), 0, st, tr, in,
-                                   ra, rec, io.grad_leaf, io.grad_basis, io.fresh);
-            else
-                hipLaunchKernelGGL((reduce_records_kernel<K, C, DT, false, true>), grid, dim3(kBlock), 0, st, tr, in,
-                                   ra, rec, io.grad_leaf, io.grad_basis, io.fresh);
-        } else {
-            if (in.identity)
-                hipLaunchKernelGGL((reduce_records_kernel<K, C, DT, true, false>), grid, dim3(kBlock), 0, st, tr, in,
-                                   ra, rec, io.grad_leaf, nullptr, io.fresh);
-            else
-                hipLaunchKernelGGL((reduce_records_kernel<K, C, DT, false, false>), grid, dim3(kBlock), 0, st, tr,
-                                   in, ra, rec, io.grad_leaf, nullptr, io.fresh);
-        }
-        if (ra.t == nullptr && io.grad_basis)
+        const bool common = ra.t == nullptr;
+        auto kern = common ? (in.identity ? reduce_records_kernel<K, C, DT, true, true>
+                                          : reduce_records_kernel<K, C, DT, false, true>)
+                           : (in.identity ? reduce_records_kernel<K, C, DT, true, false>
+                                          : reduce_records_kernel<K, C, DT, false, false>);
+        hipLaunchKernelGGL(kern, dim3(leaf_grid(kern, tr.n_leaves)), dim3(kBlock), 0, st, tr, in, ra, rec, io.grad_leaf,
+                           common ? io.grad_basis : nullptr, io.fresh);
+        if (common && io.grad_basis)
             hipLaunchKernelGGL(basis_finish_kernel, dim3(1), dim3(kWave), 0, st, tr, in, ra.t_scalar, rec, C,
                                io.grad_basis, 0, nullptr);
         e = hipGetLastError();

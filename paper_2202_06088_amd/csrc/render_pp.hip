@@ -807,12 +807,7 @@ __global__ __launch_bounds__(kBlock) void reduce_pp_records_kernel(TreeArgs tr, 
         if (first >= 0) {
             ra0 = rec.rec[2 * (int64_t)first];
             ra1 = rec.rec[2 * (int64_t)first + 1];
-            float gv[CG];
-            load_leaf<DT, CG>(tr.wgam, tr.n_leaves, leaf, tr.layout, gv);
-            float y = 0.0f;
-#pragma unroll
-            for (int c = 0; c < CG; ++c) y = fmaf(gv[c], s_bgrow[c], y);
-            const float gam = kPi * sigmoid_f(y);
+            const float gam = kPi * sigmoid_f(__int_as_float(ra1.w));   // (the leaf's y is in each of its records)
             float sn, cs, dg[6];
             sincosf(gam, &sn, &cs);
             radial_n2(sn, cs, g, dg);
@@ -883,7 +878,7 @@ __global__ __launch_bounds__(kBlock) void reduce_pp_records_kernel(TreeArgs tr, 
                     if (c < 3 * K) v = s_row[wv][q][c];
                     else if (c < 3 * K + C) v = sgx * s_brow[c - 3 * K];
                     else if (c < 3 * K + C + CG) v = sgy * s_bgrow[c - 3 * K - C];
-                    if (fresh) row[c] = v;
+                    if (fresh) store_row_value(row + c, v);
                     else if (c < 3 * K + C + CG) unsafeAtomicAdd(row + c, v);
                 }
                 if (lane < C) bacc[0] = fma((double)sgx, (double)s_row[wv][q][R + lane], bacc[0]);
@@ -987,7 +982,7 @@ __global__ __launch_bounds__(kBlock) void reduce_pp_timed_kernel(TreeArgs tr, In
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
                 const int c = pp_component(j, lane);
-                if (fresh) row[c] = acc[j];   // (acc is 0 in the padding)
+                if (fresh) store_row_value(row + c, acc[j]);   // (acc is 0 in the padding)
                 else if (c < 3 * K + C + CG) unsafeAtomicAdd(row + c, acc[j]);
             }
         }
@@ -1045,12 +1040,9 @@ static hipError_t pp_bwd_t(const TreeArgs& tr, const InstArgs& in, const RayArgs
     if (e == hipSuccess) e = pp_bwd_walk<DT>(tr, in, sc.walk, io, rec, st);
     if (e == hipSuccess && io.trace.head) e = pp_bwd_replay<DT>(tr, in, sc.replay, io, rec, st);
     if (e == hipSuccess && cap > 0) {
-        int64_t blocks = (tr.n_leaves + kBlock - 1) / kBlock;
-        const int64_t lim = (int64_t)device_cu_count() * (ra.t ? 8 : 4);
-        if (blocks > lim) blocks = lim;
         auto kern = ra.t ? (in.identity ? reduce_pp_timed_kernel<DT, true> : reduce_pp_timed_kernel<DT, false>)
                          : (in.identity ? reduce_pp_records_kernel<DT, true> : reduce_pp_records_kernel<DT, false>);
-        hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(kBlock), 0, st, tr, in, ra, rec, io);
+        hipLaunchKernelGGL(kern, dim3(leaf_grid(kern, tr.n_leaves)), dim3(kBlock), 0, st, tr, in, ra, rec, io);
         if (!ra.t && (io.grad_basis || io.grad_basis_g))
             hipLaunchKernelGGL(basis_finish_kernel, dim3(1), dim3(kWave), 0, st, tr, in, ra.t_scalar, rec, pp::C,
                                io.grad_basis, pp::CG, io.grad_basis_g);
