@@ -14,8 +14,9 @@
  *     keeps no pointer after a call returns. The only device memory it
  *     allocates is per-call scratch of the render calls: neuvv_render,
  *     neuvv_render_trace, neuvv_render_multi, neuvv_render_backward,
- *     neuvv_render_backward_trace and neuvv_find_terminal_leaves take 2 KiB
- *     of work-queue counters plus a candidate list of 4 bytes per work slot
+ *     neuvv_render_backward_trace, neuvv_render_backward_fresh and
+ *     neuvv_find_terminal_leaves take 2 KiB of work-queue counters (the
+ *     adjoints 5 KiB) plus a candidate list of 4 bytes per work slot
  *     (rounded up to 64 slots; the adjoint of a traced forward takes two);
  *     the adjoints also take the records of their two-phase reduction (4
  *     bytes per leaf plus 32 bytes per record of room, see there), and

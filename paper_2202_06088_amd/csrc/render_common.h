@@ -775,24 +775,35 @@ __device__ __forceinline__ LeafFeeder leaf_feeder(int wave_in_block) {
     return f;
 }
 
-// Gradient rows are stored non-temporally: nothing of the call reads them again,
-// and what they would push out of L2 are the lines of records that a wavefront's
-// lists share (per-point step's reduction of 1 GB of rows 442 -> 419 us, that
-// of a 30-coefficient step 170 -> 153 us, the ring's 413 -> 403 us).
-__device__ __forceinline__ void store_row_value(float* at, float v) { __builtin_nontemporal_store(v, at); }
-__device__ __forceinline__ void store_row4_zero(float4* at) {
+// Gradient rows of calls with one time for every ray are stored non-temporally:
+// what they would push out of L2 are the lines of records that a wavefront's
+// lists share (per-point step's reduction of 1 GB of rows 442 -> 419 us, the
+// ring's of 512 MB 413 -> 403 us, 256 MB of 30 coefficients 149 -> 127 us). A
+// training batch with a time per ray touches few rows and reads them next: kept
+// in the caches, its reduction takes 36 instead of 35 us, the unpacking after it
+// 34 instead of 48 us. Zero rows follow the size of all rows: what the 256 MB
+// last-level cache can hold with what follows is stored as usual.
+constexpr int64_t kStreamRows = 192ll << 20;
+template <bool STREAM>
+__device__ __forceinline__ void store_row_value(float* at, float v) {
+    if constexpr (STREAM) __builtin_nontemporal_store(v, at);
+    else *at = v;
+}
+__device__ __forceinline__ void store_row4_zero(float4* at, bool stream) {
     typedef float v4 __attribute__((ext_vector_type(4)));
-    __builtin_nontemporal_store(v4{0.0f, 0.0f, 0.0f, 0.0f}, reinterpret_cast<v4*>(at));
+    if (stream) __builtin_nontemporal_store(v4{0.0f, 0.0f, 0.0f, 0.0f}, reinterpret_cast<v4*>(at));
+    else *at = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
 }
 
 // Writes zero rows of ROW floats for the leaves of the batch at b0 whose bit is
 // set in m: sixteen bytes per lane, whole rows per instruction.
 template <int ROW>
-__device__ __forceinline__ void zero_batch_rows(float* rows, int64_t b0, uint64_t m) {
+__device__ __forceinline__ void zero_batch_rows(float* rows, int64_t b0, uint64_t m, int64_t n_leaves) {
     constexpr int per = ROW / 4;   // float4 per row
+    const bool stream = n_leaves * (int64_t)(ROW * sizeof(float)) > kStreamRows;
     float4* p = reinterpret_cast<float4*>(rows + b0 * ROW);
     for (int i = threadIdx.x & 63; i < kWave * per; i += kWave)
-        if ((m >> (i / per)) & 1ull) store_row4_zero(p + i);
+        if ((m >> (i / per)) & 1ull) store_row4_zero(p + i, stream);
 }
 
 // Gives idle lanes (leaf < 0) a leaf and its first record while leaves are left.
@@ -815,7 +826,7 @@ __device__ __forceinline__ void feed_leaves(LeafFeeder& f, const RecordArgs& rec
             const int64_t L = b0 + lane;
             const int h = L < n_leaves ? rec.head[L] : -1;
             const uint64_t m = __ballot(h >= 0);
-            if (fresh) zero_batch_rows<ROW>(rows, b0, __ballot(L < n_leaves) & ~m);
+            if (fresh) zero_batch_rows<ROW>(rows, b0, __ballot(L < n_leaves) & ~m, n_leaves);
             __builtin_amdgcn_wave_barrier();
             if (h >= 0) q[lane_rank(m)] = make_int2((int)L, h);
             __builtin_amdgcn_wave_barrier();

@@ -914,7 +914,7 @@ __global__ __launch_bounds__(kBlock) void reduce_records_kernel(TreeArgs tr, Ins
                     if (c < 3 * K || (!COMMON_T && c < R)) v = s_row[wv][q][c];
                     else if (COMMON_T && c < R) v = sgx * s_bc[c - 3 * K];
                     float* at = grad_leaf + (int64_t)L * ROW + c;
-                    if (fresh) store_row_value(at, v);
+                    if (fresh) store_row_value<COMMON_T>(at, v);
                     else if (c < R) unsafeAtomicAdd(at, v);
                 }
                 if (grad_basis && lane < C) bacc = fma((double)sgx, (double)s_row[wv][q][NA + 1 + lane], bacc);

@@ -878,7 +878,7 @@ __global__ __launch_bounds__(kBlock) void reduce_pp_records_kernel(TreeArgs tr, 
                     if (c < 3 * K) v = s_row[wv][q][c];
                     else if (c < 3 * K + C) v = sgx * s_brow[c - 3 * K];
                     else if (c < 3 * K + C + CG) v = sgy * s_bgrow[c - 3 * K - C];
-                    if (fresh) store_row_value(row + c, v);
+                    if (fresh) store_row_value<true>(row + c, v);
                     else if (c < 3 * K + C + CG) unsafeAtomicAdd(row + c, v);
                 }
                 if (lane < C) bacc[0] = fma((double)sgx, (double)s_row[wv][q][R + lane], bacc[0]);
@@ -915,7 +915,7 @@ __global__ __launch_bounds__(kBlock) void reduce_pp_timed_kernel(TreeArgs tr, In
         const int64_t own = b * kWave + lane;
         const int first = own < N ? rec.head[own] : -1;
         const uint64_t listed = __ballot(first >= 0);
-        if (fresh) zero_batch_rows<ROW>(io.grad_leaf, b * kWave, __ballot(own < N) & ~listed);
+        if (fresh) zero_batch_rows<ROW>(io.grad_leaf, b * kWave, __ballot(own < N) & ~listed, N);
         for (uint64_t m = listed; m; m &= m - 1) {
             const int src = __builtin_ctzll(m);
             const int64_t L = b * kWave + src;
@@ -982,7 +982,7 @@ __global__ __launch_bounds__(kBlock) void reduce_pp_timed_kernel(TreeArgs tr, In
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
                 const int c = pp_component(j, lane);
-                if (fresh) store_row_value(row + c, acc[j]);   // (acc is 0 in the padding)
+                if (fresh) store_row_value<false>(row + c, acc[j]);   // (acc is 0 in the padding)
                 else if (c < 3 * K + C + CG) unsafeAtomicAdd(row + c, acc[j]);
             }
         }
