@@ -48,7 +48,7 @@ def kernel_source_hash(workload: str) -> str:
     left out (a comment edit does not change the kernels)."""
     main = "render_pp.hip" if workload.endswith("per_point") else "render_kernels.h"
     h = hashlib.sha256()
-    for f in (main, "render_common.h", "neuvv_device.h"):
+    for f in (main, "render_common.h", "neuvv_device.h", "room.h"):
         with open(os.path.join(ROOT, "paper_2202_06088_amd", "csrc", f), encoding="utf-8") as fh:
             text = re.sub(r"/\*.*?\*/", "", fh.read(), flags=re.S)
         lines = [ln.split("//", 1)[0].rstrip() for ln in text.splitlines()]

@@ -9,6 +9,7 @@
 
 #include "launch.h"
 #include "neuvv_device.h"
+#include "room.h"
 
 namespace neuvv {
 
@@ -624,38 +625,20 @@ static __global__ void adjoint_init_kernel(unsigned long long* hdr, int n_hdr, i
     if (i < n_hdr) hdr[i] = 0ull;
 }
 
-// Items a wavefront takes from the room's counter at a time: a 16,384th of the
-// room, between 128 (the most that one iteration of a wavefront asks for) and
-// 2048. The rest of a wavefront's last block stays unused, so the block is kept
-// small against the room's share per wavefront; the floor of 16,384 blocks also
-// bounds the atomics on the one counter (12 thousand on the 16.6 M-ray ring).
-// Blocks of 2048 from one counter per XCD left 38 % of the ring's trace room
-// unused and, in rooms below 2 M items, let 8 wavefronts per XCD exhaust it: the
-// rays left over were walked again (65,536 training rays with room for two
-// samples each: 222 us of 717 us; 4 layers at 1920 x 1080: 1462 us of 4247 us).
-__device__ __forceinline__ int item_block(int64_t cap) {
-    const int b = (int)(cap >> 14);
-    return b < 128 ? 128 : (b > 2048 ? 2048 : b);
-}
-
 // Wave-uniform allocation of n (<= 128) consecutive items of a room of cap
 // items, out of blocks taken from its counter. [cur, end) is what is left of
 // the wavefront's current block, end = -1 once the room is exhausted. Returns
 // the first item, or -1 when there is no room. A request that fails has left
 // the counter above cap. Call with every lane of the wavefront active.
 __device__ __forceinline__ int take_items(unsigned long long* counter, int64_t cap, int n, int& cur, int& end) {
-    if (cur + n > end) {
+    if (!items_fit(cur, end, n)) {
         if (end < 0) return -1;
-        const int block = item_block(cap);
         unsigned long long b = 0;
-        if ((threadIdx.x & 63) == 0) b = atomicAdd(counter, (unsigned long long)block);
+        if ((threadIdx.x & 63) == 0) b = atomicAdd(counter, (unsigned long long)item_block(cap));
         const uint32_t b_lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b);
         const uint32_t b_hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32));
-        const int64_t first = (int64_t)(((uint64_t)b_hi << 32) | b_lo);
-        // the room is below 2^31 items, so the block's bounds fit int32 once clamped to it
-        cur = (int)(first < cap ? first : cap);
-        end = (int)(first + block <= cap ? first + block : cap);
-        if (cur + n > end) {
+        open_block((int64_t)(((uint64_t)b_hi << 32) | b_lo), cap, cur, end);
+        if (!items_fit(cur, end, n)) {
             end = -1;
             return -1;
         }
