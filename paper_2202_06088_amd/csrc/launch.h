@@ -53,7 +53,7 @@ struct BackwardIO {
 // into its leaf's list; a second pass sums each leaf's list into its
 // gradient row (one row addition per leaf instead of one per sample).
 struct RecordArgs {
-    int32_t* head;                 // [n_leaves] first record of the leaf's list, -1: none
+    int32_t* head;                 // [2^split][n_leaves] first record of the list, -1: none
     int4* rec;                     // [cap][2]: {dL/dz_r, dL/dz_g, dL/dz_b, dL/dx} (float bits),
                                    //           {next record of the same leaf (-1: end), ray, 0, 0};
                                    // K = 16, C = 8 form with one time for every ray: {next, ray
@@ -63,6 +63,7 @@ struct RecordArgs {
                                         // same for the rays that replay (the cull pass fills them)
     double* basis_sum;             // [64] the reduction's basis gradients (one time for every ray)
     int32_t max_waves;             // wavefronts that one kernel of the call can have on the device at once
+    int32_t split;                 // log2 of the lists a leaf has (record_list), head holds n_leaves << split
     int64_t cap;
 };
 

@@ -293,13 +293,14 @@ static int grid_for(KernelT kernel, const RayArgs& ra) {
 // Blocks of a reduction over the leaves, persistent: as many as are resident
 // (where three fit, a fourth that had to wait for its place made the per-point
 // reduction take 419 instead of 367 us, that of 30 coefficients 153 instead of
-// 127 us), no more than its wavefronts have batches.
+// 127 us), no more than its wavefronts have batches of at least `least` leaves.
 template <typename KernelT>
-static int leaf_grid(KernelT kernel, int64_t n_leaves) {
+static int leaf_grid(KernelT kernel, int64_t n_leaves, int least = kWave) {
     int per_cu = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kBlock, 0) != hipSuccess || per_cu <= 0)
         per_cu = 2;
-    const int64_t want = (n_leaves + kBlock - 1) / kBlock, cap = (int64_t)per_cu * device_cu_count();
+    const int64_t per_block = (int64_t)(kBlock / kWave) * least;
+    const int64_t want = (n_leaves + per_block - 1) / per_block, cap = (int64_t)per_cu * device_cu_count();
     return (int)(want < cap ? want : cap);
 }
 
@@ -676,15 +677,24 @@ __device__ __forceinline__ RecordRun record_run(uint64_t hm, bool has, int leaf)
     return r;
 }
 
+// The list that the records of one iteration, the first of which is `at`, join
+// for a leaf: the leaf's only one, or one of 2^split picked by the record's
+// index, so that the records of a leaf spread over all of them.
+__device__ __forceinline__ int64_t record_list(const RecordArgs& rec, int64_t n_leaves, int leaf, int at) {
+    if (rec.split == 0) return leaf;
+    return (int64_t)(((uint32_t)at * 0x9E3779B1u) >> (32 - rec.split)) * n_leaves + leaf;
+}
+
 // Whether every sample of the call is sure to get a record: the samples and
 // rays the cull pass counted, an unused block for every wavefront that takes
 // rays (of the persistent grids of the walk and the replay: no more than chunks
 // of rays), and the up to 63 items that a request leaves behind at a block's end. Then nothing is scattered, and a call that
 // writes its gradient rows (fresh) may leave them uninitialised until the
 // reduction stores them, each once; else they are cleared before anything is
-// added. The same answer for every thread of the call's kernels.
+// added. So they are where a leaf's records are in several lists, each of which
+// adds to the row. The same answer for every thread of the call's kernels.
 __device__ __forceinline__ bool records_fit(const RecordArgs& rec) {
-    if (!rec.head) return false;
+    if (!rec.head || rec.split > 0) return false;
     int64_t samples = 0, waves = 0;
 #pragma unroll
     for (int list = 0; list < 2; ++list) {
@@ -778,14 +788,16 @@ __device__ __forceinline__ void store_row4_zero(float4* at, bool stream) {
     else *at = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
 }
 
-// Writes zero rows of ROW floats for the leaves of the batch at b0 whose bit is
-// set in m: sixteen bytes per lane, whole rows per instruction.
+// Writes zero rows of ROW floats for the leaves of the batch at b0 (of up to
+// `batch` leaves) whose bit is set in m: sixteen bytes per lane, whole rows per
+// instruction.
 template <int ROW>
-__device__ __forceinline__ void zero_batch_rows(float* rows, int64_t b0, uint64_t m, int64_t n_leaves) {
+__device__ __forceinline__ void zero_batch_rows(float* rows, int64_t b0, uint64_t m, int64_t n_leaves,
+                                                int batch = kWave) {
     constexpr int per = ROW / 4;   // float4 per row
     const bool stream = n_leaves * (int64_t)(ROW * sizeof(float)) > kStreamRows;
     float4* p = reinterpret_cast<float4*>(rows + b0 * ROW);
-    for (int i = threadIdx.x & 63; i < kWave * per; i += kWave)
+    for (int i = threadIdx.x & 63; i < batch * per; i += kWave)
         if ((m >> (i / per)) & 1ull) store_row4_zero(p + i, stream);
 }
 
@@ -844,7 +856,7 @@ struct AdjointScratch {
 };
 struct NoHit {};
 static hipError_t adjoint_begin(const TreeArgs& tr, const RayArgs& ra, const int32_t* nsamp, const int32_t* trace_head,
-                                int64_t cap, hipStream_t st, AdjointScratch& s) {
+                                int64_t cap, hipStream_t st, AdjointScratch& s, int split = 0) {
     s = AdjointScratch{ra, ra, RecordArgs{}, nullptr};
     const bool listed = ra.n <= (int64_t)INT32_MAX;   // else the slot form: the walking kernel tests every ray
     if (trace_head && !listed) return hipErrorInvalidValue;
@@ -853,7 +865,8 @@ static hipError_t adjoint_begin(const TreeArgs& tr, const RayArgs& ra, const int
     constexpr size_t hdr = ((size_t)n_hdr * sizeof(unsigned long long) + 255) & ~(size_t)255;
     const size_t list_b = listed ? (size_t)((ra.n_slots + 63) >> 6) * 64 * sizeof(int32_t) : 0;
     const size_t lists = trace_head ? 2 * list_b : list_b;
-    const size_t head_b = cap > 0 ? ((size_t)tr.n_leaves * sizeof(int32_t) + 255) & ~(size_t)255 : 0;
+    const int64_t n_heads = cap > 0 ? tr.n_leaves << split : 0;
+    const size_t head_b = ((size_t)n_heads * sizeof(int32_t) + 255) & ~(size_t)255;
     hipError_t e = work_alloc(&s.mem, hdr + lists + head_b + (size_t)(cap > 0 ? cap : 0) * 2 * sizeof(int4), st);
     if (e != hipSuccess) {
         s.mem = nullptr;
@@ -872,11 +885,12 @@ static hipError_t adjoint_begin(const TreeArgs& tr, const RayArgs& ra, const int
         s.rec.max_waves = device_cu_count() * 32;
         s.rec.head = reinterpret_cast<int32_t*>(p + hdr + lists);
         s.rec.rec = reinterpret_cast<int4*>(p + hdr + lists + head_b);
+        s.rec.split = split;
         s.rec.cap = cap;
     }
-    const int64_t n_init = cap > 0 && tr.n_leaves > n_hdr ? tr.n_leaves : n_hdr;
+    const int64_t n_init = n_heads > n_hdr ? n_heads : n_hdr;
     hipLaunchKernelGGL(adjoint_init_kernel, dim3((unsigned)((n_init + 255) / 256)), dim3(256), 0, st, counters, n_hdr,
-                       s.rec.head, cap > 0 ? tr.n_leaves : 0);
+                       s.rec.head, n_heads);
     e = hipGetLastError();
     if (e == hipSuccess && listed) {
         s.walk.list = list;

@@ -458,7 +458,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 8))) 
                         my_rec = (int)(at + lane_rank(hm));
                         rec.rec[2 * (int64_t)my_rec] =
                             make_int4(__float_as_int(gz0), __float_as_int(gz1), __float_as_int(gz2), __float_as_int(gx));
-                        const int nxt = run.count > 0 ? atomicExch(rec.head + leaf, my_rec + run.count - 1) : my_rec - 1;
+                        const int nxt = run.count > 0 ? atomicExch(rec.head + record_list(rec, tr.n_leaves, leaf, at), my_rec + run.count - 1) : my_rec - 1;
                         rec.rec[2 * (int64_t)my_rec + 1] = make_int4(nxt, (int)ray, __float_as_int(gy), __float_as_int(y));
                     }
                 }
@@ -677,7 +677,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) 
                         my_rec = at + lane_rank(hm);
                         rec.rec[2 * (int64_t)my_rec] =
                             make_int4(__float_as_int(gz0), __float_as_int(gz1), __float_as_int(gz2), __float_as_int(gx));
-                        const int nxt = run.count > 0 ? atomicExch(rec.head + leaf, my_rec + run.count - 1) : my_rec - 1;
+                        const int nxt = run.count > 0 ? atomicExch(rec.head + record_list(rec, tr.n_leaves, leaf, at), my_rec + run.count - 1) : my_rec - 1;
                         rec.rec[2 * (int64_t)my_rec + 1] = make_int4(nxt, ray, __float_as_int(gy), __float_as_int(y));
                     }
                 }
@@ -903,22 +903,43 @@ __global__ __launch_bounds__(kBlock) void reduce_pp_records_kernel(TreeArgs tr, 
 // basis rows). Without records such samples took the per-sample scatter, whose
 // reads are as many but one lane's after the other's: 15,360 rays of 31,484
 // samples took 3.6 ms.
+//
+// A wavefront works through its leaves and their lists one after the other, so
+// the work has to be spread before it is short: small trees have several lists
+// per leaf (timed_split), each added to the row, and a wavefront takes batches
+// of as many lists as leave it eight batches. With one list per leaf and batches
+// of 64, training steps of 262,144 rays on trees of 1,000 and 4,000 leaves took
+// 18.1 and 5.3 ms (16 and 62 wavefronts; 1.7 and 2.1 ms with the scatter), now
+// 0.48 and 0.50 ms; on 60,000 and 500,000 leaves 1.46 -> 0.75 and 1.05 -> 0.93 ms.
+constexpr int64_t kTimedLists = 65536;
+constexpr int64_t kTimedBatches = 8;
+// log2 of the lists per leaf: kTimedLists lists in all, and not many more than a
+// small call has samples.
+static int timed_split(int64_t n_leaves, int64_t n_rays) {
+    const int64_t want = 4 * n_rays < kTimedLists ? 4 * n_rays : kTimedLists;
+    int s = 0;
+    while (n_leaves << s < want) ++s;
+    return s;
+}
+
 template <int DT, bool IDENT>
 __global__ __launch_bounds__(kBlock) void reduce_pp_timed_kernel(TreeArgs tr, InstArgs in, RayArgs ra, RecordArgs rec,
                                                                  BackwardIO io) {
     using namespace pp;
     __shared__ float s_h[kBlock / kWave][K];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int64_t N = tr.n_leaves, n_waves = (int64_t)gridDim.x * (kBlock / kWave);
+    const int64_t N = tr.n_leaves, lists = N << rec.split, n_waves = (int64_t)gridDim.x * (kBlock / kWave);
     const bool fresh = io.fresh && records_fit(rec);   // rows are stored; else added to
-    for (int64_t b = (int64_t)blockIdx.x * (kBlock / kWave) + wv; b * kWave < N; b += n_waves) {
-        const int64_t own = b * kWave + lane;
-        const int first = own < N ? rec.head[own] : -1;
+    const int64_t share = lists / (kTimedBatches * n_waves);
+    const int batch = share < 1 ? 1 : (share > kWave ? kWave : (int)share);
+    for (int64_t b = ((int64_t)blockIdx.x * (kBlock / kWave) + wv) * batch; b < lists; b += n_waves * batch) {
+        const bool mine = lane < batch && b + lane < lists;
+        const int first = mine ? rec.head[b + lane] : -1;
         const uint64_t listed = __ballot(first >= 0);
-        if (fresh) zero_batch_rows<ROW>(io.grad_leaf, b * kWave, __ballot(own < N) & ~listed, N);
+        if (fresh) zero_batch_rows<ROW>(io.grad_leaf, b, __ballot(mine) & ~listed, N, batch);
         for (uint64_t m = listed; m; m &= m - 1) {
             const int src = __builtin_ctzll(m);
-            const int64_t L = b * kWave + src;
+            const int64_t L = rec.split ? (int64_t)((uint32_t)(b + src) % (uint32_t)N) : b + src;   // (split: few lists)
             int r = __builtin_amdgcn_readlane(first, src);
             float wl[2] = {0.0f, 0.0f}, acc[2] = {0.0f, 0.0f};   // the component's weight, its sum
 #pragma unroll
@@ -1034,7 +1055,7 @@ static hipError_t pp_bwd_t(const TreeArgs& tr, const InstArgs& in, const RayArgs
     const int64_t cap =
         ra.n <= (int64_t)INT32_MAX && tr.n_leaves > 0 && tr.n_leaves <= (int64_t)INT32_MAX ? io.record_cap : 0;
     AdjointScratch sc;
-    hipError_t e = adjoint_begin(tr, ra, io.nsamp, io.trace.head, cap, st, sc);
+    hipError_t e = adjoint_begin(tr, ra, io.nsamp, io.trace.head, cap, st, sc, ra.t && cap > 0 ? timed_split(tr.n_leaves, ra.n) : 0);
     const RecordArgs& rec = sc.rec;
     if (e == hipSuccess && io.fresh) e = fresh_begin(tr, io, pp::ROW, rec, st);
     if (e == hipSuccess) e = pp_bwd_walk<DT>(tr, in, sc.walk, io, rec, st);
@@ -1042,7 +1063,8 @@ static hipError_t pp_bwd_t(const TreeArgs& tr, const InstArgs& in, const RayArgs
     if (e == hipSuccess && cap > 0) {
         auto kern = ra.t ? (in.identity ? reduce_pp_timed_kernel<DT, true> : reduce_pp_timed_kernel<DT, false>)
                          : (in.identity ? reduce_pp_records_kernel<DT, true> : reduce_pp_records_kernel<DT, false>);
-        hipLaunchKernelGGL(kern, dim3(leaf_grid(kern, tr.n_leaves)), dim3(kBlock), 0, st, tr, in, ra, rec, io);
+        const int grid = ra.t ? leaf_grid(kern, tr.n_leaves << rec.split, 1) : leaf_grid(kern, tr.n_leaves);
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(kBlock), 0, st, tr, in, ra, rec, io);
         if (!ra.t && (io.grad_basis || io.grad_basis_g))
             hipLaunchKernelGGL(basis_finish_kernel, dim3(1), dim3(kWave), 0, st, tr, in, ra.t_scalar, rec, pp::C,
                                io.grad_basis, pp::CG, io.grad_basis_g);

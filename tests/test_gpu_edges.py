@@ -207,3 +207,53 @@ def test_fresh_gradients(form, timed, records, monkeypatch):
         for a, b in zip(got, want):
             assert rel_err(a.cpu().numpy(), b.cpu().numpy()) <= 1e-5   # summation order of float32 atomics
         assert m == 0 or float(want[0].abs().max()) > 0
+
+
+@pytest.mark.parametrize("depth,leaves", [(2, 1), (3, 63), (3, 65), (5, 1000), (6, 16_383), (6, 16_384), (6, 16_385)])
+@pytest.mark.parametrize("traced", [False, True])
+def test_timed_reduction_lists(depth, leaves, traced):
+    """Per-point leaves with a time per ray: trees small enough for several record lists per leaf (below 16,384 leaves
+    for these 4,096 rays) and at the edge of that rule, for stored and for added rows; against the oracle."""
+    sc = make_scene_per_point(depth, leaves, "random", T=12, seed=9)
+    cam = tiny_camera(sc)
+    o, d = OC.pinhole_rays(64, 64, cam.intr(), cam.c2w)
+    n, rng = o.shape[0], np.random.default_rng(91)
+    t = rng.uniform(0, sc.T - 1, n).astype(np.float32)
+    g = rng.normal(size=(n, 3)).astype(np.float32)
+    g[stop_ambiguous(oracle_render(sc, o, d, t, 0.0, 1e-4, g_rgb=g), label="timed lists")] = 0.0
+    ref = oracle_render(sc, o, d, t, 0.0, 1e-4, g_rgb=g)
+    tree, oo, dd, tt = upload(sc), tdev(o), tdev(d), tdev(t)
+    trace = ops.Trace(n, 64 * n, oo.device) if traced else None
+    rgb, alpha, _, nsamp = ops.render(tree, oo, dd, tt, None, 1e-4, 64, trace=trace)
+    for grads in (None, tree.zero_grads()):
+        out = ops.render_backward(tree, oo, dd, rgb, alpha, nsamp, tdev(g), None, tt, None, 1e-4, 64, grads=grads,
+                                  trace=trace)
+        torch.cuda.synchronize()
+        hh, ws, wg = tree.unpack_grad(out[0])
+        got = dict(grad_hh=hh, grad_wsig=ws, grad_wgam=wg, grad_basis=out[1], grad_basis_g=out[2])
+        e = {k: rel_err(v.cpu().numpy(), ref[k]) for k, v in got.items()}
+        announce(f"timed lists {depth} {leaves} {traced}: grad rel errors {e}")
+        assert max(e.values()) <= 1e-4, e
+
+
+def test_timed_reduction_small_tree_time(monkeypatch):
+    """262,144 rays with times of their own on 1,000 per-point leaves: the adjoint with records takes no longer than
+    half as much again as with none (the lists of a small tree once ran on 16 wavefronts and took ten times as long)."""
+    sc = make_scene_per_point(5, 1000, "random", T=12, seed=9)
+    cam = tiny_camera(sc)
+    o, d = (tdev(np.repeat(v, 64, 0)) for v in OC.pinhole_rays(64, 64, cam.intr(), cam.c2w))
+    n, rng, tree = o.shape[0], np.random.default_rng(92), upload(sc)
+    t, g = tdev(rng.uniform(0, sc.T - 1, n)), tdev(rng.normal(size=(n, 3)))
+    rgb, alpha, _, nsamp = ops.render(tree, o, d, t)
+    ms = {}
+    for records in ("4000000", "0"):
+        monkeypatch.setenv("NEUVV_BWD_RECORDS", records)
+        for _ in range(2):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            ops.render_backward(tree, o, d, rgb, alpha, nsamp, g, None, t)
+            b.record()
+            torch.cuda.synchronize()
+            ms[records] = a.elapsed_time(b)
+    announce(f"timed reduction of a small tree: {ms} ms, {int(nsamp.sum())} samples")
+    assert ms["4000000"] <= 1.5 * ms["0"], ms
