@@ -393,7 +393,8 @@ int neuvv_render_backward(const neuvv_tree* tree, const neuvv_instance* inst, in
  * evaluating the leaves again; the gradients are the same up to rounding. A
  * ray whose samples do not all fit is marked untraced and its adjoint walks
  * as in neuvv_render_backward, so any trace_cap >= 0 is correct (room near
- * the call's total of nsamp avoids walking).
+ * the call's total of nsamp avoids walking). Every ray walks where the records
+ * have less room than the trace (NEUVV_BWD_RECORDS).
  * trace           device buffer of neuvv_trace_bytes(n_rays, trace_cap) bytes,
  *                 256-byte aligned, owned by the caller; written by
  *                 neuvv_render_trace, read by neuvv_render_backward_trace, and

@@ -980,11 +980,12 @@ static hipError_t bwd_t(const TreeArgs& tr, const InstArgs& in, const RayArgs& r
     const int64_t cap =
         ra.n <= (int64_t)INT32_MAX && tr.n_leaves > 0 && tr.n_leaves <= (int64_t)INT32_MAX ? io.record_cap : 0;
     AdjointScratch sc;
-    hipError_t e = adjoint_begin(tr, ra, io.nsamp, io.trace.head, cap, st, sc);
+    const bool replay = replays(io.trace, io.trace.cap, cap);
+    hipError_t e = adjoint_begin(tr, ra, io.nsamp, replay ? io.trace.head : nullptr, cap, st, sc);
     const RecordArgs& rec = sc.rec;
     if (e == hipSuccess && io.fresh) e = fresh_begin(tr, io, grad_row<K, C>(), rec, st);
     if (e == hipSuccess) e = bwd_walk<K, C, DT>(tr, in, sc.walk, io, rec, st);
-    if (e == hipSuccess && io.trace.head) e = bwd_replay<K, C, DT>(tr, in, sc.replay, io, rec, st);
+    if (e == hipSuccess && replay) e = bwd_replay<K, C, DT>(tr, in, sc.replay, io, rec, st);
     if (e == hipSuccess && cap > 0) {
         const bool common = ra.t == nullptr;
         auto kern = common ? (in.identity ? reduce_records_kernel<K, C, DT, true, true>

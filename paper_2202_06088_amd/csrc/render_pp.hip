@@ -1055,11 +1055,13 @@ static hipError_t pp_bwd_t(const TreeArgs& tr, const InstArgs& in, const RayArgs
     const int64_t cap =
         ra.n <= (int64_t)INT32_MAX && tr.n_leaves > 0 && tr.n_leaves <= (int64_t)INT32_MAX ? io.record_cap : 0;
     AdjointScratch sc;
-    hipError_t e = adjoint_begin(tr, ra, io.nsamp, io.trace.head, cap, st, sc, ra.t && cap > 0 ? timed_split(tr.n_leaves, ra.n) : 0);
+    const bool replay = replays(io.trace, io.trace.cap / 2, cap);
+    hipError_t e = adjoint_begin(tr, ra, io.nsamp, replay ? io.trace.head : nullptr, cap, st, sc,
+                                 ra.t && cap > 0 ? timed_split(tr.n_leaves, ra.n) : 0);
     const RecordArgs& rec = sc.rec;
     if (e == hipSuccess && io.fresh) e = fresh_begin(tr, io, pp::ROW, rec, st);
     if (e == hipSuccess) e = pp_bwd_walk<DT>(tr, in, sc.walk, io, rec, st);
-    if (e == hipSuccess && io.trace.head) e = pp_bwd_replay<DT>(tr, in, sc.replay, io, rec, st);
+    if (e == hipSuccess && replay) e = pp_bwd_replay<DT>(tr, in, sc.replay, io, rec, st);
     if (e == hipSuccess && cap > 0) {
         auto kern = ra.t ? (in.identity ? reduce_pp_timed_kernel<DT, true> : reduce_pp_timed_kernel<DT, false>)
                          : (in.identity ? reduce_pp_records_kernel<DT, true> : reduce_pp_records_kernel<DT, false>);

@@ -257,3 +257,31 @@ def test_timed_reduction_small_tree_time(monkeypatch):
             ms[records] = a.elapsed_time(b)
     announce(f"timed reduction of a small tree: {ms} ms, {int(nsamp.sum())} samples")
     assert ms["4000000"] <= 1.5 * ms["0"], ms
+
+
+@pytest.mark.parametrize("records", ["0", "1000"])
+def test_traced_adjoint_without_room_for_records(tiny, records, monkeypatch):
+    """A traced adjoint that has records for few samples or none takes no longer than half as much again as the
+    untraced one (it once made a basis for every sample, one lane at a time, and took three times as long), and its
+    gradients are the oracle's."""
+    sc, o, d, g, ref = tiny
+    monkeypatch.setenv("NEUVV_BWD_RECORDS", records)
+    tree, rep = upload(sc), 64
+    oo, dd, gg = (tdev(np.repeat(v, rep, 0)) for v in (o, d, g))
+    n, ms = oo.shape[0], {}
+    trace = ops.Trace(n, 16 * n, oo.device)
+    rgb, alpha, _, nsamp = ops.render(tree, oo, dd, 4.0, trace=trace)
+    for name, tr in (("untraced", None), ("traced", trace)):
+        for _ in range(2):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            gl, gb = ops.render_backward(tree, oo, dd, rgb, alpha, nsamp, gg, None, 4.0, trace=tr)
+            b.record()
+            torch.cuda.synchronize()
+            ms[name] = a.elapsed_time(b)
+    hh, ws = tree.unpack_grad(gl)
+    e = [rel_err(hh.cpu().numpy() / rep, ref["grad_hh"]), rel_err(ws.cpu().numpy() / rep, ref["grad_wsig"]),
+         rel_err(gb.cpu().numpy() / rep, ref["grad_basis"])]
+    announce(f"traced without room: {ms} ms, grad rel errors {e}")
+    assert max(e) <= 1e-4, e
+    assert ms["traced"] <= 1.5 * ms["untraced"], ms
