@@ -691,10 +691,9 @@ __device__ __forceinline__ int64_t record_list(const RecordArgs& rec, int64_t n_
 // of rays), and the up to 63 items that a request leaves behind at a block's end. Then nothing is scattered, and a call that
 // writes its gradient rows (fresh) may leave them uninitialised until the
 // reduction stores them, each once; else they are cleared before anything is
-// added. So they are where a leaf's records are in several lists, each of which
-// adds to the row. The same answer for every thread of the call's kernels.
+// added. The same answer for every thread of the call's kernels.
 __device__ __forceinline__ bool records_fit(const RecordArgs& rec) {
-    if (!rec.head || rec.split > 0) return false;
+    if (!rec.head) return false;
     int64_t samples = 0, waves = 0;
 #pragma unroll
     for (int list = 0; list < 2; ++list) {
@@ -910,10 +909,11 @@ static hipError_t adjoint_begin(const TreeArgs& tr, const RayArgs& ra, const int
     return e;
 }
 // Before a fresh call's rays: its rows of `row` floats are cleared where the
-// reduction cannot be relied on to write them.
+// reduction cannot be relied on to write them, or adds several lists to each.
 static hipError_t fresh_begin(const TreeArgs& tr, const BackwardIO& io, int row, const RecordArgs& rec, hipStream_t st) {
     const int64_t n = tr.n_leaves * (int64_t)(row / 4);
     if (n <= 0) return hipSuccess;
+    if (rec.split > 0) return launch_zero_rows(io.grad_leaf, 4 * n, st);
     const int64_t want = (n + kBlock - 1) / kBlock, cap = (int64_t)device_cu_count() * 4;
     hipLaunchKernelGGL(fresh_clear_kernel, dim3((unsigned)(want < cap ? want : cap)), dim3(kBlock), 0, st, rec,
                        reinterpret_cast<float4*>(io.grad_leaf), n);

@@ -677,7 +677,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) 
                         my_rec = at + lane_rank(hm);
                         rec.rec[2 * (int64_t)my_rec] =
                             make_int4(__float_as_int(gz0), __float_as_int(gz1), __float_as_int(gz2), __float_as_int(gx));
-                        const int nxt = run.count > 0 ? atomicExch(rec.head + record_list(rec, tr.n_leaves, leaf, at), my_rec + run.count - 1) : my_rec - 1;
+                        const int nxt = run.count > 0 ? atomicExch(rec.head + (PER_T ? record_list(rec, tr.n_leaves, leaf, at) : leaf),
+                                                               my_rec + run.count - 1) : my_rec - 1;
                         rec.rec[2 * (int64_t)my_rec + 1] = make_int4(nxt, ray, __float_as_int(gy), __float_as_int(y));
                     }
                 }
@@ -929,7 +930,7 @@ __global__ __launch_bounds__(kBlock) void reduce_pp_timed_kernel(TreeArgs tr, In
     __shared__ float s_h[kBlock / kWave][K];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int64_t N = tr.n_leaves, lists = N << rec.split, n_waves = (int64_t)gridDim.x * (kBlock / kWave);
-    const bool fresh = io.fresh && records_fit(rec);   // rows are stored; else added to
+    const bool fresh = io.fresh && rec.split == 0 && records_fit(rec);   // rows are stored; else added to
     const int64_t share = lists / (kTimedBatches * n_waves);
     const int batch = share < 1 ? 1 : (share > kWave ? kWave : (int)share);
     for (int64_t b = ((int64_t)blockIdx.x * (kBlock / kWave) + wv) * batch; b < lists; b += n_waves * batch) {
