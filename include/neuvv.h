@@ -22,7 +22,7 @@
  *     bytes per leaf plus 32 bytes per record of room, see there), and
  *     neuvv_render_multi the segment lists of its instances (see there). Scratch
  *     is taken in stream order on the call's stream, from blocks the library
- *     keeps for that stream (scratch up to 64 MiB; see neuvv_release_scratch)
+ *     keeps for that stream (scratch up to 128 MiB; see neuvv_release_scratch)
  *     or from a memory pool it keeps per device (which keeps freed memory for
  *     later calls), and freed in stream order after the kernels; each call has
  *     its own, so calls on different streams do not interfere.
@@ -594,8 +594,9 @@ int neuvv_shade(const neuvv_light* light, const float* shadow_map, int64_t n, co
 
 /*
  * neuvv_release_scratch - frees the scratch the library keeps on the current
- * device between calls (at most 32 blocks and 256 MiB, each kept for the
- * stream that last used it): waits for the calls that used it and returns it
+ * device between calls (at most 32 blocks and 512 MiB, each kept for the
+ * stream that last used it, and given to another once that is done with it and
+ * there is no room for more): waits for the calls that used it and returns it
  * to the pool. Scratch of calls that run in other threads meanwhile is left
  * alone. Not to be called while a stream of the device is captured.
  * Errors: HIP.

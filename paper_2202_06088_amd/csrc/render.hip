@@ -9,6 +9,7 @@
 #include <mutex>
 
 #include "launch.h"
+#include "scratch.h"
 
 namespace neuvv {
 
@@ -56,130 +57,90 @@ static hipError_t pool_alloc(void** p, size_t bytes, int dev, hipStream_t stream
     return pool ? hipMallocFromPoolAsync(p, bytes, pool, stream) : hipMallocAsync(p, bytes, stream);
 }
 
-// Small scratch is kept by the library between calls: a stream-ordered
-// allocation and its release cost the host 36 us together, more than the three
-// launches of a small render (11 us). A block belongs to one call at a time, and
-// afterwards to the stream of that call: the next call on the stream takes it
-// behind the event recorded at its release, so that stream order protects it as
-// it would a stream-ordered allocation (the event also covers a new stream that
-// the runtime gives the handle of a destroyed one). Calls on other streams, and
-// further calls of other threads on the same stream, have blocks of their own;
-// beyond kKeepBlocks blocks or kKeepBytes a device, for larger scratch, under
-// stream capture (the graph owns its allocations then) and on the per-thread
-// stream (one handle for many streams), the pool serves the call alone.
+// Scratch is kept between calls as KeptScratch describes, with these calls of
+// the runtime. None is taken or given back so under stream capture (the graph
+// owns its allocations then) or on the per-thread stream (one handle for many
+// streams): the pool serves such calls alone.
 namespace {
-constexpr size_t kKeepLargest = (size_t)64 << 20, kKeepSmallest = (size_t)64 << 10, kKeepBytes = (size_t)256 << 20;
-constexpr int kKeepBlocks = 32;
-struct KeptBlock {
-    void* p;
-    size_t bytes;
-    hipStream_t stream;
-    hipEvent_t done;
-    bool used;
+// Asking an event or waiting for it would end the capture of another thread's
+// stream, were this thread not in the relaxed capture mode meanwhile.
+struct RelaxedCapture {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    bool on = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+    ~RelaxedCapture() {
+        if (on) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    }
 };
-struct KeptBlocks {
-    std::mutex mu;
-    KeptBlock b[kKeepBlocks];
-    int n = 0;
-    size_t bytes = 0;
+
+struct HipRt {
+    using Status = hipError_t;
+    using Stream = hipStream_t;
+    using Event = hipEvent_t;
+    static constexpr hipError_t ok = hipSuccess;
+    int dev;
+    hipError_t alloc(void** p, size_t bytes, hipStream_t s) { return pool_alloc(p, bytes, dev, s); }
+    hipError_t free(void* p, hipStream_t s) { return hipFreeAsync(p, s); }
+    hipError_t create(hipEvent_t* e) { return hipEventCreateWithFlags(e, hipEventDisableTiming); }
+    void destroy(hipEvent_t e) { (void)hipEventDestroy(e); }
+    hipError_t record(hipEvent_t e, hipStream_t s) { return hipEventRecord(e, s); }
+    hipError_t wait(hipStream_t s, hipEvent_t e) { return hipStreamWaitEvent(s, e, 0); }
+    hipError_t sync(hipEvent_t e) { return hipEventSynchronize(e); }
+    bool passed(hipEvent_t e) {
+        RelaxedCapture relaxed;
+        if (hipEventQuery(e) == hipSuccess) return true;
+        (void)hipGetLastError();   // (hipErrorNotReady is no error of the call)
+        return false;
+    }
 };
+
 // (never destroyed: calls may still run while static objects are)
-KeptBlocks* kept_blocks(int dev) {
-    static KeptBlocks* all = new KeptBlocks[64];
+KeptScratch<HipRt>* kept_scratch(int dev) {
+    static KeptScratch<HipRt>* all = new KeptScratch<HipRt>[64];
     return dev >= 0 && dev < 64 ? all + dev : nullptr;
 }
-bool may_keep(hipStream_t stream) {
-    if (stream == hipStreamPerThread) return false;
+
+bool capturing(hipStream_t stream) {
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(stream, &st) != hipSuccess) {
         (void)hipGetLastError();
-        return false;
+        return true;
     }
-    return st == hipStreamCaptureStatusNone;
+    return st != hipStreamCaptureStatusNone;
 }
+
 }  // namespace
 
 hipError_t work_alloc(void** p, size_t bytes, hipStream_t stream) {
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
-    KeptBlocks* k = bytes <= kKeepLargest ? kept_blocks(dev) : nullptr;
-    if (!k || !may_keep(stream)) return pool_alloc(p, bytes, dev, stream);
-    size_t want = kKeepSmallest;
-    while (want < bytes) want *= 2;
-    std::lock_guard<std::mutex> lk(k->mu);
-    KeptBlock* best = nullptr;
-    for (int i = 0; i < k->n; ++i) {
-        KeptBlock& b = k->b[i];
-        if (!b.used && b.stream == stream && b.bytes >= bytes && (!best || b.bytes < best->bytes)) best = &b;
+    KeptScratch<HipRt>* k = kept_scratch(dev);
+    *p = nullptr;
+    if (k && stream != hipStreamPerThread && !capturing(stream)) {
+        HipRt rt{dev};
+        if (k->acquire(rt, p, bytes, stream) != hipSuccess) (void)hipGetLastError();
+        if (*p) return hipSuccess;
     }
-    if (best) {
-        e = hipStreamWaitEvent(stream, best->done, 0);
-        if (e != hipSuccess) return e;
-        best->used = true;
-        *p = best->p;
-        return hipSuccess;
-    }
-    if (k->n == kKeepBlocks || k->bytes + want > kKeepBytes) return pool_alloc(p, bytes, dev, stream);
-    KeptBlock b{nullptr, want, stream, nullptr, true};
-    e = hipEventCreateWithFlags(&b.done, hipEventDisableTiming);
-    if (e != hipSuccess) return e;
-    e = pool_alloc(&b.p, want, dev, stream);
-    if (e != hipSuccess) {
-        (void)hipEventDestroy(b.done);
-        return e;
-    }
-    k->b[k->n++] = b;
-    k->bytes += want;
-    *p = b.p;
-    return hipSuccess;
+    return pool_alloc(p, bytes, dev, stream);
 }
 
 hipError_t work_free(void* p, hipStream_t stream) {
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
-    if (KeptBlocks* k = kept_blocks(dev)) {
-        std::lock_guard<std::mutex> lk(k->mu);
-        for (int i = 0; i < k->n; ++i) {
-            if (k->b[i].p != p || !k->b[i].used) continue;
-            e = hipEventRecord(k->b[i].done, stream);
-            if (e == hipSuccess) {
-                k->b[i].used = false;
-                return e;
-            }
-            // (cannot be handed on behind the event: back to the pool in stream order)
-            (void)hipEventDestroy(k->b[i].done);
-            k->bytes -= k->b[i].bytes;
-            k->b[i] = k->b[--k->n];
-            (void)hipFreeAsync(p, stream);
-            return e;
-        }
-    }
+    HipRt rt{dev};
+    KeptScratch<HipRt>* k = kept_scratch(dev);
+    if (k && k->put_back(rt, p, stream, &e)) return e;
     return hipFreeAsync(p, stream);
 }
 
 hipError_t release_kept() {
     int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
+    const hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
-    KeptBlocks* k = kept_blocks(dev);
-    if (!k) return hipSuccess;
-    std::lock_guard<std::mutex> lk(k->mu);
-    for (int i = 0; i < k->n;) {
-        KeptBlock& b = k->b[i];
-        if (b.used) {
-            ++i;
-            continue;
-        }
-        e = hipEventSynchronize(b.done);
-        if (e == hipSuccess) e = hipFreeAsync(b.p, nullptr);
-        if (e != hipSuccess) return e;
-        (void)hipEventDestroy(b.done);
-        k->bytes -= b.bytes;
-        b = k->b[--k->n];
-    }
-    return hipSuccess;
+    HipRt rt{dev};
+    KeptScratch<HipRt>* k = kept_scratch(dev);
+    return k ? k->release(rt, nullptr) : hipSuccess;
 }
 
 size_t trace_bytes(int64_t n, int64_t cap) {

@@ -2,6 +2,7 @@
 block and room edges, remainders, smallest launches. Bars as in the other GPU
 tests: 1e-5 of the largest value for renders, 1e-4 for gradients, against the
 FP64 oracle."""
+import ctypes
 import threading
 
 import numpy as np
@@ -285,3 +286,82 @@ def test_traced_adjoint_without_room_for_records(tiny, records, monkeypatch):
     announce(f"traced without room: {ms} ms, grad rel errors {e}")
     assert max(e) <= 1e-4, e
     assert ms["traced"] <= 1.5 * ms["untraced"], ms
+
+
+def _hip():
+    """The HIP runtime that this process has loaded."""
+    path = next(ln.split()[-1] for ln in open("/proc/self/maps") if "libamdhip64" in ln)
+    lib = ctypes.CDLL(path)
+    lib.hipStreamCreateWithFlags.argtypes = [ctypes.c_void_p, ctypes.c_uint]
+    lib.hipStreamDestroy.argtypes = [ctypes.c_void_p]
+    return lib
+
+
+def test_scratch_of_destroyed_streams(tiny):
+    """Streams of the runtime that are destroyed while their work is queued, so that later streams may get their
+    handles: more of them than blocks are kept, two calls in flight at a time, and calls on the per-thread stream."""
+    sc, o, d, g, _ = tiny
+    hip, tree = _hip(), upload(sc)
+    oo, dd, gg = (tdev(np.repeat(v, 64, 0)) for v in (o, d, g))
+    sizes = [oo.shape[0], 64, 4096]
+
+    def once(m, stream, out):
+        ops.render(tree, oo[:m], dd[:m], 4.0, out=out[:4], stream=stream)
+        ops.render_backward(tree, oo[:m], dd[:m], out[0], out[1], out[3], gg[:m], None, 4.0, grads=out[4:],
+                            stream=stream)
+
+    def outputs(m):
+        return (torch.empty(m, 3, device="cuda"), torch.empty(m, device="cuda"), torch.empty(m, device="cuda"),
+                torch.empty(m, dtype=torch.int32, device="cuda")) + tree.zero_grads()
+
+    want = {m: outputs(m) for m in sizes}
+    for m in sizes:
+        once(m, None, want[m])
+    work = [(sizes[k % 3], outputs(sizes[k % 3])) for k in range(45)]
+    torch.cuda.synchronize()
+    streams, handles = [], set()
+    for k, (m, out) in enumerate(work):
+        if k % 9 == 8:
+            once(m, 2, out)   # hipStreamPerThread
+            continue
+        s = ctypes.c_void_p()
+        assert hip.hipStreamCreateWithFlags(ctypes.byref(s), 1) == 0   # non-blocking, default priority
+        handles.add(s.value)
+        streams.append(s)
+        once(m, s.value, out)
+        if len(streams) == 2:
+            assert hip.hipStreamDestroy(streams.pop(0)) == 0
+    for s in streams:
+        assert hip.hipStreamDestroy(s) == 0
+    torch.cuda.synchronize()
+    announce(f"{len(handles)} handles of 40 streams")
+    for m, out in work:
+        for a, b in zip(out[:4], want[m][:4]):
+            assert torch.equal(a, b)
+        for a, b in zip(out[4:], want[m][4:]):
+            assert rel_err(a.cpu().numpy(), b.cpu().numpy()) <= 1e-5   # summation order of float32 atomics
+    _lib.neuvv_release_scratch()
+
+
+def test_captured_calls(tiny):
+    """Calls captured in a graph, whose scratch is the graph's, beside eager calls on kept scratch: every replay gives
+    the eager results."""
+    sc, o, d, g, _ = tiny
+    tree, oo, dd, gg = upload(sc), tdev(o), tdev(d), tdev(g)
+    want = ops.render(tree, oo, dd, 4.0, None, 1e-4, 64)
+    wg = ops.render_backward(tree, oo, dd, want[0], want[1], want[3], gg, None, 4.0, None, 1e-4, 64)
+    out, grads = tuple(torch.empty_like(v) for v in want), tree.zero_grads()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        ops.render(tree, oo, dd, 4.0, None, 1e-4, 64, out=out)
+        ops.render_backward(tree, oo, dd, out[0], out[1], out[3], gg, None, 4.0, None, 1e-4, 64, grads=grads)
+    for _ in range(4):
+        for v in out + tuple(grads):
+            v.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(out, want))
+        assert all(rel_err(a.cpu().numpy(), b.cpu().numpy()) <= 1e-5 for a, b in zip(grads, wg))
+        again = ops.render(tree, oo, dd, 4.0, None, 1e-4, 64)
+        assert all(torch.equal(a, b) for a, b in zip(again, want))
