@@ -593,11 +593,12 @@ int neuvv_shade(const neuvv_light* light, const float* shadow_map, int64_t n, co
                 const float* rgb, const float* alpha, const float* depth, float* out_rgb, void* stream);
 
 /*
- * neuvv_release_scratch - frees the scratch the library keeps on the current
- * device between calls (at most 32 blocks and 512 MiB, each kept for the
- * stream that last used it, and given to another once that is done with it and
- * there is no room for more): waits for the calls that used it and returns it
- * to the pool. Scratch of calls that run in other threads meanwhile is left
+ * neuvv_release_scratch - gives the scratch the library holds on the current
+ * device back to the device: the blocks it keeps between calls (at most 32
+ * blocks and 512 MiB, each kept for the stream that last used it, and given to
+ * another once that is done with it and there is no room for more), and the
+ * free memory of its pool. Waits for the calls that used the blocks and for the
+ * null stream. Scratch of calls that run in other threads meanwhile is left
  * alone. Not to be called while a stream of the device is captured.
  * Errors: HIP.
  */

@@ -85,6 +85,15 @@ struct HipRt {
     hipError_t record(hipEvent_t e, hipStream_t s) { return hipEventRecord(e, s); }
     hipError_t wait(hipStream_t s, hipEvent_t e) { return hipStreamWaitEvent(s, e, 0); }
     hipError_t sync(hipEvent_t e) { return hipEventSynchronize(e); }
+    hipError_t finish(hipStream_t s) { return hipStreamSynchronize(s); }
+    hipError_t trim() {
+        hipMemPool_t pool = nullptr;
+        {
+            std::lock_guard<std::mutex> lk(g_pool_mu);
+            pool = g_pool[dev];
+        }
+        return pool ? hipMemPoolTrimTo(pool, 0) : hipSuccess;
+    }
     bool passed(hipEvent_t e) {
         RelaxedCapture relaxed;
         if (hipEventQuery(e) == hipSuccess) return true;
@@ -107,7 +116,6 @@ bool capturing(hipStream_t stream) {
     }
     return st != hipStreamCaptureStatusNone;
 }
-
 }  // namespace
 
 hipError_t work_alloc(void** p, size_t bytes, hipStream_t stream) {
@@ -138,9 +146,10 @@ hipError_t release_kept() {
     int dev = 0;
     const hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
+    RelaxedCapture relaxed;
     HipRt rt{dev};
     KeptScratch<HipRt>* k = kept_scratch(dev);
-    return k ? k->release(rt, nullptr) : hipSuccess;
+    return k ? k->give_back(rt, nullptr) : hipSuccess;
 }
 
 size_t trace_bytes(int64_t n, int64_t cap) {

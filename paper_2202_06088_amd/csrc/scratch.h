@@ -29,6 +29,8 @@ namespace neuvv {
 //   Status create(Event*)  void destroy(Event)
 //   Status record(Event, Stream)  Status wait(Stream, Event)
 //   bool passed(Event)  Status sync(Event)
+//   Status finish(Stream)                  waits for the stream
+//   Status trim()                          the pool's free memory goes back to the device
 template <class Rt>
 class KeptScratch {
   public:
@@ -134,6 +136,15 @@ class KeptScratch {
             if (e == Rt::ok) e = s != Rt::ok ? s : f;
         }
         return e;
+    }
+
+    // Gives what is held and not in use back to the device: the idle blocks and the pool's free memory. (The pool
+    // keeps what is freed to it, so the blocks alone would stay the process's until it ends.)
+    Status give_back(Rt& rt, Stream stream) {
+        Status e = release(rt, stream);
+        const Status f = rt.finish(stream);
+        if (e == Rt::ok) e = f;
+        return e == Rt::ok ? rt.trim() : e;
     }
 
     int blocks() {
