@@ -22,7 +22,7 @@
  *     bytes per leaf plus 32 bytes per record of room, see there), and
  *     neuvv_render_multi the segment lists of its instances (see there). Scratch
  *     is taken in stream order on the call's stream, from blocks the library
- *     keeps for that stream (scratch up to 128 MiB; see neuvv_release_scratch)
+ *     keeps for that stream (scratch up to 64 MiB; see neuvv_release_scratch)
  *     or from a memory pool it keeps per device (which keeps freed memory for
  *     later calls), and freed in stream order after the kernels; each call has
  *     its own, so calls on different streams do not interfere.
@@ -354,11 +354,12 @@ int neuvv_render_noalloc(const neuvv_tree* tree, const neuvv_instance* inst, int
  * Two-phase adjoint: each sample's dL/dz and dL/dsigma (and dL/dy, Cg > 0)
  * are written once as a 32-byte record linked into its leaf's list; a second
  * kernel sums every list and adds each touched leaf's row once. The room for
- * records is 2 per ray, 16 per ray up to 2^24, or the trace's room
+ * records is 2 per ray, 16 per ray up to 2^23, or the trace's room
  * (trace_cap) in neuvv_render_backward_trace, whichever is most; at least
- * 2^20, at most 2^31 - 1 (the environment
- * variable NEUVV_BWD_RECORDS, read at every call, sets it; 0 turns records
- * off); samples beyond it are added per sample in the same call. Records
+ * 2^20, at most 2^31 - 1 (the environment variable NEUVV_BWD_RECORDS, read at
+ * every call, sets it; 0 turns records off). Where the device has no memory
+ * for 16 per ray the room is less, but no less than the rest of the rule says;
+ * samples beyond it are added per sample in the same call. Records
  * are used with image_width or not, for n_rays and n_leaves below 2^31.
  * Summation order follows the atomics, so results may differ between runs in the last
  * bits, as with any atomic accumulation.
@@ -595,7 +596,7 @@ int neuvv_shade(const neuvv_light* light, const float* shadow_map, int64_t n, co
 /*
  * neuvv_release_scratch - gives the scratch the library holds on the current
  * device back to the device: the blocks it keeps between calls (at most 32
- * blocks and 512 MiB, each kept for the stream that last used it, and given to
+ * blocks and 320 MiB, each kept for the stream that last used it, and given to
  * another once that is done with it and there is no room for more), and the
  * free memory of its pool. Waits for the calls that used the blocks and for the
  * null stream. Scratch of calls that run in other threads meanwhile is left

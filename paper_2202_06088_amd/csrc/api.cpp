@@ -141,23 +141,15 @@ int make_rays(int64_t n, const float* o, const float* d, const float* t, float t
     return NEUVV_OK;
 }
 
-// Sample records of the two-phase adjoint: NEUVV_BWD_RECORDS overrides (0
-// turns the records off); by default room for two samples per ray, for sixteen
-// up to 2^24 in all (rays of a close view may all hit, thirteen samples each on
-// average; scattering 2.7 M samples of 427,000 rays one by one cost 1.7 ms) or,
-// after a traced forward, for as many samples as the trace has room for,
-// whichever is most; at least 2^20, at most 2^31 - 1. Samples beyond the room
-// take per-sample atomics.
-int64_t record_cap(int64_t n_rays, int64_t trace_cap) {
+// Sample records of the two-phase adjoint: record_room, unless NEUVV_BWD_RECORDS
+// says how many (0 turns the records off).
+neuvv::RecordRoom record_cap(int64_t n_rays, int64_t trace_cap) {
     const char* e = getenv("NEUVV_BWD_RECORDS");
-    const int64_t many = n_rays < ((int64_t)1 << 20) ? 16 * n_rays : (int64_t)1 << 24;
-    int64_t cap = 2 * n_rays > trace_cap ? 2 * n_rays : trace_cap;
-    if (cap < many) cap = many;
-    if (cap < (int64_t)1 << 20) cap = (int64_t)1 << 20;
-    if (e && *e) cap = atoll(e);
+    if (!e || !*e) return neuvv::record_room(n_rays, trace_cap);
+    int64_t cap = atoll(e);
     if (cap < 0) cap = 0;
     if (cap > (int64_t)INT32_MAX) cap = INT32_MAX;
-    return cap;
+    return {cap, cap};
 }
 
 neuvv::TreeArgs tree_args(const neuvv_tree* t) {

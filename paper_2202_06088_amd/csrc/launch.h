@@ -7,6 +7,7 @@
 #include <string>
 
 #include "neuvv_device.h"
+#include "room.h"
 
 namespace neuvv {
 
@@ -44,7 +45,7 @@ struct BackwardIO {
     float* grad_basis;
     float* grad_basis_g;   // per-point hyperangle basis gradient (Cg > 0), or nullptr
     int32_t fresh;         // grad_leaf is written, not added to: rows of leaves without a gradient become zero
-    int64_t record_cap;    // two-phase adjoint: sample records at most (0: per-sample atomics only)
+    RecordRoom records;    // two-phase adjoint: sample records (0: per-sample atomics only)
     TraceArgs trace;       // head == nullptr: walk every ray (K = 16, C = 8 form only)
 };
 
@@ -62,7 +63,7 @@ struct RecordArgs {
     const unsigned long long* counts;   // per XCD part, kQueueStride apart: {rays that walk, their samples}, then the
                                         // same for the rays that replay (the cull pass fills them)
     double* basis_sum;             // [64] the reduction's basis gradients (one time for every ray)
-    int32_t max_waves;             // wavefronts that one kernel of the call can have on the device at once
+    int32_t max_waves;             // wavefronts of the larger one of the two grids that write records
     int32_t split;                 // log2 of the lists a leaf has (record_list), head holds n_leaves << split
     int64_t cap;
 };

@@ -78,14 +78,25 @@ struct HipRt {
     using Event = hipEvent_t;
     static constexpr hipError_t ok = hipSuccess;
     int dev;
-    hipError_t alloc(void** p, size_t bytes, hipStream_t s) { return pool_alloc(p, bytes, dev, s); }
+    hipError_t alloc(void** p, size_t bytes, hipStream_t s) {
+        const hipError_t e = pool_alloc(p, bytes, dev, s);
+        if (e != hipSuccess) (void)hipGetLastError();   // (it is returned; a launch after another try must not find it)
+        return e;
+    }
+    static bool no_memory(hipError_t e) { return e == hipErrorOutOfMemory; }
     hipError_t free(void* p, hipStream_t s) { return hipFreeAsync(p, s); }
     hipError_t create(hipEvent_t* e) { return hipEventCreateWithFlags(e, hipEventDisableTiming); }
     void destroy(hipEvent_t e) { (void)hipEventDestroy(e); }
     hipError_t record(hipEvent_t e, hipStream_t s) { return hipEventRecord(e, s); }
     hipError_t wait(hipStream_t s, hipEvent_t e) { return hipStreamWaitEvent(s, e, 0); }
-    hipError_t sync(hipEvent_t e) { return hipEventSynchronize(e); }
-    hipError_t finish(hipStream_t s) { return hipStreamSynchronize(s); }
+    hipError_t sync(hipEvent_t e) {
+        RelaxedCapture relaxed;
+        return hipEventSynchronize(e);
+    }
+    hipError_t finish(hipStream_t s) {
+        RelaxedCapture relaxed;
+        return hipStreamSynchronize(s);
+    }
     hipError_t trim() {
         hipMemPool_t pool = nullptr;
         {
@@ -123,13 +134,10 @@ hipError_t work_alloc(void** p, size_t bytes, hipStream_t stream) {
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
     KeptScratch<HipRt>* k = kept_scratch(dev);
-    *p = nullptr;
-    if (k && stream != hipStreamPerThread && !capturing(stream)) {
-        HipRt rt{dev};
-        if (k->acquire(rt, p, bytes, stream) != hipSuccess) (void)hipGetLastError();
-        if (*p) return hipSuccess;
-    }
-    return pool_alloc(p, bytes, dev, stream);
+    HipRt rt{dev};
+    if (!k) return rt.alloc(p, bytes, stream);
+    const bool graph = capturing(stream);
+    return k->serve(rt, p, bytes, stream, !graph && stream != hipStreamPerThread, graph);
 }
 
 hipError_t work_free(void* p, hipStream_t stream) {
@@ -146,7 +154,6 @@ hipError_t release_kept() {
     int dev = 0;
     const hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
-    RelaxedCapture relaxed;
     HipRt rt{dev};
     KeptScratch<HipRt>* k = kept_scratch(dev);
     return k ? k->give_back(rt, nullptr) : hipSuccess;

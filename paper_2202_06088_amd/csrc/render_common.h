@@ -627,18 +627,20 @@ static __global__ void adjoint_init_kernel(unsigned long long* hdr, int n_hdr, i
 }
 
 // Wave-uniform allocation of n (<= 128) consecutive items of a room of cap
-// items, out of blocks taken from its counter. [cur, end) is what is left of
+// items, out of blocks of BLOCK(cap) taken from its counter. [cur, end) is what is left of
 // the wavefront's current block, end = -1 once the room is exhausted. Returns
 // the first item, or -1 when there is no room. A request that fails has left
 // the counter above cap. Call with every lane of the wavefront active.
+template <int (*BLOCK)(int64_t) = item_block>
 __device__ __forceinline__ int take_items(unsigned long long* counter, int64_t cap, int n, int& cur, int& end) {
     if (!items_fit(cur, end, n)) {
         if (end < 0) return -1;
+        const int block = BLOCK(cap);
         unsigned long long b = 0;
-        if ((threadIdx.x & 63) == 0) b = atomicAdd(counter, (unsigned long long)item_block(cap));
+        if ((threadIdx.x & 63) == 0) b = atomicAdd(counter, (unsigned long long)block);
         const uint32_t b_lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b);
         const uint32_t b_hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32));
-        open_block((int64_t)(((uint64_t)b_hi << 32) | b_lo), cap, cur, end);
+        open_block((int64_t)(((uint64_t)b_hi << 32) | b_lo), cap, block, cur, end);
         if (!items_fit(cur, end, n)) {
             end = -1;
             return -1;
@@ -706,7 +708,7 @@ __device__ __forceinline__ bool records_fit(const RecordArgs& rec) {
         }
         waves += chunks < rec.max_waves ? chunks : rec.max_waves;
     }
-    const int64_t block = item_block(rec.cap);
+    const int64_t block = record_block(rec.cap);
     return samples >= 0 && (samples / (block - 63) + 1 + waves) * block <= rec.cap;
 }
 
@@ -844,8 +846,8 @@ __device__ __forceinline__ void feed_leaves(LeafFeeder& f, const RecordArgs& rec
 // Scratch of one adjoint call, taken from the pool in one piece and initialised
 // by one kernel: the queues and list counts of the rays that walk and of those
 // that replay their trace, the lists, the counter of records, the leaf heads
-// and the records (room for cap of 32 bytes; with cap == 0 rec stays empty:
-// per-sample atomics only). One cull pass then lists the rays. (An allocation,
+// and the records (32 bytes each, as many of the room as the device has memory
+// for; with none rec stays empty: per-sample atomics only). One cull pass then lists the rays. (An allocation,
 // a clearing kernel and a cull pass per list and another of each for the
 // records cost an adjoint of four 1920 x 1080 layers about 25 us a layer.)
 struct AdjointScratch {
@@ -862,7 +864,7 @@ struct NoHit {};
 // step 2666 and 1217 us).
 static bool replays(const TraceArgs& trace, int64_t samples, int64_t cap) { return trace.head && cap > 0 && cap >= samples; }
 static hipError_t adjoint_begin(const TreeArgs& tr, const RayArgs& ra, const int32_t* nsamp, const int32_t* trace_head,
-                                int64_t cap, hipStream_t st, AdjointScratch& s, int split = 0) {
+                                const RecordRoom& room, hipStream_t st, AdjointScratch& s, int split = 0) {
     s = AdjointScratch{ra, ra, RecordArgs{}, nullptr};
     const bool listed = ra.n <= (int64_t)INT32_MAX;   // else the slot form: the walking kernel tests every ray
     if (trace_head && !listed) return hipErrorInvalidValue;
@@ -871,9 +873,12 @@ static hipError_t adjoint_begin(const TreeArgs& tr, const RayArgs& ra, const int
     constexpr size_t hdr = ((size_t)n_hdr * sizeof(unsigned long long) + 255) & ~(size_t)255;
     const size_t list_b = listed ? (size_t)((ra.n_slots + 63) >> 6) * 64 * sizeof(int32_t) : 0;
     const size_t lists = trace_head ? 2 * list_b : list_b;
-    const int64_t n_heads = cap > 0 ? tr.n_leaves << split : 0;
+    const int64_t n_heads = room.most > 0 ? tr.n_leaves << split : 0;
     const size_t head_b = ((size_t)n_heads * sizeof(int32_t) + 255) & ~(size_t)255;
-    hipError_t e = work_alloc(&s.mem, hdr + lists + head_b + (size_t)(cap > 0 ? cap : 0) * 2 * sizeof(int4), st);
+    int64_t cap = 0;
+    hipError_t e = take_room(
+        room, cap, [&](int64_t records) { return work_alloc(&s.mem, hdr + lists + head_b + (size_t)records * 2 * sizeof(int4), st); },
+        [](hipError_t a) { return a == hipErrorOutOfMemory; });
     if (e != hipSuccess) {
         s.mem = nullptr;
         return e;
@@ -888,7 +893,6 @@ static hipError_t adjoint_begin(const TreeArgs& tr, const RayArgs& ra, const int
         s.rec.counter = counters + 4 * kCounters;
         s.rec.counts = counters + kCounters;
         s.rec.basis_sum = reinterpret_cast<double*>(counters + 4 * kCounters + kQueueStride);
-        s.rec.max_waves = device_cu_count() * 32;
         s.rec.head = reinterpret_cast<int32_t*>(p + hdr + lists);
         s.rec.rec = reinterpret_cast<int4*>(p + hdr + lists + head_b);
         s.rec.split = split;
@@ -917,6 +921,21 @@ static hipError_t fresh_begin(const TreeArgs& tr, const BackwardIO& io, int row,
     const int64_t want = (n + kBlock - 1) / kBlock, cap = (int64_t)device_cu_count() * 4;
     hipLaunchKernelGGL(fresh_clear_kernel, dim3((unsigned)(want < cap ? want : cap)), dim3(kBlock), 0, st, rec,
                        reinterpret_cast<float4*>(io.grad_leaf), n);
+    return hipGetLastError();
+}
+// The kernels over an adjoint's rays: walk for those on the first list, replay
+// (if any ray may replay) for those on the second.
+template <class Kernel>
+static hipError_t adjoint_rays(Kernel walk, Kernel replay_kernel, bool replay, int row, const TreeArgs& tr,
+                               const InstArgs& in, const BackwardIO& io, AdjointScratch& s, hipStream_t st) {
+    const int walk_grid = grid_for(walk, s.walk), replay_grid = replay ? grid_for(replay_kernel, s.replay) : 0;
+    s.rec.max_waves = (walk_grid > replay_grid ? walk_grid : replay_grid) * (kBlock / kWave);
+    hipError_t e = io.fresh ? fresh_begin(tr, io, row, s.rec, st) : hipSuccess;
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(walk, dim3(walk_grid), dim3(kBlock), 0, st, tr, in, s.walk, io, s.rec);
+    e = hipGetLastError();
+    if (e != hipSuccess || !replay) return e;
+    hipLaunchKernelGGL(replay_kernel, dim3(replay_grid), dim3(kBlock), 0, st, tr, in, s.replay, io, s.rec);
     return hipGetLastError();
 }
 static hipError_t adjoint_end(const AdjointScratch& s, hipError_t e, hipStream_t st) {

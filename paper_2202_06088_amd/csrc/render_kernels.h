@@ -480,7 +480,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(min_wave
                 // the record stores of the wavefront are contiguous
                 const uint64_t hm = __ballot(has);
                 const int n_has = __popcll(hm);
-                const int at = n_has > 0 ? take_items(rec.counter, rec.cap, n_has, wrec, wend) : -1;
+                const int at = n_has > 0 ? take_items<record_block>(rec.counter, rec.cap, n_has, wrec, wend) : -1;
                 if (at >= 0) {
                     const RecordRun run = record_run(hm, has, leaf);
                     if (has) {
@@ -689,7 +689,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(min_wave
                 // this iteration's samples take consecutive records in lane order, so
                 // the record stores of the wavefront are contiguous
                 const uint64_t hm = __ballot(has);
-                const int at = take_items(rec.counter, rec.cap, __popcll(hm), wrec, wend);
+                const int at = take_items<record_block>(rec.counter, rec.cap, __popcll(hm), wrec, wend);
                 if (at >= 0) {
                     const RecordRun run = record_run(hm, has, leaf);
                     if (has) {
@@ -956,37 +956,31 @@ static hipError_t fwd_t(const TreeArgs& tr, const InstArgs& in, const RayArgs& r
 }
 
 template <int K, int C, int DT>
-static hipError_t bwd_walk(const TreeArgs& tr, const InstArgs& in, const RayArgs& ra, const BackwardIO& io,
-                           const RecordArgs& rec, hipStream_t st) {
-    auto kern = ra.t ? (in.identity ? render_bwd_kernel<K, C, DT, true, true> : render_bwd_kernel<K, C, DT, false, true>)
-                     : (in.identity ? render_bwd_kernel<K, C, DT, true, false> : render_bwd_kernel<K, C, DT, false, false>);
-    hipLaunchKernelGGL(kern, dim3(grid_for(kern, ra)), dim3(kBlock), 0, st, tr, in, ra, io, rec);
-    return hipGetLastError();
+static auto bwd_walk_kernel(const InstArgs& in, const RayArgs& ra) {
+    return ra.t ? (in.identity ? render_bwd_kernel<K, C, DT, true, true> : render_bwd_kernel<K, C, DT, false, true>)
+                : (in.identity ? render_bwd_kernel<K, C, DT, true, false> : render_bwd_kernel<K, C, DT, false, false>);
 }
 
 template <int K, int C, int DT>
-static hipError_t bwd_replay(const TreeArgs& tr, const InstArgs& in, const RayArgs& ra, const BackwardIO& io,
-                             const RecordArgs& rec, hipStream_t st) {
-    auto kern = ra.t ? (in.identity ? replay_bwd_kernel<K, C, DT, true, true> : replay_bwd_kernel<K, C, DT, false, true>)
-                     : (in.identity ? replay_bwd_kernel<K, C, DT, true, false> : replay_bwd_kernel<K, C, DT, false, false>);
-    hipLaunchKernelGGL(kern, dim3(grid_for(kern, ra)), dim3(kBlock), 0, st, tr, in, ra, io, rec);
-    return hipGetLastError();
+static auto bwd_replay_kernel(const InstArgs& in, const RayArgs& ra) {
+    return ra.t ? (in.identity ? replay_bwd_kernel<K, C, DT, true, true> : replay_bwd_kernel<K, C, DT, false, true>)
+                : (in.identity ? replay_bwd_kernel<K, C, DT, true, false> : replay_bwd_kernel<K, C, DT, false, false>);
 }
 
 template <int K, int C, int DT>
 static hipError_t bwd_t(const TreeArgs& tr, const InstArgs& in, const RayArgs& ra, const BackwardIO& io,
                         hipStream_t st) {
     // records need int32 ray and record indices
-    const int64_t cap =
-        ra.n <= (int64_t)INT32_MAX && tr.n_leaves > 0 && tr.n_leaves <= (int64_t)INT32_MAX ? io.record_cap : 0;
+    const RecordRoom room =
+        ra.n <= (int64_t)INT32_MAX && tr.n_leaves > 0 && tr.n_leaves <= (int64_t)INT32_MAX ? io.records : RecordRoom{0, 0};
     AdjointScratch sc;
-    const bool replay = replays(io.trace, io.trace.cap, cap);
-    hipError_t e = adjoint_begin(tr, ra, io.nsamp, replay ? io.trace.head : nullptr, cap, st, sc);
+    const bool replay = replays(io.trace, io.trace.cap, room.least);
+    hipError_t e = adjoint_begin(tr, ra, io.nsamp, replay ? io.trace.head : nullptr, room, st, sc);
     const RecordArgs& rec = sc.rec;
-    if (e == hipSuccess && io.fresh) e = fresh_begin(tr, io, grad_row<K, C>(), rec, st);
-    if (e == hipSuccess) e = bwd_walk<K, C, DT>(tr, in, sc.walk, io, rec, st);
-    if (e == hipSuccess && replay) e = bwd_replay<K, C, DT>(tr, in, sc.replay, io, rec, st);
-    if (e == hipSuccess && cap > 0) {
+    if (e == hipSuccess)
+        e = adjoint_rays(bwd_walk_kernel<K, C, DT>(in, ra), bwd_replay_kernel<K, C, DT>(in, ra), replay,
+                         grad_row<K, C>(), tr, in, io, sc, st);
+    if (e == hipSuccess && rec.cap > 0) {
         const bool common = ra.t == nullptr;
         auto kern = common ? (in.identity ? reduce_records_kernel<K, C, DT, true, true>
                                           : reduce_records_kernel<K, C, DT, false, true>)

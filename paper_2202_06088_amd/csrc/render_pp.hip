@@ -314,7 +314,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 8))) 
 // Component of lane slot j (0, 1) of the gradient row.
 __device__ __forceinline__ int pp_component(int j, int lane) { return j * kWave + lane; }
 
-template <int DT, bool IDENT>
+// PER_T: a time per ray.
+template <int DT, bool IDENT, bool PER_T>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 8))) void render_pp_bwd_kernel(
     TreeArgs tr, InstArgs in, RayArgs ra, BackwardIO io, RecordArgs rec) {
     if (no_candidates(ra)) return;
@@ -322,7 +323,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 8))) 
     __shared__ float s_h[kBlock * K];
     __shared__ float s_brow[C], s_bgrow[CG];
     __shared__ float s_acc[2 * kWave];   // block sum of the lanes' basis-gradient components
-    const bool common_t = ra.t == nullptr;
+    constexpr bool common_t = !PER_T;
     if (common_t) stage_common_rows(tr, in, ra.t_scalar, s_brow, s_bgrow);
     if (threadIdx.x < 2 * kWave) s_acc[threadIdx.x] = 0.0f;
     __syncthreads();
@@ -451,14 +452,15 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 8))) 
                 // order; their leaf rows and basis gradients are summed per leaf later
                 const uint64_t hm = __ballot(has);
                 const int n_has = __popcll(hm);
-                const int at = n_has > 0 ? take_items(rec.counter, rec.cap, n_has, wrec, wend) : -1;
+                const int at = n_has > 0 ? take_items<record_block>(rec.counter, rec.cap, n_has, wrec, wend) : -1;
                 if (at >= 0) {
                     const RecordRun run = record_run(hm, has, leaf);
                     if (has) {
                         my_rec = (int)(at + lane_rank(hm));
                         rec.rec[2 * (int64_t)my_rec] =
                             make_int4(__float_as_int(gz0), __float_as_int(gz1), __float_as_int(gz2), __float_as_int(gx));
-                        const int nxt = run.count > 0 ? atomicExch(rec.head + record_list(rec, tr.n_leaves, leaf, at), my_rec + run.count - 1) : my_rec - 1;
+                        const int nxt = run.count > 0 ? atomicExch(rec.head + (PER_T ? record_list(rec, tr.n_leaves, leaf, at) : leaf),
+                                                               my_rec + run.count - 1) : my_rec - 1;
                         rec.rec[2 * (int64_t)my_rec + 1] = make_int4(nxt, (int)ray, __float_as_int(gy), __float_as_int(y));
                     }
                 }
@@ -670,7 +672,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) 
             }
             if (rec.head) {
                 const uint64_t hm = __ballot(has);
-                const int at = take_items(rec.counter, rec.cap, __popcll(hm), wrec, wend);
+                const int at = take_items<record_block>(rec.counter, rec.cap, __popcll(hm), wrec, wend);
                 if (at >= 0) {
                     const RecordRun run = record_run(hm, has, leaf);
                     if (has) {
@@ -1034,36 +1036,31 @@ static hipError_t pp_fwd_t(const TreeArgs& tr, const InstArgs& in, const RayArgs
 }
 
 template <int DT>
-static hipError_t pp_bwd_walk(const TreeArgs& tr, const InstArgs& in, const RayArgs& ra, const BackwardIO& io,
-                              const RecordArgs& rec, hipStream_t st) {
-    auto kern = in.identity ? render_pp_bwd_kernel<DT, true> : render_pp_bwd_kernel<DT, false>;
-    hipLaunchKernelGGL(kern, dim3(grid_for(kern, ra)), dim3(kBlock), 0, st, tr, in, ra, io, rec);
-    return hipGetLastError();
+static auto pp_bwd_walk_kernel(const InstArgs& in, const RayArgs& ra) {
+    return ra.t ? (in.identity ? render_pp_bwd_kernel<DT, true, true> : render_pp_bwd_kernel<DT, false, true>)
+                : (in.identity ? render_pp_bwd_kernel<DT, true, false> : render_pp_bwd_kernel<DT, false, false>);
 }
 
 template <int DT>
-static hipError_t pp_bwd_replay(const TreeArgs& tr, const InstArgs& in, const RayArgs& ra, const BackwardIO& io,
-                                const RecordArgs& rec, hipStream_t st) {
-    auto kern = ra.t ? (in.identity ? replay_pp_kernel<DT, true, true> : replay_pp_kernel<DT, false, true>)
-                     : (in.identity ? replay_pp_kernel<DT, true, false> : replay_pp_kernel<DT, false, false>);
-    hipLaunchKernelGGL(kern, dim3(grid_for(kern, ra)), dim3(kBlock), 0, st, tr, in, ra, io, rec);
-    return hipGetLastError();
+static auto pp_bwd_replay_kernel(const InstArgs& in, const RayArgs& ra) {
+    return ra.t ? (in.identity ? replay_pp_kernel<DT, true, true> : replay_pp_kernel<DT, false, true>)
+                : (in.identity ? replay_pp_kernel<DT, true, false> : replay_pp_kernel<DT, false, false>);
 }
 
 template <int DT>
 static hipError_t pp_bwd_t(const TreeArgs& tr, const InstArgs& in, const RayArgs& ra, const BackwardIO& io,
                            hipStream_t st) {
-    const int64_t cap =
-        ra.n <= (int64_t)INT32_MAX && tr.n_leaves > 0 && tr.n_leaves <= (int64_t)INT32_MAX ? io.record_cap : 0;
+    const RecordRoom room =
+        ra.n <= (int64_t)INT32_MAX && tr.n_leaves > 0 && tr.n_leaves <= (int64_t)INT32_MAX ? io.records : RecordRoom{0, 0};
     AdjointScratch sc;
-    const bool replay = replays(io.trace, io.trace.cap / 2, cap);
-    hipError_t e = adjoint_begin(tr, ra, io.nsamp, replay ? io.trace.head : nullptr, cap, st, sc,
-                                 ra.t && cap > 0 ? timed_split(tr.n_leaves, ra.n) : 0);
+    const bool replay = replays(io.trace, io.trace.cap / 2, room.least);
+    hipError_t e = adjoint_begin(tr, ra, io.nsamp, replay ? io.trace.head : nullptr, room, st, sc,
+                                 ra.t && room.most > 0 ? timed_split(tr.n_leaves, ra.n) : 0);
     const RecordArgs& rec = sc.rec;
-    if (e == hipSuccess && io.fresh) e = fresh_begin(tr, io, pp::ROW, rec, st);
-    if (e == hipSuccess) e = pp_bwd_walk<DT>(tr, in, sc.walk, io, rec, st);
-    if (e == hipSuccess && replay) e = pp_bwd_replay<DT>(tr, in, sc.replay, io, rec, st);
-    if (e == hipSuccess && cap > 0) {
+    if (e == hipSuccess)
+        e = adjoint_rays(pp_bwd_walk_kernel<DT>(in, ra), pp_bwd_replay_kernel<DT>(in, ra), replay, pp::ROW, tr, in, io,
+                         sc, st);
+    if (e == hipSuccess && rec.cap > 0) {
         auto kern = ra.t ? (in.identity ? reduce_pp_timed_kernel<DT, true> : reduce_pp_timed_kernel<DT, false>)
                          : (in.identity ? reduce_pp_records_kernel<DT, true> : reduce_pp_records_kernel<DT, false>);
         const int grid = ra.t ? leaf_grid(kern, tr.n_leaves << rec.split, 1) : leaf_grid(kern, tr.n_leaves);

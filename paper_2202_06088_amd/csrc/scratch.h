@@ -25,6 +25,7 @@ namespace neuvv {
 //
 // Rt has the types Status, Stream and Event, the status `ok`, and
 //   Status alloc(void**, size_t, Stream)   from the pool, in stream order
+//   static bool no_memory(Status)          whether alloc failed for want of memory
 //   Status free(void*, Stream)             to the pool, in stream order
 //   Status create(Event*)  void destroy(Event)
 //   Status record(Event, Stream)  Status wait(Stream, Event)
@@ -38,9 +39,10 @@ class KeptScratch {
     using Stream = typename Rt::Stream;
     using Event = typename Rt::Event;
     static constexpr size_t kSmallest = (size_t)64 << 10;
-    // the records of 200,000 rays (sixteen each, 32 bytes a record) still are kept
-    static constexpr size_t kLargest = (size_t)128 << 20;
-    static constexpr size_t kBytes = (size_t)512 << 20;
+    // Calls that need more run for some 300 us on the device and hide the host's 36 us; the event's packets between
+    // their kernels cost them more (640 x 360 per-point adjoint, 118 MiB: 297 us from the pool, 311 us kept).
+    static constexpr size_t kLargest = (size_t)64 << 20;
+    static constexpr size_t kBytes = (size_t)320 << 20;   // the smallest adjoints of eight streams, 34 MiB each
     static constexpr int kBlocks = 32;
 
     // The size of the block that serves a request: powers of two up to 1 MiB, then steps of 2 MiB (the smallest
@@ -95,6 +97,18 @@ class KeptScratch {
         b_[n_++] = b;
         *p = b.p;
         return Rt::ok;
+    }
+
+    // Scratch of a call: a kept block where `keep`, else from the pool. Where the device has no memory left, what is
+    // held here and not in use goes back first (waiting for it, so not where `graph`: the stream is captured).
+    Status serve(Rt& rt, void** p, size_t bytes, Stream stream, bool keep, bool graph) {
+        for (bool again = false;; again = true) {
+            *p = nullptr;
+            if (keep) (void)acquire(rt, p, bytes, stream);
+            if (*p) return Rt::ok;
+            const Status e = rt.alloc(p, bytes, stream);
+            if (!rt.no_memory(e) || again || graph || give_back(rt, stream) != Rt::ok) return e;
+        }
     }
 
     // Ends a call's use of p. False: not a kept block (the caller frees it).
