@@ -171,10 +171,22 @@ class VOctree:
 
     def rows_to_payload_f32(self, grad_leaf: torch.Tensor):
         """Leaf gradient rows -> the float32 payload layout of hh and wsig (and wgam), a
-        rearrangement only, for an element-wise optimizer step on float32 payload tensors."""
-        N = self.n_leaves
-        rows = grad_leaf.view(N, self.grad_row).detach().to(self.nodes.device, torch.float32).contiguous()
-        out = [torch.empty(N * (-(-R // 4) * 4), device=rows.device)
-               for R in (3 * self.K, self.C) + ((self.Cg,) if self.Cg > 0 else ())]
-        _lib.neuvv_unpack_grad_rows(self.K, self.C, self.Cg, self.layout, N, rows, *out)
+        rearrangement only, for an element-wise optimizer step on float32 payload tensors. The
+        results are where the rows are."""
+        N, K, C, G = self.n_leaves, self.K, self.C, self.Cg
+        rows = grad_leaf.view(N, self.grad_row)
+        parts = [(0, 3 * K), (3 * K, C)] + ([(3 * K + C, G)] if G > 0 else [])
+        if rows.is_cuda and not (torch.is_grad_enabled() and rows.requires_grad):
+            with torch.cuda.device(rows.device):   # (the library launches on the current device)
+                rows = rows.to(torch.float32).contiguous()
+                out = [torch.empty(N * (-(-R // 4) * 4), device=rows.device) for _, R in parts]
+                _lib.neuvv_unpack_grad_rows(K, C, G, self.layout, N, rows, *out)
+            return tuple(out)
+        out = []   # rows in host memory, or part of a graph: the same in torch
+        for start, R in parts:
+            ng = -(-R // 4)
+            a = torch.nn.functional.pad(rows[:, start:start + R].float(), (0, 4 * ng - R))
+            if self.layout == _lib.LAYOUT_VEC_SOA:
+                a = a.view(N, ng, 4).permute(1, 0, 2)
+            out.append(a.reshape(-1).contiguous())
         return tuple(out)
