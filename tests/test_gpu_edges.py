@@ -365,3 +365,29 @@ def test_captured_calls(tiny):
         assert all(rel_err(a.cpu().numpy(), b.cpu().numpy()) <= 1e-5 for a, b in zip(grads, wg))
         again = ops.render(tree, oo, dd, 4.0, None, 1e-4, 64)
         assert all(torch.equal(a, b) for a, b in zip(again, want))
+
+
+@pytest.mark.parametrize("traced", [False, True])
+@pytest.mark.parametrize("n", [16_383 * 64, 16_384 * 64 - 37, 16_384 * 64, 16_384 * 64 + 1])
+def test_cull_groups(tiny, n, traced):
+    """Lists of rays on both sides of the size (16,384 chunks of 64) from which a wavefront culls more of them at a time,
+    ragged at the end: the outputs are those of the same rays as an image, bit for bit, gradients up to summation
+    order, rows written by the call itself as well as added."""
+    sc, o, d, g, _ = tiny
+    shift = 1237   # (rays of every part of the view in each group)
+    pick = (np.arange(n) * shift) % o.shape[0]
+    tree, oo, dd, gg = upload(sc), tdev(o[pick]), tdev(d[pick]), tdev(g[pick])
+    got = []
+    for w in (0, 1024):
+        trace = ops.Trace(n, n, oo.device) if traced else None
+        out = ops.render(tree, oo, dd, 4.0, None, 1e-4, w, trace=trace)
+        for grads in (None, tree.zero_grads()):
+            got.append(out + ops.render_backward(tree, oo, dd, out[0], out[1], out[3], gg, None, 4.0, None, 1e-4, w,
+                                                 grads=grads, trace=trace))
+    torch.cuda.synchronize()
+    assert int(got[0][3].sum()) > n // 4
+    for other in got[1:]:
+        for a, b in zip(got[0][:4], other[:4]):
+            assert torch.equal(a, b)
+        for a, b in zip(got[0][4:], other[4:]):
+            assert rel_err(a.cpu().numpy(), b.cpu().numpy()) <= 1e-4   # the gradients' bar: lists of thousands of records
