@@ -2,7 +2,7 @@
 // dtype/K/C dispatch and error reporting around the kernels. Nothing here
 // keeps pointers to caller buffers beyond a call. The render calls take
 // their scratch (work-queue counters, candidate lists, adjoint records) from
-// a stream-ordered memory pool the library keeps per device (render.hip),
+// blocks kept per stream and a memory pool per device (render.hip),
 // except neuvv_render_noalloc, which uses a fixed device array.
 #include <hip/hip_runtime.h>
 #include <stdarg.h>

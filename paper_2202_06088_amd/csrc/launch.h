@@ -111,9 +111,12 @@ hipError_t launch_pack_rows(int R, int dtype, int layout, int64_t n, const float
                             void* out, hipStream_t stream);
 hipError_t launch_pack(int K, int C, int dtype, int layout, int64_t n, const float* hh_in, const float* wsig_in,
                        const int64_t* slot_of_input, void* hh_out, void* wsig_out, hipStream_t stream);
-// The brick directory of a depth-D node table (directory_entries(D) entries).
+// Leaf gradient rows to the float32 payload layout.
 hipError_t launch_unpack_rows(int K, int C, int Cg, int layout, int64_t n, const float* rows, float* hh, float* wsig,
                               float* wgam, hipStream_t stream);
+// Clears n floats of gradient rows (a multiple of 4, 16-byte aligned).
+hipError_t launch_zero_rows(float* rows, int64_t n, hipStream_t stream);
+// The brick directory of a depth-D node table (directory_entries(D) entries).
 hipError_t launch_build_directory(const int4* nodes, int depth, int32_t* dir, hipStream_t stream);
 
 // Lighting (Sec. 5.2): Gaussian taps of the shadow-map low-pass, and the light.
@@ -158,11 +161,10 @@ constexpr size_t kFixedScratchBytes = kListHeaderBytes + (size_t)kFixedScratchSl
 hipError_t fixed_scratch(void** p);
 
 // Stream-ordered scratch of a call (work-queue counters, candidate lists,
-// records): from the blocks kept for its stream when it is small, else from a
-// memory pool the library keeps per device, which holds on to its memory
-// between calls instead of returning it at every synchronisation.
-// release_kept frees the kept blocks of the current device that no call holds.
-hipError_t launch_zero_rows(float* rows, int64_t n, hipStream_t stream);
+// records): from the blocks kept for its stream when it is small (scratch.h),
+// else from a memory pool the library keeps per device, which holds on to its
+// memory between calls instead of returning it at every synchronisation.
+// release_kept gives back to the current device what no call holds of both.
 hipError_t work_alloc(void** p, size_t bytes, hipStream_t stream);
 hipError_t work_free(void* p, hipStream_t stream);
 hipError_t release_kept();
