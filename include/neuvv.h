@@ -19,7 +19,8 @@
  *     adjoints 5 KiB) plus a candidate list of 4 bytes per work slot
  *     (rounded up to 64 slots; the adjoint of a traced forward takes two);
  *     the adjoints also take the records of their two-phase reduction (4
- *     bytes per leaf plus 32 bytes per record of room, see there), and
+ *     bytes per leaf, up to 512 KiB with Cg > 0 and a time per ray on a tree
+ *     of fewer leaves, plus 32 bytes per record of room, see there), and
  *     neuvv_render_multi the segment lists of its instances (see there). Scratch
  *     is taken in stream order on the call's stream, from blocks the library
  *     keeps for that stream (scratch up to 64 MiB; see neuvv_release_scratch)
