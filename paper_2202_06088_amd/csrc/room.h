@@ -53,7 +53,8 @@ struct RecordRoom {
 // 2^20, are what a call asks for at least. Rays of a close view may all hit,
 // six or more samples each on average (scattering 2.7 M samples of 427,000 rays
 // one by one cost 1.7 ms), so up to 2^23 records, 256 MiB, it asks for sixteen
-// per ray. Below 2^31.
+// per ray (up to 2^24, 512 MiB, 2.1 M rays with half of their samples traced took
+// 1042 us instead of 1059, and no other call less). Below 2^31.
 __host__ __device__ inline RecordRoom record_room(int64_t n_rays, int64_t trace_cap) {
     const int64_t most = 1ll << 23, last = INT32_MAX;
     int64_t least = 2 * n_rays > trace_cap ? 2 * n_rays : trace_cap;
